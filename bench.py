@@ -1,16 +1,18 @@
 """Throughput of the per-head spectral-norm path on one MI355X.
 
 One step = one spectral_step call: all layers, all query heads, n_iter
-power-iteration steps each (one W_K sweep from v, then per step one fused W_Q
-sweep and one fused W_K sweep), plus the per-layer E4M3 scale.  Weights,
+power-iteration steps each, plus the per-layer E4M3 scale: by default as
+spectral_step runs such a call (two or more iterations: Gram matrices and the
+iteration in d_h-space, one workgroup per head), with ``--form chain`` as
+sweeps over the weights (one W_K sweep from v, then per step one fused W_Q
+sweep and one fused W_K sweep).  The iterates are the same.  Weights,
 start vectors and outputs are resident in HBM before the timed region.
 
-    python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload KEY] [--form chain|gram]
+    python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload KEY] [--form step|chain|gram]
 
 Prints one JSON line.  ``value`` is heads*iterations per second over all
 layers; ``roofline`` reports the dominant kernel against the HBM peak (the
-W_Q sweep of the default sweep chain; the Gram sweep with ``--form gram``,
-which runs the same iterates through d_h x d_h Gram matrices);
+per-head kernel of the Gram form; the W_Q sweep with ``--form chain``);
 ``cpu_baseline`` times the float64 oracle on host cores over a bounded sample
 of the same workload.
 """
@@ -36,6 +38,9 @@ ARITHMETIC = {
              "normalisation and the scale fp32",
     "gram": "Gram matrices: bf16 (fp32: fp32) matrix-core products, fp32 accumulation; d_h-space iteration, norms "
             "and the scale fp32; final sweeps as in the chain",
+    "step": "Gram matrices: bf16 (fp32: fp32) matrix-core products, summed in two levels with the rounding of the "
+            "second kept; d_h-space iteration, norms and the scale fp32; first product with v: bf16 matrix cores on two "
+            "(groups of 6 and more, d_h 64/128) or three bf16 parts of each fp32 vector; final sweeps as in the chain",
     "layer": "fp32 FMA on the weights (bf16 widened exactly), fp32 norms and scale",
 }
 METRIC = "heads·iters/sec (all layers) and achieved HBM GB/s vs MI355X peak"
@@ -61,8 +66,9 @@ def parse():
     p.add_argument("--q-strips", type=int, default=0, help="column strips per head in the W_Q sweep (0 = auto)")
     p.add_argument("--k-strips", type=int, default=0, help="column strips per KV head in the W_K sweep (0 = auto)")
     p.add_argument("--flags", type=int, default=0, help="sn_params.flags (SN_FLAG_* bits)")
-    p.add_argument("--form", choices=("chain", "gram", "layer", "fp8"), default="chain",
-                   help="gram: the Gram form of the iteration (adds SN_FLAG_GRAM); layer: the paper-literal "
+    p.add_argument("--form", choices=("step", "chain", "gram", "layer", "fp8"), default="step",
+                   help="step: spectral_step as a program calls it; chain: the sweeps over the weights (their "
+                        "automatic strip counts given explicitly, which keeps a call on them); gram: the Gram form of the iteration (adds SN_FLAG_GRAM); layer: the paper-literal "
                         "layer-level estimator (one u, v per layer, spectral_step_layer); fp8: the E4M3 logit "
                         "consumer of the scale (spectral_logits_fp8) on --seq tokens per layer")
     p.add_argument("--seq", type=int, default=1024, help="tokens per layer of the fp8 form")
@@ -133,7 +139,7 @@ def source_hash() -> str:
 
 def measured_traffic(kernel: str = ""):
     """HBM bytes per launch of the W_Q sweep (or of ``kernel``, a sub-entry
-    such as "gram_sweep") from the committed rocprofv3 counter summary, if it
+    such as "heads") from the committed rocprofv3 counter summary, if it
     was taken on the current kernel source; else None."""
     try:
         with open(TRAFFIC_FILE) as f:
@@ -265,13 +271,26 @@ def cpu_baseline_fp8(wl, budget_s: float, seq: int):
                       f"float64 numpy, {dt:.1f} s", **host_info()}
 
 
+def chain_strips(wl, q_strips: int, k_strips: int) -> tuple[int, int]:
+    """The automatic strip counts of the sweeps (workgroup items aimed for over the heads, at least four tiles of
+    128 bytes per strip), or the counts given."""
+    tiles = -(-wl.d_model * wl.elem_bytes // 128)
+    most = max(1, tiles // 4)
+    g = wl.group
+    chunks = -(-g // 8) if g > 1 else 1
+    units = wl.n_layers * wl.n_kv * chunks
+    mfma = wl.dtype == "bf16" and wl.head_dim in (64, 128) and g >= 3
+    q = min(most, -(-10240 // wl.n_heads))
+    k = min(most, max(1, 2048 // units) if mfma else -(-4096 // units))
+    return q_strips or q, k_strips or k
+
+
 def context_lines(args, flags: int) -> dict:
     """Calls reported beside the headline (context, not the metric): n_iter
-    = 1 from cold vectors (one pure stream of W_K, W_Q, W_K); for the sweep
-    chain, the Gram form on the same weights and iteration count; and the
-    per-step scenario of Sec. 5.1 (planted 0.98-gap spectra iterated to
-    tolerance 1e-4 untimed, weights perturbed, then one timed warm call), in
-    the chosen form and, for the chain, in the Gram form too."""
+    = 1 from cold vectors (one pure stream of W_K, W_Q, W_K); the sweeps on
+    the same weights and iteration count; and the per-step scenario of Sec.
+    5.1 (planted 0.98-gap spectra iterated to tolerance 1e-4 untimed, weights
+    perturbed, then one timed warm call), in the default and the Gram form."""
     import torch
 
     from paper_2602_18851_amd import Spectral
@@ -299,13 +318,13 @@ def context_lines(args, flags: int) -> dict:
     est.close()
 
     from paper_2602_18851_amd.spectral import SN_FLAG_GRAM
-    if not flags & SN_FLAG_GRAM and wl.head_dim >= 16:
-        # the Gram form on the same weights and iteration count: the same
-        # iterates through d_h x d_h Gram matrices, weights read about four
-        # times per call instead of twice per iteration
+    if args.form != "chain" and not args.q_strips and not args.k_strips:
+        # the sweeps on the same weights and iteration count: the same iterates,
+        # every iteration streaming all weights
         n_iter = args.n_iter or wl.n_iter
-        est = Spectral(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha,
-                       flags=flags | SN_FLAG_GRAM)
+        qs, ks = chain_strips(wl, 0, 0)
+        est = Spectral(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha, q_strips=qs,
+                       k_strips=ks)
         v = start_vectors(wl, dev)
         for _ in range(3):
             est.step(wq, wk, v, n_iter)
@@ -320,15 +339,13 @@ def context_lines(args, flags: int) -> dict:
         prof = est.profile_read()
         est.profile(False)
         ms = e0.elapsed_time(e1) / n
-        g_ms, g_n = prof["gram_sweep"]
-        # every weight read once, the upper-triangle 16 x 16 blocks written once per query / key head
-        g_bytes = q_bytes + k_bytes + (H + wl.n_layers * wl.n_kv) * wl.head_dim * (wl.head_dim + 16) // 2 * 4
-        out["gram_form"] = {"ms": ms, "heads_iters_per_s": H * n_iter / (ms * 1e-3), "n_iter": n_iter,
-                            "gram_sweep_ms": g_ms / g_n,
-                            "gram_sweep_GBps": g_bytes / (g_ms / g_n * 1e-3) / 1e9,
-                            "gram_sweep_frac_of_peak": g_bytes / (g_ms / g_n * 1e-3) / 1e9 / HBM_PEAK_GBPS,
-                            "note": "SN_FLAG_GRAM on the same weights; not the headline, whose iterations each "
-                                    "stream the weights"}
+        s_ms, s_n = prof["q_sweep"]
+        s_bytes = q_bytes + H * 2 * wl.head_dim * 4
+        out["sweep_chain"] = {"ms": ms, "heads_iters_per_s": H * n_iter / (ms * 1e-3), "n_iter": n_iter,
+                              "q_sweep_ms": s_ms / s_n, "q_sweep_GBps": s_bytes / (s_ms / s_n * 1e-3) / 1e9,
+                              "q_sweep_frac_of_peak": s_bytes / (s_ms / s_n * 1e-3) / 1e9 / HBM_PEAK_GBPS,
+                              "note": "the sweep form of the same calls (explicit strip counts): every iteration "
+                                      "streams the weights; what calls of one iteration run"}
         est.close()
     del wq, wk, v
     torch.cuda.empty_cache()
@@ -638,6 +655,11 @@ def main():
     scale = torch.empty(wl.n_layers, dtype=torch.float32, device=dev)
     iters = torch.empty(wl.n_layers, wl.n_q, dtype=torch.int32, device=dev)
     gram = args.form == "gram"
+    # calls of two or more iterations with automatic strips run the Gram form with one workgroup per head
+    heads = gram or (args.form == "step" and n_iter > 1 and wl.head_dim >= 16 and not args.q_strips
+                     and not args.k_strips and not args.flags & 1)
+    if args.form == "chain":
+        args.q_strips, args.k_strips = chain_strips(wl, args.q_strips, args.k_strips)
     flags = args.flags | (SN_FLAG_GRAM if gram else 0) | (SN_FLAG_LAYER if layer else 0)
     est = Spectral(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha, tol=0.0,
                    q_strips=args.q_strips, k_strips=args.k_strips, flags=flags)
@@ -715,16 +737,14 @@ def main():
         dom_flops = None
         call_bytes = n_iter * (2 * (q_bytes + k_bytes) + col_buf) + 12 * wl.d_model * wl.n_layers
         H = wl.n_layers  # one estimate per layer
-    elif gram:
-        # Gram sweep: every weight read once, the upper-triangle 16 x 16 Gram
-        # blocks written once per query / key head (d_h (d_h + 16) / 2 floats)
-        units = H + wl.n_layers * wl.n_kv
-        g_out = units * wl.head_dim * (wl.head_dim + 16) // 2 * 4
-        dom_name, dom_kind = "gram_sweep (G = R R^T of every head, matrix cores)", "gram_sweep"
-        dom_alg = q_bytes + k_bytes + g_out
+    elif heads:
+        # heads_kernel: with grouped heads every W_Q element read once, else every W_Q and W_K element
+        units = H + (wl.n_layers * wl.n_kv if wl.group == 1 else 0)
+        dom_name, dom_kind = "heads_kernel (Gram matrix and iteration of every head)", "gram_iterate"
+        dom_alg = q_bytes + (k_bytes if wl.group == 1 else 0)
         dom_flops = 2.0 * units * wl.head_dim * (wl.head_dim + 16) / 2 * wl.d_model
-        # first W_K sweep, Gram sweep, final W_K sweep, Gram blocks read back, vectors
-        call_bytes = 3 * k_bytes + q_bytes + 2 * g_out + 12 * wl.d_model * H
+        # W_Q once, W_K for its Gram matrices and for the final sweep, vectors in and out
+        call_bytes = 2 * k_bytes + q_bytes + 8 * wl.d_model * H
     else:
         dom_name, dom_kind = "q_sweep (fused W_Q sweep)", "q_sweep"
         dom_alg = q_bytes + H * 2 * wl.head_dim * 4          # weights + z in + y out, per launch
@@ -760,7 +780,7 @@ def main():
             "cache": "1 GiB written before every timed call, calls timed one by one" if args.flush
                      else "calls back to back, no flush",
         },
-        "arithmetic": ARITHMETIC["gram" if gram else "layer" if layer else "chain"],
+        "arithmetic": ARITHMETIC["step" if heads else "gram" if gram else "layer" if layer else "chain"],
         "effective_GBps": call_bytes / (ms * 1e-3) / 1e9,
         "effective_frac_of_peak": call_bytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBPS,
         "call_bytes": call_bytes,
@@ -773,7 +793,7 @@ def main():
             "peak": HBM_PEAK_GBPS,
             "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBPS,
-            "traffic": None if layer else measured_traffic("gram_sweep" if gram else ""),
+            "traffic": None if layer else measured_traffic("heads" if heads else ""),
             "algorithmic_bytes_per_launch": dom_alg,
             "avg_launch_ms": dom_avg_ms,
             "launches": dom_n,

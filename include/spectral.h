@@ -81,7 +81,9 @@ typedef struct {
                           Gram matrices of the tail (see spectral_step; 240 MB
                           at 80 x 64 heads of d_h 128, d 8192).                   */
   int32_t q_strips;    /* column strips per head in the W_Q sweep; 0 = automatic  */
-  int32_t k_strips;    /* column strips per KV head in the W_K sweep; 0 = auto    */
+  int32_t k_strips;    /* column strips per KV head in the W_K sweep; 0 = auto.
+                          A count given here keeps spectral_step on the sweeps
+                          (without SN_FLAG_GRAM).                               */
   int32_t flags;       /* SN_FLAG_* bits; 0 for the defaults                      */
 } sn_params;
 
@@ -90,16 +92,20 @@ typedef struct {
  * per KV head).  Results agree to rounding; the flag exists for comparison. */
 #define SN_FLAG_VALU_K_SWEEP 1
 
-/* Gram form of the same iteration.  For one head, ||W^Q z||^2 = z^T G_Q z
+/* Gram form of the same iteration, for every call of the context (without
+ * the flag spectral_step chooses; see there).  For one head, ||W^Q z||^2 = z^T G_Q z
  * with G_Q = Q_h Q_h^T (d_h x d_h), and ||W^K y||^2 = y^T G_K y with
  * G_K = K_j K_j^T, so the step maps of Sec. 4.1 factor through the two Gram
- * matrices:  y = G_Q z / sigma,  z_next = G_K y / ||v'||.  With this flag one
+ * matrices:  y = G_Q z / sigma,  z_next = G_K y / ||v'||.  One
  * sweep over all weights forms G_Q for every query head and G_K for every
  * key head on the matrix cores, the iteration runs in d_h-space, and one
  * final W_K sweep (plus one W_Q sweep when u is requested) maps the last y
- * (z) back to v (u).  The iterates, sigma, u and v are those of the default
- * path up to rounding; the weights are read about four times per call
- * instead of twice per iteration.  Needs head_dim >= 16.  The workspace
+ * (z) back to v (u).  The iterates, sigma, u and v are those of the sweeps
+ * up to rounding; W_K is read twice and W_Q once (twice with u) per call
+ * instead of once each per iteration.  A head whose rows nearly cancel
+ * (sigma^2 or ||v'||^2 below 1/16 of its terms' squares), where the products
+ * in d_h-space would lose digits, or whose weights lie near the ends of the
+ * float range, is iterated on its weights instead.  Needs head_dim >= 16.  The workspace
  * grows by the Gram partials, 2 d_h (d_h + 16) bytes per query or key head
  * and column strip (spectral_workspace_bytes gives the total). */
 #define SN_FLAG_GRAM 2
@@ -141,6 +147,10 @@ SN_API int spectral_init(sn_ctx** ctx, const sn_shape* shape, const sn_params* p
  *              -1 if the start vector is zero or not finite (sigma = NaN,
  *              v unchanged, u = 0); -2 if M v = 0 (sigma = 0, v normalised
  *              start vector, u = 0).
+ * Calls of a fixed count n_iter >= 2 with head_dim >= 16, automatic strips
+ * and no SN_FLAG_VALU_K_SWEEP run the Gram form (see SN_FLAG_GRAM), whose
+ * iterates are those of the sweeps up to rounding; the others run n_iter
+ * pairs of sweeps over the weights.
  * The call is queued asynchronously on the context's stream and never waits
  * on the host.  With tol > 0 and head_dim >= 16, the first two steps (the
  * fewest the stopping rule allows) run as sweeps over all heads; then one

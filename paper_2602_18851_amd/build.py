@@ -15,7 +15,7 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SOURCES = [os.path.join(HERE, "csrc", name)
-           for name in ("spectral.hip", "sweeps.hip", "gram.hip", "layer_form.hip", "logits_fp8.hip", "calibration.cpp")]
+           for name in ("spectral.hip", "sweeps.hip", "gram.hip", "gram_heads.hip", "layer_form.hip", "logits_fp8.hip", "calibration.cpp")]
 INCLUDE = os.path.join(ROOT, "include")
 LIB_PATH = os.path.join(HERE, "libspectral.so")
 ARCH = "gfx950"

@@ -1,0 +1,894 @@
+// The Gram form with one workgroup per head (gfx950, wave64): Gram matrices
+// and the whole d_h-space iteration of a head without leaving the compute
+// unit, so that no query Gram matrix is ever written to memory.
+//
+// Per head the arithmetic is that of gram.hip (G_Q = Q Q^T, G_K = K K^T; one
+// step is w = G_Q z, sigma^2 = z^T w, y = w / sigma, t = G_K y, ||v'||^2 =
+// y^T t, z = t / ||v'||); what differs is where it runs.
+//   units_kernel (grouped heads, or few heads): one workgroup per key head,
+//     chunk of query heads and column strip reads its part of K_j once and
+//     forms G_K (chunk 0) and z0 = K_j v, ||v||^2 for the heads of the chunk.
+//     With fewer heads than compute units it also forms the G_Q, in column
+//     strips, so that the whole chip streams.
+//   heads_kernel: one workgroup per query head reads Q_h once, forms G_Q in
+//     registers, loads G_K (or, with g = 1, streams K_h first and forms G_K,
+//     z0 and ||v|| itself), iterates to the count or the tolerance and leaves
+//     z / sigma and y / ||v'|| of the last step, which the final sweeps map to
+//     u and v, already normalised.
+// Against n_iter pairs of sweeps, whole calls on one box: 70B GQA shape, 30
+// iterations 56.1 -> 2.56 ms; Llama-2-7B shape 10.5 -> 0.66 ms; GPT-2 XL shape
+// with u 2.55 -> 0.32 ms; GPT-2 small, 20 iterations 405 -> 78 us; 5
+// iterations of 144 heads, d 3001, 261 -> 74 us.  Against the strip-wise Gram
+// form (gram.hip: one wave per Gram matrix, all matrices through memory) the
+// 70B call went from 3.28 to 2.56 ms.  heads_kernel streams at 6.7 TB/s there
+// with two steps and at 5.9 TB/s with 30.
+//
+// Streaming.  The workgroup's four waves share a ring of row tiles (d_h rows
+// x 128 bytes) in LDS, filled by buffer loads straight to LDS; one bare
+// barrier per tile says that the tile has landed and that its predecessor's
+// slot is free, and the loads of the next NST - 1 tiles stay in flight across
+// it.  The upper-triangle 16 x 16 blocks of G are split over the waves by
+// quadrants (waves 0 and 1: the two diagonal triangles; waves 2 and 3: halves
+// of the off-diagonal square), so a wave reads at most 6 of the 8 row blocks
+// of a tile (d_h = 128) and no sum over waves is needed.  The z0 products
+// (slots: heads x bf16 parts of v) go to waves 2 and 3, which hold fewer
+// blocks.
+//
+// Precision.  z^T G z rounds relative to b = sum_i z_i^2 G_ii, a sweep of Q
+// relative to sqrt(b): a head whose rows nearly cancel in Q^T z (or K^T y)
+// would lose digits here that the sweeps keep.  Every step therefore compares
+// sigma^2 and ||v'||^2 with b; a head that falls under kCancel * b, whose
+// Gram diagonal is near the ends of the float range, or whose values are not
+// finite is iterated again from z0 by reading Q_h and K_j directly
+// (direct_sweep), in the order of the sweep form and with its stopping rules.
+#include <hip/hip_runtime.h>
+
+#include <cmath>
+#include <cstdint>
+#include <type_traits>
+
+#include "gram_device.h"
+
+namespace sn {
+namespace {
+
+constexpr int kHThreads = 64 * kHWaves;
+// sigma^2 = z^T G z carries about 1e-7 b of rounding: at b / 16 sigma keeps a
+// relative error of about 1e-6, what the grouped sweeps' bf16 halves leave.
+// Rows that do not cancel have sigma^2 near b or above.
+constexpr float kCancel = 1.f / 16.f;
+constexpr float kGramMin = 1e-26f, kGramMax = 1e34f;  // diagonal range where no product under- or overflows
+constexpr float kTiny = 1e-30f;                       // smallest sigma^2, ||v'||^2 taken from Gram products
+
+template <typename T, int DH>
+struct HShape {
+  static constexpr int ES = sizeof(T);
+  static constexpr int VEC = 16 / ES;
+  static constexpr int TC = 128 / ES;               // columns per tile
+  static constexpr int RB = DH / 16, NB = RB * (RB + 1) / 2;
+  static constexpr int STAGE = DH * 128;            // bytes of one tile
+  static constexpr int NST = DH == 128 ? 4 : DH == 64 ? 7 : 8;  // ring slots: with the start vectors' at most 72 KB
+  static constexpr int VROW = TC * 4;               // bytes of one start vector's columns of a tile
+  static constexpr int VCH = VROW / 16;             // ... in 16-byte chunks
+  static constexpr int VST = 2048;                  // start vectors of a tile: 8 heads (bf16) or 16 (fp32)
+  static constexpr int RING = NST * (STAGE + VST);
+  static constexpr int NI = DH / 8;                 // 1 KB load instructions per tile
+  static constexpr int NR = RB > 1 ? RB / 2 : 1;    // row blocks of a diagonal triangle
+  static constexpr int NC = RB >= 4 ? RB / 4 : 1;   // column blocks of an off-diagonal half
+  static constexpr int NTRI = NR * (NR + 1) / 2;
+  static constexpr int NACC = NTRI > NR * NC ? NTRI : NR * NC;
+  static constexpr int NZ = RB >= 4 ? RB / 2 : RB;  // row blocks of z0 per wave (2 and 3, or 2 alone)
+  static constexpr int P = DH + 1;                  // LDS row pitch of a whole Gram matrix
+  static constexpr int RPT = DH / 16;               // rows (and columns) per thread in the iteration
+  static constexpr int BIG = RING > DH * P * 4 ? RING : DH * P * 4;
+};
+
+// What a wave computes: its blocks of G and its row blocks of z0.
+template <typename S>
+struct Role {
+  bool tri, rect;
+  int r0, c0;  // triangle: first row block; off-diagonal half: rotation of its rows, first column block
+  __device__ __forceinline__ explicit Role(int wv) {
+    tri = wv < 2 && wv * S::NR < S::RB;
+    rect = wv >= 2 && (S::RB >= 4 || (wv == 2));
+    r0 = tri ? wv * S::NR : (wv - 2) * S::NC;
+    c0 = S::RB >= 4 ? S::NR + (wv - 2) * S::NC : S::RB - 1;
+  }
+  // off-diagonal half: row block of its i-th row operand (each of the two
+  // waves starts at its own share of z0)
+  __device__ __forceinline__ int row(int i) const { return S::RB >= 4 ? (r0 + i) & (S::NR - 1) : 0; }
+};
+
+__device__ __forceinline__ void lds_fence() { asm volatile("" ::: "memory"); }
+__device__ __forceinline__ void bare_barrier() {
+  lds_fence();
+  __builtin_amdgcn_s_barrier();
+  lds_fence();
+}
+
+template <int N>
+__device__ __forceinline__ void wait_vm() {  // at most N vector-memory operations outstanding
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+
+template <typename T>
+__device__ __forceinline__ f32x4 gram_mfma(const u32x4& a, const u32x4& b, f32x4 c) {
+  if constexpr (sizeof(T) == 2) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                   0, 0);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[e]), __uint_as_float(b[e]), c, 0, 0, 0);
+    return c;
+  }
+}
+
+// Zeroes the elements of a 16-byte chunk at positions >= nval.
+template <int ES>
+__device__ __forceinline__ void mask_chunk(u32x4& x, int nval) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if constexpr (ES == 2)
+      x[e] &= (2 * e < nval ? 0x0000ffffu : 0u) | (2 * e + 1 < nval ? 0xffff0000u : 0u);
+    else
+      x[e] &= e < nval ? 0xffffffffu : 0u;
+  }
+}
+
+// The start vectors of a key stream: `heads` rows of d floats at `rows`.  Slot
+// s of the z0 products is head s / np, part s % np of its bf16 split (fp32
+// weights: one part, the vector itself).
+struct VSlots {
+  const float* rows;
+  int heads, np;
+};
+
+// Streams tiles t0 .. t1 - 1 of one d_h x d row block through the ring and
+// accumulates this wave's blocks of R R^T (GRAM); with Z also its row blocks
+// of z0 and the sums of squares of its slot's columns.  The start vectors'
+// columns ride in the ring beside their tile (chunk c of head i at slot
+// c ^ vswz(i)), as 16-byte loads where their alignment allows, else as 4-byte
+// ones.
+template <typename S>
+__device__ __forceinline__ int vswz(int i) {
+  return S::ES == 2 ? 2 * (i & 7) : i & 7;
+}
+
+template <typename T, int DH, bool Z, bool GRAM>
+__device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d, int t0, int t1, int seed,
+                                             uint8_t* ring, int wv, int lane, const Role<HShape<T, DH>>& role,
+                                             const VSlots& vs, f32x4 (&acc)[HShape<T, DH>::NACC],
+                                             f32x4 (&zacc)[HShape<T, DH>::NZ], float& nrm) {
+  using S = HShape<T, DH>;
+  constexpr int ISS = S::NI < kHWaves ? S::NI : kHWaves;  // waves that issue tile loads
+  constexpr int OWN = S::NI / ISS;
+  const uint32_t nrec = (uint32_t)((((int64_t)(DH - 1) * ld + d) * S::ES + 15) & ~int64_t(15));
+  const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(blk, nrec);
+  const uint32_t row_bytes = (uint32_t)(ld * S::ES);
+  const int q = lane >> 4, s = lane & 15;
+  const int n = t1 - t0;
+  if (n <= 0) return;
+  // whole tiles from a staggered start, as in the sweeps; the ragged last tile
+  // of the block (columns past d) comes last, in a copy of the loop body
+  const int n_whole = min(t1, d / S::TC) - t0;
+  const int rot = n_whole > 0 ? (int)((((uint32_t)seed * 2654435761u) >> 16) % (uint32_t)n_whole) : 0;
+  auto tile_at = [&](int i) {
+    const int u = rot + i;
+    return t0 + (i >= n_whole ? i : u >= n_whole ? u - n_whole : u);
+  };
+  const int sr = lane >> 3, p = lane & 7;
+  uint8_t* vring = ring + S::NST * S::STAGE;
+  const __amdgpu_buffer_rsrc_t vrsrc = make_rsrc(vs.rows, Z ? (uint32_t)vs.heads * (uint32_t)d * 4u : 0u);
+  const bool vec = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(vs.rows) & 15) == 0;
+  const int rpi = vec ? 64 / S::VCH : 16 / S::VCH > 0 ? 16 / S::VCH : 1;   // start-vector rows per load instruction
+  const int nvi = Z ? (vs.heads + rpi - 1) / rpi : 0;                      // load instructions of a tile's rows
+  const int vfirst = (wv + 2) & 3;                                         // this wave's: vfirst, vfirst + 4
+  const int vown = nvi > vfirst + 4 ? 2 : nvi > vfirst ? 1 : 0;
+  auto issue = [&](int i) {
+    const int slot = i % S::NST, t = tile_at(i);
+    if (wv < ISS) {
+      uint8_t* dst = ring + slot * S::STAGE;
+      const uint32_t col = (uint32_t)t * 128u;
+#pragma unroll
+      for (int jj = 0; jj < OWN; ++jj) {
+        const int j = wv * OWN + jj;
+        const uint32_t voff = (uint32_t)sr * row_bytes + col + 16u * (uint32_t)(p ^ stage_swz(8 * j + sr));
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(dst + 1024 * j), 16, voff, 8u * j * row_bytes, 0,
+                                                 kStreamPolicy);
+      }
+    }
+    if constexpr (Z) {
+      for (int x = vfirst; x < nvi; x += 4) {
+        const int ln = vec ? lane : lane >> 2;  // 16-byte slot of this lane within the instruction
+        const int row = x * rpi + ln / S::VCH, c = (ln % S::VCH) ^ vswz<S>(row);
+        const uint32_t voff = (uint32_t)row * (uint32_t)d * 4u + (uint32_t)t * S::VROW + 16u * (uint32_t)c;
+        uint8_t* dst = vring + slot * S::VST;
+        if (vec)
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(vrsrc, (lds_void*)(dst + 1024 * x), 16, voff, 0, 0, 0);
+        else
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(vrsrc, (lds_void*)(dst + 256 * x), 4, voff + 4u * (lane & 3), 0, 0,
+                                                   0);
+      }
+    }
+  };
+
+#pragma unroll 1
+  for (int i = 0; i < S::NST - 1; ++i)
+    if (i < n) issue(i);
+  // Two-level sums: the products of about n / 16 tiles (fp32, four times the
+  // instructions per tile: n / 32) are summed from zero and then added to the
+  // totals with the rounding error of that addition kept (two-sum).  One
+  // accumulation of the matrix cores errs by 0.57 ulp rms, and unlike an error
+  // within a sweep one in G or z0 is not averaged over the iterations: with one
+  // chain over all columns the error of v was 2.5e-6 (d = 768, fp32, 20
+  // iterations) against 2e-7 in the sweeps.
+  const int flush = S::ES == 2 ? (n + 15) / 16 : (n + 31) / 32;
+  f32x4 cur[S::NACC], err[S::NACC], zcur[S::NZ];
+#pragma unroll
+  for (int x = 0; x < S::NACC; ++x) cur[x] = err[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int x = 0; x < S::NZ; ++x) zcur[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto add_up = [](f32x4& total, f32x4& part, f32x4& lost) {
+    const f32x4 sum = total + part, b = sum - total;
+    lost += (total - (sum - b)) + (part - b);
+    total = sum;
+    part = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  int left = flush;
+  auto body = [&](int i, auto ragged_tag) {
+    constexpr bool RAGGED = decltype(ragged_tag)::value;
+    // this wave's part of tile i has landed (the loads of NST - 2 later tiles may be outstanding)
+    if (i + S::NST - 2 < n) {
+      if (Z && vown == 2)
+        wait_vm<(S::NST - 2) * (OWN + 2)>();
+      else if (Z && vown == 1)
+        wait_vm<(S::NST - 2) * (OWN + 1)>();
+      else
+        wait_vm<(S::NST - 2) * OWN>();
+    } else {
+      wait_vm<0>();
+    }
+    bare_barrier();  // every part of tile i, and tile i - 1 fully read
+    if (i + S::NST - 1 < n) issue(i + S::NST - 1);
+    const int t = tile_at(i);
+    const uint8_t* tile = ring + (i % S::NST) * S::STAGE;
+    auto chunk = [&](int rb, int kc) {
+      u32x4 x = stage_chunk(tile, 16 * rb + s, 4 * kc + q);
+      if constexpr (RAGGED) mask_chunk<S::ES>(x, d - (t * S::TC + (4 * kc + q) * S::VEC));
+      return x;
+    };
+    if (GRAM && role.tri) {
+#pragma unroll
+      for (int kc = 0; kc < 2; ++kc) {
+        u32x4 fr[S::NR];
+        if (Z && kc == 1) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int a = 0; a < S::NR; ++a) fr[a] = chunk(role.r0 + a, kc);
+#pragma unroll
+        for (int a = 0; a < S::NR; ++a)
+#pragma unroll
+          for (int b = a; b < S::NR; ++b)
+            cur[tri_index<S::NR>(a, b)] = gram_mfma<T>(fr[a], fr[b], cur[tri_index<S::NR>(a, b)]);
+      }
+    }
+    if (role.rect) {
+#pragma unroll
+      for (int kc = 0; kc < 2; ++kc) {
+        u32x4 fa[S::NR], fb[S::NC];
+        if (Z && kc == 1) __builtin_amdgcn_sched_barrier(0);  // keeps the two halves' operands from piling up in registers
+#pragma unroll
+        for (int a = 0; a < S::NR; ++a) fa[a] = chunk(role.row(a), kc);
+        if constexpr (S::RB > 1) {
+#pragma unroll
+          for (int b = 0; b < S::NC; ++b) fb[b] = chunk(role.c0 + b, kc);
+          if constexpr (GRAM) {
+#pragma unroll
+            for (int a = 0; a < S::NR; ++a)
+#pragma unroll
+              for (int b = 0; b < S::NC; ++b)
+                cur[a * S::NC + b] = gram_mfma<T>(fa[a], fb[b], cur[a * S::NC + b]);
+              }
+        }
+        if constexpr (Z) {
+          const uint8_t* vt = vring + (i % S::NST) * S::VST;
+          const int head = s / vs.np, part = s % vs.np;
+          const int cols = d - (t * S::TC + (4 * kc + q) * S::VEC);  // columns left from this chunk on
+          u32x4 bv;
+          if constexpr (S::ES == 2) {
+            bf16x8 o;
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+              const float4 y = *reinterpret_cast<const float4*>(
+                  vt + head * S::VROW + 16 * ((2 * (4 * kc + q) + half) ^ vswz<S>(head)));
+              const float x4[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const float x = !RAGGED || 4 * half + e < cols ? x4[e] : 0.f;
+                nrm = fmaf(x, x, nrm);
+                const __bf16 h0 = (__bf16)x;
+                const float x1 = x - (float)h0;
+                const __bf16 h1 = (__bf16)x1;
+                const __bf16 h2 = (__bf16)(x1 - (float)h1);
+                o[4 * half + e] = part == 0 ? h0 : part == 1 ? h1 : h2;
+              }
+            }
+            bv = __builtin_bit_cast(u32x4, o);
+          } else {
+            const float4 y =
+                *reinterpret_cast<const float4*>(vt + head * S::VROW + 16 * ((4 * kc + q) ^ vswz<S>(head)));
+            const float x4[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float x = !RAGGED || e < cols ? x4[e] : 0.f;
+              nrm = fmaf(x, x, nrm);
+              bv[e] = __float_as_uint(x);
+            }
+          }
+#pragma unroll
+          for (int a = 0; a < S::NC; ++a) zcur[a] = gram_mfma<T>(fa[a], bv, zcur[a]);
+          if constexpr (S::RB > 1) {
+#pragma unroll
+            for (int b = 0; b < S::NC; ++b) zcur[S::NC + b] = gram_mfma<T>(fb[b], bv, zcur[S::NC + b]);
+          }
+        }
+      }
+    }
+    if (--left == 0 || i + 1 == n) {
+      left = flush;
+      if constexpr (GRAM) {
+#pragma unroll
+        for (int x = 0; x < S::NACC; ++x) add_up(acc[x], cur[x], err[x]);
+      }
+      if constexpr (Z) {
+#pragma unroll
+        for (int x = 0; x < S::NZ; ++x) {  // a start: no error of it is repeated
+          zacc[x] += zcur[x];
+          zcur[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+      }
+    }
+  };
+#pragma unroll 1
+  for (int i = 0; i < n_whole; ++i) body(i, std::false_type{});
+  if (n_whole < n) body(n - 1, std::true_type{});
+#pragma unroll
+  for (int x = 0; x < S::NACC; ++x) acc[x] += err[x];
+  __syncthreads();  // the ring is free again
+}
+
+// Row block of zacc[i] in wave wv.
+template <typename S>
+__device__ __forceinline__ int z_row_block(const Role<S>& role, int i) {
+  return i < S::NC ? role.row(i) : role.c0 + i - S::NC;
+}
+
+// This wave's blocks of G into the whole symmetric matrix gl (LDS, pitch P).
+template <typename T, int DH>
+__device__ __forceinline__ void blocks_to_lds(const Role<HShape<T, DH>>& role,
+                                              const f32x4 (&acc)[HShape<T, DH>::NACC], float* gl, int lane) {
+  using S = HShape<T, DH>;
+  const int q = lane >> 4, s = lane & 15;
+  auto put = [&](int bi, int bj, const f32x4& x, bool mirror) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = 16 * bi + 4 * q + e, c = 16 * bj + s;
+      gl[r * S::P + c] = x[e];
+      if (mirror) gl[c * S::P + r] = x[e];
+    }
+  };
+  if (role.tri) {
+#pragma unroll
+    for (int a = 0; a < S::NR; ++a)
+#pragma unroll
+      for (int b = a; b < S::NR; ++b) put(role.r0 + a, role.r0 + b, acc[tri_index<S::NR>(a, b)], a != b);
+  } else if (S::RB > 1 && role.rect) {
+#pragma unroll
+    for (int a = 0; a < S::NR; ++a)
+#pragma unroll
+      for (int b = 0; b < S::NC; ++b) put(role.row(a), role.c0 + b, acc[a * S::NC + b], true);
+  }
+}
+
+// Thread t = 16 R + C takes rows RPT R .. + RPT - 1 and columns C, C + 16, ..
+// of the matrix in gl; thread t < DH also its diagonal element.  Returns
+// whether the whole diagonal lies in the range where Gram products neither
+// under- nor overflow.
+template <int DH>
+__device__ __forceinline__ bool lds_to_regs(const float* gl, float* diag, float (&reg)[DH / 16][DH / 16]) {
+  constexpr int P = DH + 1, RPT = DH / 16;
+  const int t = threadIdx.x, R = t >> 4, C = t & 15;
+  bool bad = false;
+  if (t < DH) {
+    const float x = gl[t * P + t];
+    diag[t] = x;
+    bad = !(x >= kGramMin && x <= kGramMax);
+  }
+#pragma unroll
+  for (int i = 0; i < RPT; ++i)
+#pragma unroll
+    for (int j = 0; j < RPT; ++j) reg[i][j] = gl[(RPT * R + i) * P + C + 16 * j];
+  return __syncthreads_or(bad) == 0;  // gl is read out too
+}
+
+// out[i] = sum_c G[RPT R + i][c] x[c], complete in every lane of the DPP row.
+template <int RPT>
+__device__ __forceinline__ void matvec(const float (&g)[RPT][RPT], const float* x, int C, float (&out)[RPT]) {
+  float xv[RPT];
+#pragma unroll
+  for (int j = 0; j < RPT; ++j) xv[j] = x[C + 16 * j];
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    float a = 0.f;
+#pragma unroll
+    for (int j = 0; j < RPT; ++j) a = fmaf(g[i][j], xv[j], a);
+    out[i] = row16_sum(a);
+  }
+}
+
+// One pass over a d_h x d row block R by the workgroup: w = R^T x, out = R w
+// (unnormalised, in LDS) and ||w||^2, as in a fused sweep.  x, out and part
+// are LDS arrays of d_h, d_h and kHWaves * d_h floats.
+template <typename T, int DH>
+__device__ __forceinline__ float direct_sweep(const char* blk, int64_t ld, int d, const float* x, float* out,
+                                              float* part, float* npart, int wv, int lane) {
+  using S = HShape<T, DH>;
+  constexpr int RPL = DH / kRG;
+  const uint32_t nrec = (uint32_t)((((int64_t)(DH - 1) * ld + d) * S::ES + 15) & ~int64_t(15));
+  const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(blk, nrec);
+  const uint32_t row_bytes = (uint32_t)(ld * S::ES);
+  const int chunk = lane & 7, rg = lane >> 3;
+  const int n = (d + S::TC - 1) / S::TC, n_full = d / S::TC;
+  const uint32_t lane_off = (uint32_t)(((int64_t)rg * RPL * ld + chunk * S::VEC) * S::ES);
+  float xr[RPL], acc[RPL], nrm = 0.f;
+#pragma unroll
+  for (int rr = 0; rr < RPL; ++rr) {
+    xr[rr] = x[rg * RPL + rr];
+    acc[rr] = 0.f;
+  }
+#pragma unroll 1
+  for (int t = wv; t < n; t += kHWaves) {
+    u32x4 tile[RPL];
+#pragma unroll
+    for (int rr = 0; rr < RPL; ++rr)
+      tile[rr] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_off + (uint32_t)t * 128u, rr * row_bytes, kStreamPolicy);
+    if (t >= n_full) {
+#pragma unroll
+      for (int rr = 0; rr < RPL; ++rr) mask_chunk<S::ES>(tile[rr], d - (t * S::TC + chunk * S::VEC));
+    }
+    float w[S::VEC];
+#pragma unroll
+    for (int c = 0; c < S::VEC; ++c) w[c] = 0.f;
+#pragma unroll
+    for (int rr = 0; rr < RPL; ++rr)
+#pragma unroll
+      for (int c = 0; c < S::VEC; ++c) w[c] = fmaf(elem<T>(tile[rr], c), xr[rr], w[c]);
+#pragma unroll
+    for (int rr = 0; rr < RPL; ++rr) reuse_fence(tile[rr]);
+#pragma unroll
+    for (int c = 0; c < S::VEC; ++c) {
+      w[c] = group_sum(w[c]);
+      nrm = fmaf(w[c], w[c], nrm);
+    }
+#pragma unroll
+    for (int rr = 0; rr < RPL; ++rr)
+#pragma unroll
+      for (int c = 0; c < S::VEC; ++c) acc[rr] = fmaf(elem<T>(tile[rr], c), w[c], acc[rr]);
+  }
+#pragma unroll
+  for (int m = 1; m < 8; m <<= 1) nrm = xor_sum(nrm, m);
+  if (lane == 0) npart[wv] = nrm;
+#pragma unroll
+  for (int rr = 0; rr < RPL; ++rr) {
+    float a = acc[rr];
+#pragma unroll
+    for (int m = 1; m < 8; m <<= 1) a = xor_sum(a, m);
+    if ((rr & 7) == chunk) part[wv * DH + rg * RPL + rr] = a;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < DH) {
+    float a = 0.f;
+#pragma unroll
+    for (int w = 0; w < kHWaves; ++w) a += part[w * DH + threadIdx.x];
+    out[threadIdx.x] = a;
+  }
+  const float n2 = sum_waves<kHWaves>(npart);
+  __syncthreads();
+  return n2;
+}
+
+// Sums the parts of each head's z0 slot (slots of head i: i np .. + np - 1)
+// from zacc through LDS (16 slots x d_h floats at zl) and the squared norms of
+// the start vectors into nv[0 .. 16).
+template <typename T, int DH>
+__device__ __forceinline__ void z0_to_lds(const Role<HShape<T, DH>>& role, const f32x4 (&zacc)[HShape<T, DH>::NZ],
+                                          float nrm, int wv, int lane, int np, float* zl, float* nv) {
+  using S = HShape<T, DH>;
+  const int q = lane >> 4, s = lane & 15;
+  if (role.rect) {
+#pragma unroll
+    for (int i = 0; i < S::NZ; ++i)
+      *reinterpret_cast<f32x4*>(zl + s * DH + 16 * z_row_block(role, i) + 4 * q) = zacc[i];
+  }
+  if (wv == 2) {  // both z0 waves read every column; the q lanes of a slot hold disjoint ones
+    nrm += __shfl_xor(nrm, 16);
+    nrm += __shfl_xor(nrm, 32);
+    if (q == 0 && s % np == 0) nv[s / np] = nrm;
+  }
+  __syncthreads();
+}
+
+// This wave's blocks of G to memory, in the block order and lane layout of
+// tri_index and the matrix-core output.
+template <typename T, int DH>
+__device__ __forceinline__ void blocks_to_memory(const Role<HShape<T, DH>>& role,
+                                                 const f32x4 (&acc)[HShape<T, DH>::NACC], float* dst, int lane) {
+  using S = HShape<T, DH>;
+  f32x4* out = reinterpret_cast<f32x4*>(dst) + lane;
+  if (role.tri) {
+#pragma unroll
+    for (int x = 0; x < S::NR; ++x)
+#pragma unroll
+      for (int y = x; y < S::NR; ++y)
+        out[tri_index<S::RB>(role.r0 + x, role.r0 + y) * 64] = acc[tri_index<S::NR>(x, y)];
+  } else if (S::RB > 1 && role.rect) {
+#pragma unroll
+    for (int x = 0; x < S::NR; ++x)
+#pragma unroll
+      for (int y = 0; y < S::NC; ++y) out[tri_index<S::RB>(role.row(x), role.c0 + y) * 64] = acc[x * S::NC + y];
+  }
+}
+
+// The sum of `strips` Gram matrices written by blocks_to_memory, as a whole
+// symmetric matrix in LDS.
+template <typename T, int DH>
+__device__ __forceinline__ void memory_to_lds(const float* src, int strips, float* gl) {
+  using S = HShape<T, DH>;
+  const f32x4* in = reinterpret_cast<const f32x4*>(src);
+  for (int x = threadIdx.x; x < S::NB * 64; x += kHThreads) {
+    const int b = x >> 6, ln = x & 63;
+    int bi = 0, start = 0;
+    while (b >= start + (S::RB - bi)) {  // upper-triangle block b -> (bi, bj)
+      start += S::RB - bi;
+      ++bi;
+    }
+    const int bj = bi + (b - start);
+    f32x4 y = in[x];
+#pragma unroll 4
+    for (int st = 1; st < strips; ++st) y += in[(size_t)st * S::NB * 64 + x];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = 16 * bi + 4 * (ln >> 4) + e, c = 16 * bj + (ln & 15);
+      gl[r * S::P + c] = y[e];
+      if (bi != bj) gl[c * S::P + r] = y[e];
+    }
+  }
+  __syncthreads();
+}
+
+// Items: (key head, chunk of query heads, column strip) for the key heads of
+// the launch, then (query head, column strip) where the query matrices are
+// split over workgroups too (a.sq > 0).
+template <typename T, int DH>
+__global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(2))) units_kernel(HeadArgs a) {
+  using S = HShape<T, DH>;
+  __shared__ __attribute__((aligned(16))) uint8_t big[S::RING];
+  __shared__ float nv[16];
+  const int lane = threadIdx.x & 63, wv = uni((int)(threadIdx.x >> 6));
+  const Role<S> role(wv);
+  const int n_tiles = (a.d + S::TC - 1) / S::TC;
+  f32x4 acc[S::NACC], zacc[S::NZ];
+#pragma unroll
+  for (int i = 0; i < S::NACC; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < S::NZ; ++i) zacc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float nrm = 0.f;
+  const int item = blockIdx.x, n_key = a.units * a.nch * a.sk;
+  if (item >= n_key) {
+    const int hl = (item - n_key) / a.sq, strip = (item - n_key) % a.sq;
+    const int h = a.head0 + hl;
+    const char* blk = uni(a.mats[h / a.n_q]) + (int64_t)(h % a.n_q) * DH * a.ld * S::ES;
+    const int t0 = strip * a.tps_q, t1 = min(t0 + a.tps_q, n_tiles);
+    stream_block<T, DH, false, true>(blk, a.ld, a.d, t0, t1, item, big, wv, lane, role, VSlots{nullptr, 0, 1}, acc,
+                                     zacc, nrm);
+    blocks_to_memory<T, DH>(role, acc, a.gq + (size_t)(hl * a.sq + strip) * S::NB * 256, lane);
+    return;
+  }
+  const int strip = item % a.sk, ch = item / a.sk % a.nch, ul = item / (a.sk * a.nch);
+  const int unit = a.unit0 + ul, layer = unit / a.n_kv, j = unit % a.n_kv;
+  const int hin = ch * a.hps, nvalid = min(a.hps, a.g - hin);
+  const int h0 = ul * a.g + hin;  // first query head, counted from the launch's
+  const char* blk = uni(a.mats[a.L + layer]) + (int64_t)j * DH * a.ld * S::ES;
+  const VSlots vs{a.v + (size_t)(a.head0 + h0) * a.d, nvalid, a.np};
+  const int t0 = strip * a.tps_k, t1 = min(t0 + a.tps_k, n_tiles);
+  if (ch == 0) {
+    stream_block<T, DH, true, true>(blk, a.ld, a.d, t0, t1, item, big, wv, lane, role, vs, acc, zacc, nrm);
+    blocks_to_memory<T, DH>(role, acc, a.gk + (size_t)(ul * a.sk + strip) * S::NB * 256, lane);
+  } else {
+    stream_block<T, DH, true, false>(blk, a.ld, a.d, t0, t1, item, big, wv, lane, role, vs, acc, zacc, nrm);
+  }
+  float* zl = reinterpret_cast<float*>(big);
+  z0_to_lds<T, DH>(role, zacc, nrm, wv, lane, a.np, zl, nv);
+  for (int x = threadIdx.x; x < nvalid * DH; x += kHThreads) {
+    const int i = x / DH, r = x % DH;
+    float z = 0.f;
+    for (int p = 0; p < a.np; ++p) z += zl[(i * a.np + p) * DH + r];
+    const size_t o = (size_t)(h0 + i) * a.sk + strip;
+    a.zp[o * DH + r] = z;
+    if (r == 0) a.zn[o] = nv[i];
+  }
+}
+
+// SRC: where a head's Gram matrices come from.  H_OWN (g = 1): the workgroup
+// streams K_h, then Q_h.  H_KEYS: G_K and z0 from units_kernel, Q_h streamed
+// here.  H_SPLIT: both from units_kernel.
+enum { H_OWN = 0, H_KEYS = 1, H_SPLIT = 2 };
+
+template <typename T, int DH, int SRC>
+__global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(2))) heads_kernel(HeadArgs a) {
+  using S = HShape<T, DH>;
+  constexpr int RPT = S::RPT;
+  __shared__ __attribute__((aligned(16))) uint8_t big[SRC == H_SPLIT ? DH * S::P * 4 : S::BIG];
+  __shared__ float z0[DH], tb[DH], wb[DH], dq[DH], dk[DH];
+  __shared__ float nv[16], red[4][kHWaves];
+  float* gl = reinterpret_cast<float*>(big);
+  const int t = threadIdx.x, lane = t & 63, wv = uni(t >> 6);
+  const int R = t >> 4, C = t & 15;
+  const int hl = blockIdx.x, h = a.head0 + hl;
+  const int layer = h / a.n_q, hq = h % a.n_q, j = hq / a.g;
+  const char* qblk = uni(a.mats[layer]) + (int64_t)hq * DH * a.ld * S::ES;
+  const char* kblk = uni(a.mats[a.L + layer]) + (int64_t)j * DH * a.ld * S::ES;
+  const int n_tiles = (a.d + S::TC - 1) / S::TC;
+  const Role<S> role(wv);
+  f32x4 acc[S::NACC], zacc[S::NZ];
+  float gq[RPT][RPT], gk[RPT][RPT];
+  float nrm = 0.f, n2v = 0.f, zr = 0.f;  // ||v||^2 and, in thread r < d_h, z0[r] ||v||
+  auto clear = [&] {
+#pragma unroll
+    for (int i = 0; i < S::NACC; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  bool in_range = true;
+  if constexpr (SRC == H_OWN) {
+#pragma unroll
+    for (int i = 0; i < S::NZ; ++i) zacc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    clear();
+    stream_block<T, DH, true, true>(kblk, a.ld, a.d, 0, n_tiles, hl, big, wv, lane, role,
+                                    VSlots{a.v + (size_t)h * a.d, 1, a.np}, acc, zacc, nrm);
+    z0_to_lds<T, DH>(role, zacc, nrm, wv, lane, a.np, gl, nv);
+    n2v = nv[0];
+    if (t < DH)
+      for (int p = 0; p < a.np; ++p) zr += gl[p * DH + t];
+    __syncthreads();
+    blocks_to_lds<T, DH>(role, acc, gl, lane);
+    __syncthreads();
+    in_range = lds_to_regs<DH>(gl, dk, gk);
+  } else {
+    for (int st = 0; st < a.sk; ++st) n2v += a.zn[(size_t)hl * a.sk + st];
+    if (t < DH)
+      for (int st = 0; st < a.sk; ++st) zr += a.zp[((size_t)hl * a.sk + st) * DH + t];
+  }
+  const float vn = sqrtf(n2v);
+  if (t == 0) a.w.vnorm0[h] = vn;
+  if (!(vn > 0.f) || !isfinite(vn)) {  // zero or non-finite start vector
+    if (t == 0) {
+      a.sigma[h] = __builtin_nanf("");
+      a.iters[h] = -1;
+    }
+    return;
+  }
+  if (t < DH) tb[t] = z0[t] = zr / vn;
+  if constexpr (SRC != H_SPLIT) {
+    clear();
+    stream_block<T, DH, false, true>(qblk, a.ld, a.d, 0, n_tiles, hl, big, wv, lane, role, VSlots{nullptr, 0, 1}, acc,
+                                     zacc, nrm);
+    blocks_to_lds<T, DH>(role, acc, gl, lane);
+    __syncthreads();
+  } else {
+    memory_to_lds<T, DH>(a.gq + (size_t)hl * a.sq * S::NB * 256, a.sq, gl);
+  }
+  in_range = lds_to_regs<DH>(gl, dq, gq) && in_range;
+  if constexpr (SRC != H_OWN) {
+    memory_to_lds<T, DH>(a.gk + (size_t)(layer * a.n_kv + j - a.unit0) * a.sk * S::NB * 256, a.sk, gl);
+    in_range = lds_to_regs<DH>(gl, dk, gk) && in_range;
+  }
+
+  float* fin = a.w.fin + (size_t)h * 2 * DH;
+  auto finish = [&](int k, float sig, const float* z, float zs, const float* y, float ys) {
+    if (t < DH) {
+      fin[t] = z[t] * zs;
+      fin[DH + t] = y[t] * ys;
+    }
+    if (t == 0) {
+      a.sigma[h] = sig;
+      a.iters[h] = k;
+    }
+  };
+  auto stop = [&](int k, float sig, float prev) {
+    return k >= a.n_iter || (a.tol > 0.f && k >= 2 && fabsf(sig - prev) <= a.tol * sig);
+  };
+
+  if (in_range) {
+    float dqr[RPT], dkr[RPT];
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      dqr[i] = dq[RPT * R + i];
+      dkr[i] = dk[RPT * R + i];
+    }
+    float zscale = 1.f, prev = 0.f, out[RPT];
+#pragma unroll 1
+    for (int k = 1;; ++k) {
+      // w = G_Q z with z = zscale * tb
+      matvec<RPT>(gq, tb, C, out);
+      float part = 0.f, bound = 0.f;
+      if (C == 0) {
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+          const float wr = out[i] * zscale, zr = tb[RPT * R + i] * zscale;
+          part = fmaf(zr, wr, part);
+          bound = fmaf(zr * zr, dqr[i], bound);
+          wb[RPT * R + i] = wr;
+        }
+      }
+      part = c0_lanes_sum(part);
+      bound = c0_lanes_sum(bound);
+      if (lane == 0) {
+        red[0][wv] = part;
+        red[1][wv] = bound;
+      }
+      __syncthreads();
+      const float s2 = sum_waves<kHWaves>(red[0]);
+      if (!(s2 >= kCancel * sum_waves<kHWaves>(red[1])) || !(s2 >= kTiny)) break;
+      const float sig = sqrtf(s2), inv = 1.0f / sig;
+      const bool last = stop(k, sig, prev);
+      // t = G_K y with y = w / sigma
+      matvec<RPT>(gk, wb, C, out);
+      part = 0.f;
+      bound = 0.f;
+      if (C == 0) {
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+          const float tr = out[i] * inv, yr = wb[RPT * R + i] * inv;
+          part = fmaf(yr, tr, part);
+          bound = fmaf(yr * yr, dkr[i], bound);
+          if (!last) tb[RPT * R + i] = tr;
+        }
+      }
+      part = c0_lanes_sum(part);
+      bound = c0_lanes_sum(bound);
+      if (lane == 0) {
+        red[2][wv] = part;
+        red[3][wv] = bound;
+      }
+      __syncthreads();
+      const float n2 = sum_waves<kHWaves>(red[2]);
+      if (!(n2 >= kCancel * sum_waves<kHWaves>(red[3])) || !(n2 >= kTiny)) break;
+      const float rn = 1.0f / sqrtf(n2);
+      if (last) {
+        finish(k, sig, tb, zscale * inv, wb, inv * rn);
+        return;
+      }
+      zscale = rn;
+      prev = sig;
+    }
+    __syncthreads();
+  }
+
+  // the head's rows cancel, or its values leave the range of the Gram
+  // products: iterate by reading the weights, from z0
+  float* part = gl;
+  if (t < DH) tb[t] = z0[t];
+  __syncthreads();
+  float prev = 0.f;
+#pragma unroll 1
+  for (int k = 1;; ++k) {
+    const float s2 = direct_sweep<T, DH>(qblk, a.ld, a.d, tb, wb, part, red[0], wv, lane);
+    const float sig = sqrtf(s2);
+    if (s2 == 0.f) {  // M v = 0
+      if (t == 0) {
+        a.sigma[h] = 0.f;
+        a.iters[h] = -2;
+      }
+      return;
+    }
+    const bool last = stop(k, sig, prev);
+    const float inv = 1.0f / sig;
+    if (t < DH) wb[t] *= inv;
+    __syncthreads();
+    const float n2 = direct_sweep<T, DH>(kblk, a.ld, a.d, wb, dq, part, red[0], wv, lane);
+    const float rn = 1.0f / sqrtf(n2);
+    if (last) {
+      finish(k, sig, tb, inv, wb, rn);
+      return;
+    }
+    if (t < DH) tb[t] = dq[t] * rn;
+    __syncthreads();
+    prev = sig;
+  }
+}
+
+// Layer scales, and the vectors of the heads that took no step (the others
+// leave the final sweeps normalised): block l.
+__global__ void __launch_bounds__(kThreads) heads_finalize_kernel(FinArgs f) {
+  const int l = blockIdx.x;
+  __shared__ float red[kThreads / 64];
+  __shared__ int nan_seen;
+  if (threadIdx.x == 0) nan_seen = 0;
+  __syncthreads();
+  float m = 0.f;
+  for (int i = threadIdx.x; i < f.n_q; i += kThreads) {
+    const float s = f.sigma[(size_t)l * f.n_q + i];
+    if (isnan(s)) nan_seen = 1;
+    m = fmaxf(m, s);
+  }
+#pragma unroll
+  for (int x = 32; x >= 1; x >>= 1) m = fmaxf(m, __shfl_xor(m, x));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int w = 1; w < kThreads / 64; ++w) m = fmaxf(m, red[w]);
+    f.scale[l] = nan_seen ? __builtin_nanf("") : f.coef * m;
+  }
+  __shared__ int list[kThreads], n_list;
+  for (int i0 = 0; i0 < f.n_q; i0 += kThreads) {
+    if (threadIdx.x == 0) n_list = 0;
+    __syncthreads();
+    const int i = i0 + (int)threadIdx.x;
+    if (i < f.n_q && f.iters[l * f.n_q + i] <= 0) list[atomicAdd(&n_list, 1)] = l * f.n_q + i;
+    __syncthreads();
+    for (int x = 0; x < n_list; ++x) {  // rare, and independent of the order of the list
+      const int h = list[x];
+      const bool scale_v = f.iters[h] == -2;
+      const float vs = 1.0f / f.w.vnorm0[h];
+      for (int c = threadIdx.x; c < f.d; c += kThreads) {
+        if (scale_v) f.v[(size_t)h * f.d + c] *= vs;
+        if (f.u) f.u[(size_t)h * f.d + c] = 0.f;
+      }
+    }
+    __syncthreads();
+  }
+}
+
+template <typename T, int DH>
+void launch_dh(const HeadArgs& a, bool units, hipStream_t st) {
+  const int heads = a.units * a.g;
+  if (units)
+    units_kernel<T, DH><<<dim3(a.units * a.nch * a.sk + heads * a.sq), kHThreads, 0, st>>>(a);
+  else if (a.sq > 0)
+    heads_kernel<T, DH, H_SPLIT><<<dim3(heads), kHThreads, 0, st>>>(a);
+  else if (a.g > 1)
+    heads_kernel<T, DH, H_KEYS><<<dim3(heads), kHThreads, 0, st>>>(a);
+  else
+    heads_kernel<T, DH, H_OWN><<<dim3(heads), kHThreads, 0, st>>>(a);
+}
+
+template <typename T>
+void launch_t(int dh, const HeadArgs& a, bool units, hipStream_t st) {
+  switch (dh) {
+    case 16: launch_dh<T, 16>(a, units, st); break;
+    case 32: launch_dh<T, 32>(a, units, st); break;
+    case 64: launch_dh<T, 64>(a, units, st); break;
+    default: launch_dh<T, 128>(a, units, st); break;
+  }
+}
+
+}  // namespace
+
+void launch_heads(bool bf16, int head_dim, bool units, hipStream_t st, HeadArgs a) {
+  // slots of a z0 operand: three bf16 parts per head (24 bits, 5 heads); two
+  // (16 bits, 8 heads) only where they save an operand and the grouped sweeps
+  // keep no more either (d_h 64 and 128); fp32 weights take v as it is
+  a.np = !bf16 ? 1 : a.g > 5 && head_dim >= 64 ? 2 : 3;
+  a.hps = 16 / a.np;
+  a.nch = (a.g + a.hps - 1) / a.hps;
+  if (bf16)
+    launch_t<uint16_t>(head_dim, a, units, st);
+  else
+    launch_t<float>(head_dim, a, units, st);
+}
+
+void launch_heads_finalize(int layers, hipStream_t st, const FinArgs& f) {
+  heads_finalize_kernel<<<dim3(layers), kThreads, 0, st>>>(f);
+}
+
+}  // namespace sn

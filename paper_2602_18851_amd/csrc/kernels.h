@@ -28,6 +28,7 @@ constexpr int kMWaves = 2;                 // waves per workgroup
 constexpr int kMTileC = 64;                // columns per tile: 128-byte row segments
 constexpr int kGWaves = 4;                 // waves per workgroup of the Gram sweep
 constexpr int kGTargetItems = 4096;        // Gram work items aimed for (about two waves per SIMD)
+constexpr int kHWaves = 4;                 // waves per workgroup of the one-workgroup-per-head Gram form
 constexpr int kRedThreads = 512;
 
 // Sweep phases: the first W_K sweep from v, the W_Q and W_K sweeps of a step,
@@ -88,7 +89,6 @@ struct SweepArgs {
 
 struct FinArgs {
   int32_t H, L, n_q, d, s_k;
-  int32_t slot_fixed;  // workspace slot of the ||v'||^2 partials; -1: parity of the last step
   const int32_t* zs;   // per-head strips of those partials, or nullptr: s_k for every head
   const int32_t* tail; // tolerance mode: flags of the heads the tail finished (else nullptr) ...
   const float* zt;     // ... whose ||v'||^2 partials are zt[head][zs[head]]
@@ -125,6 +125,28 @@ struct IterArgs {
   const int32_t* ctl;
   const int32_t* kvpos;
   Work w;
+  float* sigma;
+  int32_t* iters;
+};
+
+// The Gram form with one workgroup per head (gram_heads.hip): one launch pair
+// covers `units` key heads from unit0 and their query heads from head0.
+struct HeadArgs {
+  const void* const* mats;  // device table: wq pointers of all layers, then wk pointers
+  int64_t ld;
+  int32_t d, L, n_q, n_kv, g;
+  int32_t unit0, units, head0;
+  int32_t sk, tps_k;        // column strips of a key head, and tiles per strip
+  int32_t sq, tps_q;        // ... of a query head; sq = 0: its own workgroup reads all of it
+  int32_t np, hps, nch;     // bf16 parts per start vector, heads per z0 operand, operands per key head
+  int32_t n_iter;
+  float tol;
+  const float* v;
+  float* gk;                // [units][sk][NB][64][4]: G_K partials, blocks as in GramArgs::gp
+  float* gq;                // [heads][sq][NB][64][4]: G_Q partials
+  float* zp;                // [heads][sk][DH]: partials of K_j v
+  float* zn;                // [heads][sk]: partials of ||v||^2
+  Work w;                   // fin and vnorm0
   float* sigma;
   int32_t* iters;
 };
@@ -208,6 +230,9 @@ struct TailPlan {
 void launch_tail_lists(const SweepArgs& a, int slot, int gc, int n_units, const TailPlan& tp, hipStream_t st);
 void launch_gram(bool bf16, int head_dim, int n_items, hipStream_t st, const GramArgs& g);
 void launch_gram_iterate(int head_dim, int heads, hipStream_t st, const IterArgs& a);
+// units: the units_kernel of the pair (none where a head's workgroup reads both its matrices), else heads_kernel
+void launch_heads(bool bf16, int head_dim, bool units, hipStream_t st, HeadArgs a);
+void launch_heads_finalize(int layers, hipStream_t st, const FinArgs& f);
 void launch_layer_sweep(bool bf16, int head_dim, int mode, int n_items, hipStream_t st, const LayerArgs& a);
 void launch_layer_vin(int layers, hipStream_t st, const LayerVinArgs& v);
 void launch_layer_reduce(int layers, hipStream_t st, const LayerReduceArgs& r);

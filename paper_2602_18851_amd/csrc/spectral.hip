@@ -69,6 +69,10 @@ struct Plan {
   size_t off_zp, off_zn, off_yp, off_yn, off_sig, off_vn, off_alive, off_iters, off_fin, off_gp;
   size_t off_lz, off_ly, off_lvin, off_lcol, off_lu, off_lv, off_ln2, off_ln2p, off_lstat;
   size_t off_zs, off_lg, off_lk, off_kvpos, off_ctl, off_zt;
+  bool heads;   // calls of two or more iterations may run the Gram form with one workgroup per head
+  int h_units;  // key heads of one launch pair
+  int h_sk, h_tps_k, h_sq, h_tps_q;  // column strips of their key and query matrices (h_sq 0: not split)
+  size_t off_hfin, off_gk, off_gq, off_hz, off_hn;
   size_t bytes;
 };
 
@@ -121,7 +125,55 @@ void strips(int n_tiles, int64_t units, int requested, int target, bool round_do
   *s_out = ceil_div(n_tiles, tps);
 }
 
-Plan make_plan(const sn_shape* s, const sn_params* p) {
+// Bytes of Gram matrices one launch pair of the one-workgroup-per-head form
+// works on: all 640 key heads of the 70B GQA shape (23.6 MB); larger shapes
+// go through in several pairs, each long enough to hide its launches.
+constexpr size_t kGkBytes = size_t(26) << 20;
+constexpr int kSplitHeads = 256;     // below this many heads their query matrices are split over workgroups
+constexpr int kSplitTarget = 384;    // ... into about this many (with about 256 for the key heads)
+constexpr int kKeyTarget = 512;      // workgroups aimed for over the key heads: two per compute unit
+
+// The one-workgroup-per-head form: column strips, and its buffers, which
+// share the bytes of the sweeps' partials, sweep0 .. *off (a call uses one or
+// the other), and go past their end where those are smaller.
+// `slack` >= 0: they may add at most that many bytes to the workspace.  The
+// results do not depend on it, only how many key heads a launch pair covers.
+void plan_heads(const sn_shape* s, Plan& pl, size_t sweep0, int64_t slack, size_t* off) {
+  const size_t H = pl.H, dh = s->head_dim, g = pl.g, n_units = (size_t)s->n_layers * s->n_kv_heads;
+  const int tiles = ceil_div((int64_t)s->d_model * esize(s->dtype), 128);
+  const bool split = pl.H < kSplitHeads;
+  pl.h_sq = pl.h_sk = 1;
+  pl.h_tps_q = pl.h_tps_k = tiles;
+  if (split) strips(tiles, pl.H, 0, kSplitTarget, true, &pl.h_sq, &pl.h_tps_q);
+  if (split || g > 1) strips(tiles, n_units, 0, split ? kSplitTarget - 128 : kKeyTarget, true, &pl.h_sk, &pl.h_tps_k);
+  if (!split) pl.h_sq = 0;
+  const size_t fin = (H * 2 * dh * 4 + 255) & ~size_t(255);
+  const size_t mat = (dh / 16) * (dh / 16 + 1) / 2 * 1024;
+  const size_t per_unit = split || g > 1 ? (pl.h_sk + g * pl.h_sq) * mat + g * pl.h_sk * (dh + 1) * 4 : 0;
+  const size_t room = *off - sweep0;  // >= fin: the sweeps keep three or more d_h-vectors per head
+  size_t most = std::max(kGkBytes, room - fin);
+  if (slack >= 0) most = std::min(most, room - fin + (size_t)slack);
+  pl.h_units = per_unit ? (int)std::min(n_units, (most - std::min<size_t>(most, 1024)) / per_unit) : (int)n_units;
+  pl.heads = pl.h_units > 0;
+  size_t o = sweep0;
+  auto take = [&](size_t bytes) {
+    const size_t r = o;
+    o += (bytes + 255) & ~size_t(255);
+    return r;
+  };
+  pl.off_hfin = take(fin);
+  if (per_unit) {
+    const size_t u = pl.h_units;
+    pl.off_gk = take(u * pl.h_sk * mat);
+    pl.off_gq = take(u * g * pl.h_sq * mat);
+    pl.off_hz = take(u * g * pl.h_sk * dh * 4);
+    pl.off_hn = take(u * g * pl.h_sk * 4);
+  }
+  *off = std::max(*off, o);
+}
+
+// `slack`: see plan_heads.
+Plan make_plan(const sn_shape* s, const sn_params* p, int64_t slack = -1) {
   Plan pl{};
   const int dh = s->head_dim;
   pl.H = s->n_layers * s->n_q_heads;
@@ -164,14 +216,17 @@ Plan make_plan(const sn_shape* s, const sn_params* p) {
     return o;
   };
   const size_t H = pl.H;
-  pl.off_zp = take(2 * H * pl.s_k * dh * 4);
   pl.off_zn = take(2 * H * pl.s_k * 4);
-  pl.off_yp = take(H * pl.s_q * dh * 4);
   pl.off_yn = take(H * pl.s_q * 4);
   pl.off_sig = take(2 * H * 4);
   pl.off_vn = take(H * 4);
   pl.off_alive = take(2 * H * 4);
   pl.off_iters = take(H * 4);
+  // the z and y partials of the sweeps
+  const size_t sweep0 = off;
+  pl.off_zp = take(2 * H * pl.s_k * dh * 4);
+  pl.off_yp = take(H * pl.s_q * dh * 4);
+  if (dh >= 16) plan_heads(s, pl, sweep0, slack, &off);
   if (pl.tail) {
     const size_t nkvh = (size_t)s->n_layers * s->n_kv_heads;
     pl.off_zs = take(H * 4);
@@ -554,21 +609,62 @@ int run_chain(sn_ctx* c, SweepArgs a, float* u) {
   return SN_OK;
 }
 
-// The Gram form of one call: first W_K sweep, Gram sweep, d_h-space
-// iteration, final W_K sweep (and W_Q sweep for u).
-int run_gram(sn_ctx* c, SweepArgs a, float* u) {
+// Whether a call runs the Gram form with one workgroup per head: where it was
+// asked for, and for two or more iterations of a fixed count (it reads W_K
+// twice and W_Q once; the sweeps read each once per iteration, and W_K once
+// more).  At one iteration both read the same and the sweeps need no Gram
+// products (70B GQA shape 2.25 ms; two iterations: sweeps 4.0, here 2.4 ms).
+// Strip counts and SN_FLAG_VALU_K_SWEEP are the sweeps' own parameters.
+bool heads_call(const sn_ctx* c, int n_iter) {
   const Plan& pl = c->plan;
+  const sn_params& p = c->params;
+  if (!pl.heads) return false;
+  if (pl.gram) return true;
+  if (p.q_strips > 0 || p.k_strips > 0 || (p.flags & SN_FLAG_VALU_K_SWEEP)) return false;
+  return n_iter >= 2 && !(p.tol > 0.f);
+}
+
+// The Gram form with one workgroup per head (gram_heads.hip), then the final
+// sweeps, which find z / sigma and y / ||v'|| and so write unit vectors.
+int run_heads(sn_ctx* c, SweepArgs a, float* u) {
+  const Plan& pl = c->plan;
+  const int n_units = c->shape.n_layers * c->shape.n_kv_heads, dh = c->shape.head_dim;
+  a.w.fin = reinterpret_cast<float*>(c->ws + pl.off_hfin);
+  HeadArgs h{};
+  h.mats = c->tab;
+  h.ld = c->shape.ld;
+  h.d = c->shape.d_model;
+  h.L = c->shape.n_layers;
+  h.n_q = c->shape.n_q_heads;
+  h.n_kv = c->shape.n_kv_heads;
+  h.g = pl.g;
+  h.n_iter = a.n_iter;
+  h.tol = a.tol;
+  h.v = a.v;
+  h.sk = pl.h_sk;
+  h.tps_k = pl.h_tps_k;
+  h.sq = pl.h_sq;
+  h.tps_q = pl.h_tps_q;
+  h.gk = reinterpret_cast<float*>(c->ws + pl.off_gk);
+  h.gq = reinterpret_cast<float*>(c->ws + pl.off_gq);
+  h.zp = reinterpret_cast<float*>(c->ws + pl.off_hz);
+  h.zn = reinterpret_cast<float*>(c->ws + pl.off_hn);
+  h.w = a.w;
+  h.sigma = a.sigma;
+  h.iters = a.iters;
   int rc;
+  for (h.unit0 = 0; h.unit0 < n_units; h.unit0 += pl.h_units) {
+    h.units = std::min(pl.h_units, n_units - h.unit0);
+    h.head0 = h.unit0 * pl.g;
+    const bool bf16 = c->shape.dtype == SN_BF16;
+    if (pl.g > 1 || h.sq > 0) {
+      rc = timed(c, KIND_GRAM, [&] { launch_heads(bf16, dh, true, c->stream, h); });
+      if (rc != SN_OK) return rc;
+    }
+    rc = timed(c, KIND_ITER, [&] { launch_heads(bf16, dh, false, c->stream, h); });
+    if (rc != SN_OK) return rc;
+  }
   a.k = 0;
-  if ((rc = run_sweep(c, PH_INIT, a)) != SN_OK) return rc;
-  GramArgs g = gram_args(c);
-  const int dh = c->shape.head_dim;
-  rc = timed(c, KIND_GRAM, [&] { launch_gram(c->shape.dtype == SN_BF16, dh, g.n_items, c->stream, g); });
-  if (rc != SN_OK) return rc;
-  IterArgs it = iter_args(c, a);
-  rc = timed(c, KIND_ITER, [&] { launch_gram_iterate(dh, pl.H, c->stream, it); });
-  if (rc != SN_OK) return rc;
-  a.k = 0;  // the final sweeps write their ||v'||^2 partials to slot 0
   if ((rc = run_sweep(c, PH_EK, a)) != SN_OK) return rc;
   if (u && (rc = run_sweep(c, PH_EQ, a)) != SN_OK) return rc;
   return SN_OK;
@@ -621,17 +717,17 @@ int step_body(sn_ctx* c, float* v, float* u, int32_t n_iter, float* sigma, float
   a.sigma = sigma;
   a.iters = iters ? iters : c->w.iters;
 
-  int rc = pl.gram ? run_gram(c, a, u) : run_chain(c, a, u);
+  const bool heads = heads_call(c, n_iter);
+  int rc = heads ? run_heads(c, a, u) : run_chain(c, a, u);
   if (rc != SN_OK) return rc;
 
-  const bool tail_ran = pl.tail && n_iter > kTailSteps;
+  const bool tail_ran = pl.tail && !heads && n_iter > kTailSteps;
   FinArgs f{};
   f.H = pl.H;
   f.L = L;
   f.n_q = c->shape.n_q_heads;
   f.d = c->shape.d_model;
   f.s_k = pl.s_k;
-  f.slot_fixed = pl.gram ? 0 : -1;
   f.zs = pl.tail ? c->w.zs : nullptr;
   f.tail = tail_ran ? c->w.alive + (size_t)(kTailSteps & 1) * pl.H : nullptr;
   f.zt = c->w.zt;
@@ -642,7 +738,12 @@ int step_body(sn_ctx* c, float* v, float* u, int32_t n_iter, float* sigma, float
   f.sigma = sigma;
   f.scale = scale;
   f.iters = a.iters;
-  return timed(c, KIND_FIN, [&] { launch_finalize(pl.H + L, c->stream, f); });
+  return timed(c, KIND_FIN, [&] {
+    if (heads)
+      launch_heads_finalize(L, c->stream, f);
+    else
+      launch_finalize(pl.H + L, c->stream, f);
+  });
 }
 
 }  // namespace
@@ -676,9 +777,9 @@ SN_API int spectral_init(sn_ctx** ctx, const sn_shape* shape, const sn_params* p
   };
   if (hipGetDevice(&c->device) != hipSuccess) return cleanup(fail(SN_ESTATE, "no HIP device"));
   const size_t L = c->shape.n_layers;
-  if (hipMalloc(&c->ws, c->plan.bytes) != hipSuccess) return cleanup(fail(SN_EHIP, "hipMalloc(workspace) failed"));
-  if (hipMalloc(&c->d_tab, 4 * L * sizeof(void*)) != hipSuccess)
-    return cleanup(fail(SN_EHIP, "hipMalloc(pointer table) failed"));
+  if (hipMalloc(&c->ws, c->plan.bytes + 4 * L * sizeof(void*)) != hipSuccess)
+    return cleanup(fail(SN_EHIP, "hipMalloc(workspace and pointer table) failed"));
+  c->d_tab = reinterpret_cast<const void**>(c->ws + c->plan.bytes);
   if (hipEventCreateWithFlags(&c->tab_event, hipEventDisableTiming) != hipSuccess)
     return cleanup(fail(SN_EHIP, "hipEventCreate failed"));
   c->tab = c->d_tab;
@@ -711,7 +812,6 @@ SN_API void spectral_destroy(sn_ctx* c) {
   }
   for (auto e : c->pool) (void)hipEventDestroy(e);
   if (c->tab_event) (void)hipEventDestroy(c->tab_event);
-  if (c->owns_ws && c->d_tab) (void)hipFree(c->d_tab);
   if (c->owns_ws && c->ws) (void)hipFree(c->ws);
   delete c;
 }
@@ -807,13 +907,14 @@ SN_API int spectral_step_noalloc(const sn_shape* shape, const sn_params* params,
   if (c.shape.ld == 0) c.shape.ld = shape->d_model;
   c.params = *params;
   c.params.flags &= ~SN_FLAG_LAYER;  // only reserves space for spectral_step_layer
-  c.plan = make_plan(&c.shape, &c.params);
+  c.plan = make_plan(&c.shape, &c.params, 0);
   const int L = c.shape.n_layers;
   const size_t tab_bytes = ((size_t)4 * L * sizeof(void*) + 255) & ~size_t(255);
   const size_t need = tab_bytes + c.plan.bytes;
   if (need > kScratchBytes)
     return fail(SN_EINVAL, "this shape needs " + std::to_string(need) + " bytes of scratch; spectral_step_noalloc " +
                                "holds at most " + std::to_string(kScratchBytes) + " (use spectral_init / spectral_step)");
+  c.plan = make_plan(&c.shape, &c.params, (int64_t)(kScratchBytes - need));
   SN_HIP(hipGetDevice(&c.device));
   char* base = nullptr;
   if ((rc = scratch_on_device(c.device, &base)) != SN_OK) return rc;

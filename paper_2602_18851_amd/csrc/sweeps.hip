@@ -726,7 +726,7 @@ __global__ void __launch_bounds__(kThreads) finalize_kernel(FinArgs f) {
       if (f.tail && f.tail[b] != 0) {  // finished by the tail: the final W_K sweep's own buffer
         for (int s = 0; s < sk; ++s) n2 += f.zt[(size_t)b * sk + s];
       } else {
-        const int slot = f.slot_fixed >= 0 ? f.slot_fixed : (it & 1);
+        const int slot = it & 1;
         for (int s = 0; s < sk; ++s) n2 += f.w.zn[((size_t)slot * f.H + b) * sk + s];
       }
       vs = 1.0f / sqrtf(n2);

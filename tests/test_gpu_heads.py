@@ -1,0 +1,150 @@
+"""The Gram form with one workgroup per head, which calls of two or more
+iterations run: against the float64 oracle and against the sweeps (forced by
+explicit strip counts) at the edges of its tiles, slots and launch shapes."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle.power_iteration import spectral_step as oracle_step
+from workloads import WORKLOADS, all_weights, start_vectors
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # pragma: no cover - collected on CPU machines, skipped there
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+from paper_2602_18851_amd import Spectral  # noqa: E402
+from paper_2602_18851_amd import spectral as sp  # noqa: E402
+
+# sigma: fp32 sums, about 1e-7; vectors: the grouped key products split fp32
+# vectors into two bf16 halves (2^-17 = 8e-6), which a head whose two largest
+# singular values lie close together can carry on a few times larger.  The
+# sweeps take sigma itself through such halves (twice per step), and at d = 1
+# no sum over columns averages their errors.
+SIGMA_TOL, VEC_TOL, SWEEP_SIGMA_TOL = 2e-6, 1e-4, 2e-5
+
+CASES = [
+    # (id, layers, d, pad, n_kv, group, d_h, dtype)
+    ("one-tile", 1, 64, 0, 2, 1, 64, "bf16"),                 # one whole tile
+    ("one-column", 1, 1, 7, 2, 3, 64, "bf16"),                # a single column, ragged only
+    ("tile-and-one", 1, 65, 7, 2, 2, 32, "bf16"),             # unaligned rows of v: 4-byte loads
+    ("dh16-f32-17-heads", 1, 100, 0, 2, 17, 16, "f32"),       # two z0 operands of 16 heads
+    ("dh16-bf16", 2, 333, 3, 3, 1, 16, "bf16"),
+    ("dh32-6-heads", 1, 200, 0, 2, 6, 32, "bf16"),            # three parts: 5 + 1 heads
+    ("dh64-9-heads", 1, 1001, 7, 2, 9, 64, "bf16"),           # two parts: 8 + 1 heads
+    ("dh128-8-heads", 2, 1000, 0, 3, 8, 128, "bf16"),
+    ("dh128-f32", 1, 1003, 1, 2, 2, 128, "f32"),              # unaligned rows of v
+    ("own-dh128", 2, 136, 0, 128, 1, 128, "bf16"),            # 256 heads: Q and K by one workgroup
+    ("own-dh64-f32", 4, 203, 1, 65, 1, 64, "f32"),
+    ("keys-dh64", 4, 200, 0, 32, 2, 64, "bf16"),              # 256 heads: Q by one workgroup, K by another
+    ("keys-dh32-f32", 2, 257, 3, 9, 16, 32, "f32"),
+    ("keys-dh128-chunks", 4, 64, 0, 200, 2, 128, "bf16"),     # more key heads than one launch pair takes
+]
+
+
+def _workload(layers, d, n_kv, group, dh, dtype, n_iter=6):
+    return WORKLOADS["llama2-70b-gqa"].replace(key="heads", cfg_id=77, n_layers=layers, d_model=d, n_q=n_kv * group,
+                                               n_kv=n_kv, head_dim=dh, dtype=dtype, n_iter=n_iter, std=0.02)
+
+
+def _padded(w, pad):
+    if not pad:
+        return w.cuda()
+    p = torch.full((*w.shape[:2], w.shape[2] + pad), float("nan"), dtype=w.dtype)  # columns past d are never used
+    p[:, :, :w.shape[2]] = w
+    return p.cuda()[:, :, :w.shape[2]]
+
+
+def _run(wl, wq, wk, v0, ld=0, **kw):
+    est = Spectral(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha, ld=ld, **kw)
+    v = v0.cuda().clone()
+    u = torch.empty_like(v)
+    sigma, scale, iters = est.step(wq, wk, v, wl.n_iter, u=u)
+    torch.cuda.synchronize()
+    est.close()
+    return {k: t.cpu().double().numpy() for k, t in
+            dict(sigma=sigma, scale=scale, iters=iters, v=v, u=u).items()}
+
+
+def _check(got, ref, what, sigma_tol=SIGMA_TOL, vec_tol=VEC_TOL):
+    np.testing.assert_array_equal(got["iters"], ref["iters"], err_msg=what)
+    for k, tol in (("sigma", sigma_tol), ("scale", sigma_tol)):
+        err = np.max(np.abs(got[k] - ref[k]) / np.abs(ref[k]))
+        assert err <= tol, (what, k, err)
+    for k in ("v", "u"):
+        err = np.linalg.norm(got[k] - ref[k], axis=-1).max()
+        assert err <= vec_tol, (what, k, err)
+
+
+@pytest.mark.parametrize("layers,d,pad,n_kv,group,dh,dtype", [c[1:] for c in CASES], ids=[c[0] for c in CASES])
+def test_heads_against_oracle_and_sweeps(layers, d, pad, n_kv, group, dh, dtype):
+    wl = _workload(layers, d, n_kv, group, dh, dtype)
+    wq, wk = all_weights(wl, "cpu")
+    v0 = start_vectors(wl, "cpu")
+    gq, gk, ld = _padded(wq, pad), _padded(wk, pad), d + pad
+    ref = oracle_step(wq.float().numpy(), wk.float().numpy(), v0.double().numpy(), wl.n_iter, n_kv=n_kv, head_dim=dh,
+                      alpha=wl.alpha, want_u=True)
+    heads = _run(wl, gq, gk, v0, ld)
+    _check(heads, ref, "heads")
+    _check(_run(wl, gq, gk, v0, ld, q_strips=1, k_strips=1), heads, "sweeps", SWEEP_SIGMA_TOL)
+
+
+@pytest.mark.parametrize("layers,n_kv,group", [(1, 2, 2), (4, 65, 1), (4, 33, 2)], ids=["split", "own", "keys"])
+def test_cancelling_rows(layers, n_kv, group):
+    """Rows that share a large common part, which key rows summing to zero make
+    cancel in Q^T z: sigma^2 = z^T G_Q z loses all its digits in fp32 (shown
+    here with exact Gram matrices), so these heads have to be iterated on the
+    weights.  There Q^T z rounds at 6e-8 of the common part, about 1e-4 of
+    sigma (the common part is 1e3 times the rest)."""
+    dh, d = 16, 96
+    wl = _workload(layers, d, n_kv, group, dh, "f32", n_iter=4)
+    wq, wk = all_weights(wl, "cpu")
+    g = torch.Generator().manual_seed(5)
+    common = torch.randn(layers, n_kv * group, 1, d, generator=g) * 20.0
+    wq = (wq.view(layers, -1, dh, d) + common).reshape(wq.shape)
+    wk = wk.view(layers, n_kv, dh, d)
+    wk = (wk - wk.double().mean(dim=2, keepdim=True).float()).reshape(layers, n_kv * dh, d)
+    v0 = start_vectors(wl, "cpu")
+    qd, kd = wq[0, :dh].double().numpy(), wk[0, :dh].double().numpy()
+    z = kd @ v0[0, 0].double().numpy()
+    g32, z32 = (qd @ qd.T).astype(np.float32), z.astype(np.float32)
+    gram, true = float(z32 @ (g32 @ z32)), float(np.sum((qd.T @ z) ** 2))
+    assert abs(gram - true) > 0.1 * true
+    ref = oracle_step(wq.numpy(), wk.numpy(), v0.double().numpy(), wl.n_iter, n_kv=n_kv, head_dim=dh, alpha=wl.alpha,
+                      want_u=True)
+    gq, gk = wq.cuda(), wk.cuda()
+    _check(_run(wl, gq, gk, v0, q_strips=1, k_strips=1), ref, "sweeps", 1e-3, 5e-3)
+    _check(_run(wl, gq, gk, v0), ref, "heads", 1e-3, 5e-3)
+
+
+def test_values_outside_the_range_of_gram_products():
+    """Query weights near 1e-20 and key weights near 1e18: the products in G_Q
+    underflow, those in G_K overflow, and u' = Q^T z is an ordinary number."""
+    wl = _workload(2, 200, 2, 2, 32, "f32")
+    wq, wk = all_weights(wl, "cpu")
+    wq, wk = wq * 2.0 ** -60, wk * 2.0 ** 66
+    v0 = start_vectors(wl, "cpu")
+    ref = oracle_step(wq.numpy(), wk.numpy(), v0.double().numpy(), wl.n_iter, n_kv=2, head_dim=32, alpha=wl.alpha,
+                      want_u=True)
+    _check(_run(wl, wq.cuda(), wk.cuda(), v0), ref, "heads")
+
+
+def test_noalloc_gives_the_same_bits_in_several_launch_pairs():
+    """The static scratch leaves room for fewer key heads per launch pair than
+    a context; the results do not depend on it."""
+    wl = _workload(4, 64, 200, 2, 128, "bf16")
+    gq, gk = all_weights(wl, "cuda")
+    v0 = start_vectors(wl, "cuda")
+    ref = _run(wl, gq, gk, v0)
+    v, u = v0.clone(), torch.empty_like(v0)
+    sigma = torch.empty(wl.n_layers, wl.n_q, device="cuda")
+    scale, iters = torch.empty(wl.n_layers, device="cuda"), torch.empty(sigma.shape, dtype=torch.int32, device="cuda")
+    shape = sp.sn_shape(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, sp.SN_BF16, 0)
+    sp.spectral_step_noalloc(shape, sp.sn_params(wl.alpha, 0.8, 448.0, 0.0, 0, 0, 0),
+                             [t.data_ptr() for t in gq.unbind(0)], [t.data_ptr() for t in gk.unbind(0)], v.data_ptr(),
+                             u.data_ptr(), wl.n_iter, sigma.data_ptr(), scale.data_ptr(), iters.data_ptr(),
+                             torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    for k, t in dict(v=v, u=u, sigma=sigma, scale=scale, iters=iters).items():
+        np.testing.assert_array_equal(t.cpu().double().numpy(), ref[k], err_msg=k)

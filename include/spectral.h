@@ -147,12 +147,13 @@ SN_API int spectral_init(sn_ctx** ctx, const sn_shape* shape, const sn_params* p
  *              -1 if the start vector is zero or not finite (sigma = NaN,
  *              v unchanged, u = 0); -2 if M v = 0 (sigma = 0, v normalised
  *              start vector, u = 0).
- * Calls of a fixed count n_iter >= 2 with head_dim >= 16, automatic strips
- * and no SN_FLAG_VALU_K_SWEEP run the Gram form (see SN_FLAG_GRAM), whose
- * iterates are those of the sweeps up to rounding; the others run n_iter
- * pairs of sweeps over the weights.
+ * With head_dim >= 16, automatic strips and no SN_FLAG_VALU_K_SWEEP, calls
+ * of a fixed count n_iter >= 2, and calls with tol > 0 and n_iter > 2 over
+ * 64 MiB of weights or more, run the Gram form (see SN_FLAG_GRAM), whose
+ * iterates are those of the sweeps up to rounding; the others run sweeps
+ * over the weights, two per iteration.
  * The call is queued asynchronously on the context's stream and never waits
- * on the host.  With tol > 0 and head_dim >= 16, the first two steps (the
+ * on the host.  On the sweeps, with tol > 0 and head_dim >= 16, the first two steps (the
  * fewest the stopping rule allows) run as sweeps over all heads; then one
  * fixed sequence of launches lists the heads still running on the device,
  * forms their Gram matrices G_Q = Q_h Q_h^T and G_K = K_j K_j^T (see

@@ -13,8 +13,8 @@
 //   heads_kernel: one workgroup per query head reads Q_h once, forms G_Q in
 //     registers, loads G_K (or, with g = 1, streams K_h first and forms G_K,
 //     z0 and ||v|| itself), iterates to the count or the tolerance and leaves
-//     z / sigma and y / ||v'|| of the last step, which the final sweeps map to
-//     u and v, already normalised.
+//     z / sigma and y of the last step with 1 / ||K^T y||, which the final sweeps
+//     map to u and v, already normalised.
 // Against n_iter pairs of sweeps, whole calls on one box: 70B GQA shape, 30
 // iterations 56.1 -> 2.56 ms; Llama-2-7B shape 10.5 -> 0.66 ms; GPT-2 XL shape
 // with u 2.55 -> 0.32 ms; GPT-2 small, 20 iterations 405 -> 78 us; 5
@@ -553,9 +553,14 @@ __device__ __forceinline__ void memory_to_lds(const float* src, int strips, floa
       ++bi;
     }
     const int bj = bi + (b - start);
-    f32x4 y = in[x];
+    f32x4 y = in[x], lost = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
-    for (int st = 1; st < strips; ++st) y += in[(size_t)st * S::NB * 64 + x];
+    for (int st = 1; st < strips; ++st) {  // two-sum, as in stream_block
+      const f32x4 p = in[(size_t)st * S::NB * 64 + x], sum = y + p, b = sum - y;
+      lost += (y - (sum - b)) + (p - b);
+      y = sum;
+    }
+    y += lost;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int r = 16 * bi + 4 * (ln >> 4) + e, c = 16 * bj + (ln & 15);
@@ -693,15 +698,26 @@ __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(
   }
 
   float* fin = a.w.fin + (size_t)h * 2 * DH;
-  auto finish = [&](int k, float sig, const float* z, float zs, const float* y, float ys) {
+  auto finish = [&](int k, float sig, const float* z, float zs, const float* y, float rn) {
     if (t < DH) {
       fin[t] = z[t] * zs;
-      fin[DH + t] = y[t] * ys;
+      fin[DH + t] = a.round_y ? y[t] : y[t] * rn;
     }
     if (t == 0) {
       a.sigma[h] = sig;
       a.iters[h] = k;
+      a.w.sig[h] = rn;  // read by the final W_K sweep with round_y
     }
+  };
+  // y = w / sigma of the last step, in place; with round_y as the final W_K
+  // sweep will take it, so that ||K^T y|| is the norm of what that sweep writes
+  auto last_y = [&](float inv) {
+    if (t < DH) {
+      const float y = wb[t] * inv;
+      const float hi = (float)(__bf16)y;
+      wb[t] = a.round_y ? hi + (float)(__bf16)(y - hi) : y;
+    }
+    __syncthreads();
   };
   auto stop = [&](int k, float sig, float prev) {
     return k >= a.n_iter || (a.tol > 0.f && k >= 2 && fabsf(sig - prev) <= a.tol * sig);
@@ -738,9 +754,11 @@ __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(
       __syncthreads();
       const float s2 = sum_waves<kHWaves>(red[0]);
       if (!(s2 >= kCancel * sum_waves<kHWaves>(red[1])) || !(s2 >= kTiny)) break;
-      const float sig = sqrtf(s2), inv = 1.0f / sig;
+      const float sig = sqrtf(s2), inv_sig = 1.0f / sig;
       const bool last = stop(k, sig, prev);
       // t = G_K y with y = w / sigma
+      if (last) last_y(inv_sig);
+      const float inv = last ? 1.f : inv_sig;
       matvec<RPT>(gk, wb, C, out);
       part = 0.f;
       bound = 0.f;
@@ -764,7 +782,7 @@ __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(
       if (!(n2 >= kCancel * sum_waves<kHWaves>(red[3])) || !(n2 >= kTiny)) break;
       const float rn = 1.0f / sqrtf(n2);
       if (last) {
-        finish(k, sig, tb, zscale * inv, wb, inv * rn);
+        finish(k, sig, tb, zscale * inv_sig, wb, rn);
         return;
       }
       zscale = rn;
@@ -792,8 +810,12 @@ __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(
     }
     const bool last = stop(k, sig, prev);
     const float inv = 1.0f / sig;
-    if (t < DH) wb[t] *= inv;
-    __syncthreads();
+    if (last) {
+      last_y(inv);
+    } else {
+      if (t < DH) wb[t] *= inv;
+      __syncthreads();
+    }
     const float n2 = direct_sweep<T, DH>(kblk, a.ld, a.d, wb, dq, part, red[0], wv, lane);
     const float rn = 1.0f / sqrtf(n2);
     if (last) {

@@ -79,6 +79,7 @@ struct SweepArgs {
   float tol;
   const int32_t* list;      // tail launches: the decoded unit of item index r is list[r]
   const int32_t* ctl;       // tail launches: count, strips, tiles per strip at ctl[0..2] (else nullptr)
+  const float* vscale;      // final W_K sweep on the matrix cores: factor of each head's v' (nullptr: 1)
   const int32_t* only;      // final sweeps of the tail: a head takes part only if only[head] != 0
   Work w;
   float* v;
@@ -138,6 +139,7 @@ struct HeadArgs {
   int32_t unit0, units, head0;
   int32_t sk, tps_k;        // column strips of a key head, and tiles per strip
   int32_t sq, tps_q;        // ... of a query head; sq = 0: its own workgroup reads all of it
+  int32_t round_y;          // the final W_K sweep takes y as two bf16 halves and 1 / ||v'|| from w.sig
   int32_t np, hps, nch;     // bf16 parts per start vector, heads per z0 operand, operands per key head
   int32_t n_iter;
   float tol;
@@ -146,7 +148,7 @@ struct HeadArgs {
   float* gq;                // [heads][sq][NB][64][4]: G_Q partials
   float* zp;                // [heads][sk][DH]: partials of K_j v
   float* zn;                // [heads][sk]: partials of ||v||^2
-  Work w;                   // fin and vnorm0
+  Work w;                   // fin, vnorm0 and sig
   float* sigma;
   int32_t* iters;
 };

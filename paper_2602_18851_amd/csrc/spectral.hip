@@ -621,11 +621,24 @@ bool heads_call(const sn_ctx* c, int n_iter) {
   if (!pl.heads) return false;
   if (pl.gram) return true;
   if (p.q_strips > 0 || p.k_strips > 0 || (p.flags & SN_FLAG_VALU_K_SWEEP)) return false;
-  return n_iter >= 2 && !(p.tol > 0.f);
+  if (p.tol > 0.f) {
+    // A stop at step 2, the earliest, costs the sweeps five passes over the
+    // weights and a tail for the heads still running.  Warm calls that stop
+    // there for nearly every head, sweeps and tail against here: 12 GB of
+    // weights (70B GQA shape) 4.18 -> 2.33 ms, 0.5 GB 387 -> 188 us, 151 MB
+    // 230 -> 126 us, 31 MB 112 -> 75 us.  Below 64 MB, where the weights stay
+    // in the Infinity Cache and launches are what is left to gain, calls keep
+    // the sweeps and the tail.
+    const int64_t bytes = (int64_t)c->shape.n_layers * (c->shape.n_q_heads + c->shape.n_kv_heads) *
+                          c->shape.head_dim * c->shape.d_model * esize(c->shape.dtype);
+    return n_iter > kTailSteps && bytes >= (int64_t(64) << 20);
+  }
+  return n_iter >= 2;
 }
 
 // The Gram form with one workgroup per head (gram_heads.hip), then the final
-// sweeps, which find z / sigma and y / ||v'|| and so write unit vectors.
+// sweeps, which write unit vectors: they find z / sigma, and y with its factor
+// 1 / ||v'||.
 int run_heads(sn_ctx* c, SweepArgs a, float* u) {
   const Plan& pl = c->plan;
   const int n_units = c->shape.n_layers * c->shape.n_kv_heads, dh = c->shape.head_dim;
@@ -641,6 +654,7 @@ int run_heads(sn_ctx* c, SweepArgs a, float* u) {
   h.n_iter = a.n_iter;
   h.tol = a.tol;
   h.v = a.v;
+  h.round_y = pl.mfma_k;
   h.sk = pl.h_sk;
   h.tps_k = pl.h_tps_k;
   h.sq = pl.h_sq;
@@ -665,6 +679,7 @@ int run_heads(sn_ctx* c, SweepArgs a, float* u) {
     if (rc != SN_OK) return rc;
   }
   a.k = 0;
+  if (h.round_y) a.vscale = a.w.sig;
   if ((rc = run_sweep(c, PH_EK, a)) != SN_OK) return rc;
   if (u && (rc = run_sweep(c, PH_EQ, a)) != SN_OK) return rc;
   return SN_OK;

@@ -537,6 +537,12 @@ ksweep_mfma_kernel(SweepArgs args) {
   const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(blk, nrec);
   const uint32_t row_bytes = (uint32_t)(a.ld * ES);
 
+  float vs0 = 1.f, vs1 = 1.f;  // factors of heads 2g, 2g + 1
+  if (PH == PH_EK && a.vscale) {
+    vs0 = act0 ? a.vscale[head0 + 2 * g] : 1.f;
+    vs1 = act1 ? a.vscale[head0 + 2 * g + 1] : 1.f;
+  }
+
   f32x4 zacc[RB];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) zacc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -653,8 +659,8 @@ ksweep_mfma_kernel(SweepArgs args) {
         nrm0 = fmaf(v0, v0, nrm0);
         nrm1 = fmaf(v1, v1, nrm1);
         if (inside) {
-          if (last0) a.v[(size_t)(head0 + 2 * g) * a.d + col] = v0;
-          if (last1) a.v[(size_t)(head0 + 2 * g + 1) * a.d + col] = v1;
+          if (last0) a.v[(size_t)(head0 + 2 * g) * a.d + col] = PH == PH_EK ? v0 * vs0 : v0;
+          if (last1) a.v[(size_t)(head0 + 2 * g + 1) * a.d + col] = PH == PH_EK ? v1 * vs1 : v1;
         }
         if (!PROD2) continue;
         const __bf16 h0 = (__bf16)v0, h1 = (__bf16)v1;

@@ -148,3 +148,34 @@ def test_noalloc_gives_the_same_bits_in_several_launch_pairs():
     torch.cuda.synchronize()
     for k, t in dict(v=v, u=u, sigma=sigma, scale=scale, iters=iters).items():
         np.testing.assert_array_equal(t.cpu().double().numpy(), ref[k], err_msg=k)
+
+
+def test_tolerance_calls_over_64_mib_of_weights():
+    """Large tolerance calls iterate in the per-head kernel: the stop of every
+    head against the oracle's own sequence (10% of the threshold, the precision
+    of the difference of two estimates), and its vectors at that step."""
+    from oracle.power_iteration import head_slices, power_iteration
+
+    wl = WORKLOADS["llama2-70b-perstep"].replace(key="tol-heads", cfg_id=78, n_layers=2, d_model=2048, n_q=64, n_kv=8)
+    assert sum(wl.weight_bytes()) >= 64 << 20
+    wq, wk = all_weights(wl, "cpu")
+    v0 = start_vectors(wl, "cpu")
+    est = Spectral(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha, tol=wl.tol)
+    v = v0.cuda()
+    est.profile(True)
+    sigma, _, iters = est.step(wq.cuda(), wk.cuda(), v, wl.n_iter)
+    torch.cuda.synchronize()
+    prof = est.profile_read()
+    est.close()
+    assert prof["q_sweep"][1] == 0 and prof["gram_iterate"][1] == 1
+    it, sig, vv = iters.cpu().numpy(), sigma.cpu().double().numpy(), v.cpu().double().numpy()
+    wqf, wkf = wq.float().numpy(), wk.float().numpy()
+    for l in range(wl.n_layers):
+        for h in range(0, wl.n_q, 5):
+            q, k = head_slices(wqf[l], wkf[l], h, wl.n_kv, wl.head_dim)
+            n = int(it[l, h])
+            r = power_iteration(q, k, v0[l, h].double().numpy(), n)
+            change = [abs(b - a) / (wl.tol * b) for a, b in zip(r.history, r.history[1:])]
+            assert n >= 2 and change[-1] <= 1.1 and min(change[:-1], default=1.0) >= 0.9, (l, h, n)
+            assert abs(sig[l, h] - r.sigma) <= SIGMA_TOL * r.sigma
+            assert np.linalg.norm(vv[l, h] - r.v) <= VEC_TOL

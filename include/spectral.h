@@ -113,8 +113,11 @@ typedef struct {
 /* Reserve the workspace of the layer-level form (spectral_step_layer): the
  * row-sweep partials, one d_h-vector per query head, the column sums (one row
  * of d_model rounded up to 64 per layer and row split, up to n_q splits on
- * small shapes) and per-layer vectors; spectral_workspace_bytes gives the
- * total.  spectral_step itself is unaffected. */
+ * small shapes) and per-layer vectors; with grouped heads and up to 1024 key
+ * rows (n_kv * head_dim) per layer also the sums of each group's query rows
+ * in float32, for as many layers at a time as fit 1 GiB.
+ * spectral_workspace_bytes gives the total.  spectral_step itself is
+ * unaffected. */
 #define SN_FLAG_LAYER 4
 
 

@@ -29,6 +29,9 @@ constexpr int kMTileC = 64;                // columns per tile: 128-byte row seg
 constexpr int kGWaves = 4;                 // waves per workgroup of the Gram sweep
 constexpr int kGTargetItems = 4096;        // Gram work items aimed for (about two waves per SIMD)
 constexpr int kHWaves = 4;                 // waves per workgroup of the one-workgroup-per-head Gram form
+constexpr int kLFWaves = 16;               // most waves of a one-pass layer sweep (one workgroup per CU then)
+constexpr int kLFRowsPerWave = 64;         // rows each wave holds of a column tile
+constexpr int kLFRows = kLFWaves * kLFRowsPerWave;
 constexpr int kRedThreads = 512;
 
 // Sweep phases: the first W_K sweep from v, the W_Q and W_K sweeps of a step,
@@ -173,6 +176,32 @@ struct LayerArgs {
   int32_t cstride;          // multiple of 64 and >= d
 };
 
+// A one-pass sweep of the layer form over a layers' chunk, and the gather
+// after it.
+struct LayerFusedArgs {
+  const void* const* mats;  // device table of per-layer pointers, or nullptr:
+  const float* dense;       // ... fp32 [chunk layers][rows][ld]
+  int64_t ld;
+  int32_t d, n_tiles, rows, strips, tps, layer0;
+  int32_t mode;             // gather: 0 start vectors, 1 after W_Q, 2 after W_K
+  const float* v;           // first sweep: the start vectors [L][d]
+  float* vec;               // [L][d]: receives u' (v') unnormalised, or nullptr
+  float* x;                 // [L][rows]: the sweep's input, written by the gather before it
+  float* part;              // [chunk layers][strips][rows]
+  float* n2part;            // [chunk layers][strips]
+  float* n2;                // [L]
+  float* n2_start;          // [L]
+  int32_t* lstat;           // [L]
+};
+
+struct GroupSumArgs {
+  const void* const* wq;    // device table
+  int64_t ld;
+  int32_t d, rows, dh, g, layer0;
+  int32_t ldq;              // padded row length of the sums, a multiple of 32
+  float* out;               // [chunk layers][rows][ldq]
+};
+
 // Inputs of a column sweep, one d_h-vector per row block of the swept matrix:
 // vin[l][b] = sum over the cnt source units starting at (b / div) * cnt of
 // their strip partials (src_units units per layer, strips strips each), in
@@ -236,6 +265,9 @@ void launch_gram_iterate(int head_dim, int heads, hipStream_t st, const IterArgs
 void launch_heads(bool bf16, int head_dim, bool units, hipStream_t st, HeadArgs a);
 void launch_heads_finalize(int layers, hipStream_t st, const FinArgs& f);
 void launch_layer_sweep(bool bf16, int head_dim, int mode, int n_items, hipStream_t st, const LayerArgs& a);
+void launch_layer_fused(bool bf16, bool init, int layers, hipStream_t st, const LayerFusedArgs& a);
+void launch_layer_gather(int layers, hipStream_t st, const LayerFusedArgs& a);
+void launch_group_sum(bool bf16, int layers, hipStream_t st, const GroupSumArgs& a);
 void launch_layer_vin(int layers, hipStream_t st, const LayerVinArgs& v);
 void launch_layer_reduce(int layers, hipStream_t st, const LayerReduceArgs& r);
 void launch_layer_finalize(int layers, hipStream_t st, const LayerFinArgs& f);

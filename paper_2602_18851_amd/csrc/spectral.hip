@@ -67,6 +67,10 @@ struct Plan {
   int s_lq, tps_lq, s_lk, tps_lk;  // strips of the layer-form row sweeps over W_Q and W_K
   int rs_q, rbp_q, rs_k, rbp_k;    // row splits (and row blocks per split) of its column sweeps
   size_t off_zp, off_zn, off_yp, off_yn, off_sig, off_vn, off_alive, off_iters, off_fin, off_gp;
+  bool fused;      // its one-pass sweeps apply
+  int lf_layers, lf_ldq;                    // layers per chunk, row length of the group sums (grouped heads)
+  int lf_sq, lf_tq, lf_sk, lf_tk;           // strips and tiles per strip over W_Q (or the group sums) and W_K
+  size_t off_lsum, off_lx, off_lpart, off_lnp;
   size_t off_lz, off_ly, off_lvin, off_lcol, off_lu, off_lv, off_ln2, off_ln2p, off_lstat;
   size_t off_zs, off_lg, off_lk, off_kvpos, off_ctl, off_zt;
   bool heads;   // calls of two or more iterations may run the Gram form with one workgroup per head
@@ -123,6 +127,54 @@ void strips(int n_tiles, int64_t units, int requested, int target, bool round_do
   const int tps = ceil_div(n_tiles, s);
   *tps_out = tps;
   *s_out = ceil_div(n_tiles, tps);
+}
+
+// Bytes the group sums of the layer form may take: a chunk of layers at a
+// time (29 layers of the 70B GQA shape).
+constexpr int64_t kGroupSumBytes = int64_t(1) << 30;
+
+// The one-pass sweeps of the layer form: the rows of a layer after grouping
+// have to fit the registers of one workgroup.  Strips: the fewest rounds of
+// workgroups over the chip, each round costing its tiles and about half a tile
+// of set-up.
+void plan_fused(const sn_shape* s, Plan& pl) {
+  const int dh = s->head_dim, rows = s->n_kv_heads * dh, es = esize(s->dtype), d = s->d_model;
+  const int64_t ld = s->ld == 0 ? d : s->ld;
+  pl.lf_ldq = ceil_div(d, 32) * 32;
+  const int64_t layer = (int64_t)rows * pl.lf_ldq * 4;
+  pl.fused = (int64_t)s->n_kv_heads * dh <= kLFRows && kLFRowsPerWave * std::max<int64_t>(ld * es, pl.lf_ldq * 4) < (int64_t(1) << 31) &&
+             (pl.g == 1 || layer <= kGroupSumBytes);
+  if (!pl.fused) return;
+  pl.lf_layers = s->n_layers;
+  if (pl.g > 1) {
+    const int chunks = ceil_div(s->n_layers, std::max<int64_t>(1, kGroupSumBytes / layer));
+    pl.lf_layers = ceil_div(s->n_layers, chunks);
+  }
+  const int slots = 256 * std::max(1, kLFWaves / ceil_div(rows, kLFRowsPerWave));
+  auto best = [&](int tiles, int* strips_out, int* tps_out) {
+    double cost = 1e30;
+    for (int tps = 1; tps <= std::min(tiles, 4096); ++tps) {
+      const int st = ceil_div(tiles, tps);
+      const double c = (double)ceil_div((int64_t)pl.lf_layers * st, slots) * (tps + 0.5);
+      if (c < cost) {
+        cost = c;
+        *strips_out = st;
+        *tps_out = tps;
+      }
+    }
+  };
+  best(ceil_div((int64_t)d * (pl.g > 1 ? 4 : es), 128), &pl.lf_sq, &pl.lf_tq);
+  best(ceil_div((int64_t)d * es, 128), &pl.lf_sk, &pl.lf_tk);
+}
+
+// Whether a layer-form call runs them: with grouped heads where forming and
+// reading the fp32 group sums (4 / (g es) of W_Q's bytes) moves less than
+// reading W_Q twice per iteration.
+bool fused_call(const Plan& pl, int dtype, int n_iter) {
+  if (!pl.fused) return false;
+  if (pl.g == 1) return true;
+  const double r = 4.0 / (pl.g * esize(dtype));
+  return 1.0 + r * (1 + n_iter) < 2.0 * n_iter;
 }
 
 // Bytes of Gram matrices one launch pair of the one-workgroup-per-head form
@@ -264,6 +316,14 @@ Plan make_plan(const sn_shape* s, const sn_params* p, int64_t slack = -1) {
     pl.off_ln2 = take(3 * L * 4);
     pl.off_ln2p = take(L * (size_t)ceil_div(d, kRedThreads) * 4);
     pl.off_lstat = take(L * 4);
+    plan_fused(s, pl);
+    if (pl.fused) {
+      const size_t rows = (size_t)s->n_kv_heads * dh, c = pl.lf_layers, smax = std::max(pl.lf_sq, pl.lf_sk);
+      if (pl.g > 1) pl.off_lsum = take(c * rows * pl.lf_ldq * 4);
+      pl.off_lx = take(L * rows * 4);
+      pl.off_lpart = take(c * smax * rows * 4);
+      pl.off_lnp = take(c * smax * 4);
+    }
   }
   pl.bytes = off;
   return pl;
@@ -504,6 +564,90 @@ int layer_reduce(sn_ctx* c, const float* col, int units, int cstride, int mode, 
   r.lstat = reinterpret_cast<int32_t*>(c->ws + pl.off_lstat);
   return timed(c, KIND_LRED,
                [&] { launch_layer_reduce(c->shape.n_layers, c->stream, r); });
+}
+
+// One layer-form call with one-pass sweeps: per chunk of layers the group
+// sums, the first W_K sweep, then per iteration a sweep over the sums (g = 1:
+// W_Q) and one over W_K, each followed by the gather of its row sums.
+int run_layer_fused(sn_ctx* c, const float* v, bool want_u, int n_iter, float* lu, float* lv, float* n2) {
+  const Plan& pl = c->plan;
+  const sn_shape& sh = c->shape;
+  const int L = sh.n_layers, rows = sh.n_kv_heads * sh.head_dim;
+  const bool bf16 = sh.dtype == SN_BF16;
+  float* sums = pl.g > 1 ? reinterpret_cast<float*>(c->ws + pl.off_lsum) : nullptr;
+  LayerFusedArgs k{};
+  k.mats = c->tab + L;
+  k.ld = sh.ld;
+  k.d = sh.d_model;
+  k.n_tiles = ceil_div((int64_t)sh.d_model * esize(sh.dtype), 128);
+  k.rows = rows;
+  k.strips = pl.lf_sk;
+  k.tps = pl.lf_tk;
+  k.v = v;
+  k.x = reinterpret_cast<float*>(c->ws + pl.off_lx);
+  k.part = reinterpret_cast<float*>(c->ws + pl.off_lpart);
+  k.n2part = reinterpret_cast<float*>(c->ws + pl.off_lnp);
+  k.n2_start = n2 + 2 * L;
+  k.lstat = reinterpret_cast<int32_t*>(c->ws + pl.off_lstat);
+  LayerFusedArgs q = k;
+  q.mats = c->tab;
+  q.strips = pl.lf_sq;
+  q.tps = pl.lf_tq;
+  if (sums) {
+    q.mats = nullptr;
+    q.dense = sums;
+    q.ld = pl.lf_ldq;
+    q.n_tiles = ceil_div(sh.d_model, 32);
+  }
+  q.mode = 1;
+  q.n2 = n2;
+  k.n2 = n2 + L;
+  int rc;
+  for (int l0 = 0; l0 < L; l0 += pl.lf_layers) {
+    const int nl = std::min(pl.lf_layers, L - l0);
+    q.layer0 = k.layer0 = l0;
+    auto sweep = [&](bool is_q, bool init, const LayerFusedArgs& a) {
+      int e = timed(c, is_q ? KIND_LCOLS : KIND_LROWS,
+                    [&] { launch_layer_fused(is_q && sums ? false : bf16, init, nl, c->stream, a); });
+      if (e != SN_OK) return e;
+      return timed(c, KIND_LRED, [&] { launch_layer_gather(nl, c->stream, a); });
+    };
+    if (sums) {
+      GroupSumArgs g{c->tab, sh.ld, sh.d_model, rows, sh.head_dim, pl.g, l0, pl.lf_ldq, sums};
+      if ((rc = timed(c, KIND_LRED, [&] { launch_group_sum(bf16, nl, c->stream, g); })) != SN_OK) return rc;
+    }
+    k.mode = 0;
+    k.vec = nullptr;
+    if ((rc = sweep(false, true, k)) != SN_OK) return rc;
+    k.mode = 2;
+    for (int i = 1; i <= n_iter; ++i) {
+      q.vec = i == n_iter && want_u ? lu : nullptr;
+      k.vec = i == n_iter ? lv : nullptr;
+      if ((rc = sweep(true, false, q)) != SN_OK) return rc;
+      if ((rc = sweep(false, false, k)) != SN_OK) return rc;
+    }
+  }
+  return SN_OK;
+}
+
+int layer_finalize(sn_ctx* c, float* v, float* u, float* sigma, float* scale, const float* lu, const float* lv,
+                   const float* n2_u) {
+  const int L = c->shape.n_layers;
+  LayerFinArgs f{};
+  f.d = c->shape.d_model;
+  f.L = L;
+  f.coef = scale_coef(c);
+  f.lstat = reinterpret_cast<const int32_t*>(c->ws + c->plan.off_lstat);
+  f.lu = lu;
+  f.lv = lv;
+  f.n2_u = n2_u;
+  f.n2_v = n2_u + L;
+  f.n2_start = n2_u + 2 * L;
+  f.v = v;
+  f.u = u;
+  f.sigma = sigma;
+  f.scale = scale;
+  return timed(c, KIND_LRED, [&] { launch_layer_finalize(L, c->stream, f); });
 }
 
 GramArgs gram_args(const sn_ctx* c) {
@@ -962,6 +1106,10 @@ SN_API int spectral_step_layer(sn_ctx* c, const void* const* wq_layers, const vo
   float* lv = reinterpret_cast<float*>(c->ws + pl.off_lv);
   float* n2_u = reinterpret_cast<float*>(c->ws + pl.off_ln2);
   float* n2_v = n2_u + L;
+  if (fused_call(pl, c->shape.dtype, n_iter)) {
+    if ((rc = run_layer_fused(c, v, u != nullptr, n_iter, lu, lv, n2_u)) != SN_OK) return rc;
+    return layer_finalize(c, v, u, sigma, scale, lu, lv, n2_u);
+  }
   // start vectors: copy, squared norms, layer status
   if ((rc = layer_reduce(c, v, 1, c->shape.d_model, 0, lv, n2_v)) != SN_OK) return rc;
   for (int k = 1; k <= n_iter; ++k) {
@@ -990,21 +1138,7 @@ SN_API int spectral_step_layer(sn_ctx* c, const void* const* wq_layers, const vo
     if ((rc = layer_sweep(c, false, LM_COLS, a)) != SN_OK) return rc;
     if ((rc = layer_reduce(c, lcol, pl.rs_k, col_stride(c->shape.d_model), 2, lv, n2_v)) != SN_OK) return rc;
   }
-  LayerFinArgs f{};
-  f.d = c->shape.d_model;
-  f.L = L;
-  f.coef = scale_coef(c);
-  f.lstat = reinterpret_cast<const int32_t*>(c->ws + pl.off_lstat);
-  f.lu = lu;
-  f.lv = lv;
-  f.n2_u = n2_u;
-  f.n2_v = n2_v;
-  f.n2_start = n2_u + 2 * L;
-  f.v = v;
-  f.u = u;
-  f.sigma = sigma;
-  f.scale = scale;
-  return timed(c, KIND_LRED, [&] { launch_layer_finalize(L, c->stream, f); });
+  return layer_finalize(c, v, u, sigma, scale, lu, lv, n2_u);
 }
 
 SN_API int spectral_logits_workspace_bytes(const sn_shape* shape, int32_t seq_len, int64_t* bytes) {

@@ -107,7 +107,8 @@ typedef struct {
  * in d_h-space would lose digits, or whose weights lie near the ends of the
  * float range, is iterated on its weights instead.  Needs head_dim >= 16.  The workspace
  * grows by the Gram partials, 2 d_h (d_h + 16) bytes per query or key head
- * and column strip (spectral_workspace_bytes gives the total). */
+ * and column strip, twice that with head_dim <= 64, where they are kept as two
+ * floats per element (spectral_workspace_bytes gives the total). */
 #define SN_FLAG_GRAM 2
 
 /* Reserve the workspace of the layer-level form (spectral_step_layer): the

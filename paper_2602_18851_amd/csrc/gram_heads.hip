@@ -16,12 +16,11 @@
 //     z / sigma and y of the last step with 1 / ||K^T y||, which the final sweeps
 //     map to u and v, already normalised.
 // Against n_iter pairs of sweeps, whole calls on one box: 70B GQA shape, 30
-// iterations 56.1 -> 2.56 ms; Llama-2-7B shape 10.5 -> 0.66 ms; GPT-2 XL shape
-// with u 2.55 -> 0.32 ms; GPT-2 small, 20 iterations 405 -> 78 us; 5
-// iterations of 144 heads, d 3001, 261 -> 74 us.  Against the strip-wise Gram
+// iterations 54.2 -> 2.46 ms; Llama-2-7B shape 10.5 -> 0.66 ms; GPT-2 XL shape
+// with u 2.55 -> 0.26 ms; GPT-2 small, 20 iterations 405 -> 81 us; 5
+// iterations of 144 heads, d 3001, 261 -> 70 us.  Against the strip-wise Gram
 // form (gram.hip: one wave per Gram matrix, all matrices through memory) the
-// 70B call went from 3.28 to 2.56 ms.  heads_kernel streams at 6.7 TB/s there
-// with two steps and at 5.9 TB/s with 30.
+// 70B call went from 3.28 to 2.46 ms.
 //
 // Streaming.  The workgroup's four waves share a ring of row tiles (d_h rows
 // x 128 bytes) in LDS, filled by buffer loads straight to LDS; one bare
@@ -67,11 +66,8 @@ struct HShape {
   static constexpr int TC = 128 / ES;               // columns per tile
   static constexpr int RB = DH / 16, NB = RB * (RB + 1) / 2;
   static constexpr int STAGE = DH * 128;            // bytes of one tile
-  static constexpr int NST = DH == 128 ? 4 : DH == 64 ? 7 : 8;  // ring slots: with the start vectors' at most 72 KB
   static constexpr int VROW = TC * 4;               // bytes of one start vector's columns of a tile
   static constexpr int VCH = VROW / 16;             // ... in 16-byte chunks
-  static constexpr int VST = 2048;                  // start vectors of a tile: 8 heads (bf16) or 16 (fp32)
-  static constexpr int RING = NST * (STAGE + VST);
   static constexpr int NI = DH / 8;                 // 1 KB load instructions per tile
   static constexpr int NR = RB > 1 ? RB / 2 : 1;    // row blocks of a diagonal triangle
   static constexpr int NC = RB >= 4 ? RB / 4 : 1;   // column blocks of an off-diagonal half
@@ -79,9 +75,29 @@ struct HShape {
   static constexpr int NACC = NTRI > NR * NC ? NTRI : NR * NC;
   static constexpr int NZ = RB >= 4 ? RB / 2 : RB;  // row blocks of z0 per wave (2 and 3, or 2 alone)
   static constexpr int P = DH + 1;                  // LDS row pitch of a whole Gram matrix
-  static constexpr int RPT = DH / 16;               // rows (and columns) per thread in the iteration
-  static constexpr int BIG = RING > DH * P * 4 ? RING : DH * P * 4;
+  // d_h <= 64: a Gram matrix is kept as two floats per element and the
+  // iteration runs in double.  An error in G repeats in every step, where those
+  // of a sweep differ: with G and the vectors in float the error of v was 4.2e-7
+  // (d 768, fp32, 20 iterations), against 2.2e-7 of the sweeps.
+  static constexpr bool LOW = DH <= 64;
+  static constexpr int MAT = (LOW ? 2 : 1) * NB * 256;         // floats of a Gram matrix in memory
+  static constexpr int GL = (LOW ? 2 : 1) * DH * P * 4;        // bytes of a whole one in LDS
+  static constexpr int EU = DH == 128 ? 2 : 4;                 // workgroups per compute unit (waves per SIMD)
 };
+
+// The ring of a stream with VST bytes of start vectors beside each tile.  Two
+// workgroups per compute unit with d_h 128, whose registers allow no more; four
+// of at most 38 KB below: a workgroup that iterates streams nothing, and the
+// others have to fill the memory pipe meanwhile.
+template <typename T, int DH, int VST>
+struct HRing {
+  using S = HShape<T, DH>;
+  static constexpr int FIT = (DH == 128 ? 73728 : 38912) / (S::STAGE + VST);
+  static constexpr int NST = FIT < 8 ? FIT : 8;  // slots
+  static constexpr int BYTES = NST * (S::STAGE + VST);
+};
+constexpr int kVKeys = 2048;  // start vectors of a tile: 8 heads (bf16) or 16 (fp32)
+constexpr int kVOwn = 1024;   // one head: one load instruction
 
 // What a wave computes: its blocks of G and its row blocks of z0.
 template <typename S>
@@ -145,8 +161,9 @@ struct VSlots {
 };
 
 // Streams tiles t0 .. t1 - 1 of one d_h x d row block through the ring and
-// accumulates this wave's blocks of R R^T (GRAM); with Z also its row blocks
-// of z0 and the sums of squares of its slot's columns.  The start vectors'
+// accumulates this wave's blocks of R R^T (GRAM), as acc + low; with start
+// vectors (VST > 0) also its row blocks of z0 and the sums of squares of its
+// slot's columns.  The start vectors'
 // columns ride in the ring beside their tile (chunk c of head i at slot
 // c ^ vswz(i)), as 16-byte loads where their alignment allows, else as 4-byte
 // ones.
@@ -155,12 +172,15 @@ __device__ __forceinline__ int vswz(int i) {
   return S::ES == 2 ? 2 * (i & 7) : i & 7;
 }
 
-template <typename T, int DH, bool Z, bool GRAM>
+template <typename T, int DH, int VST, bool GRAM>
 __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d, int t0, int t1, int seed,
                                              uint8_t* ring, int wv, int lane, const Role<HShape<T, DH>>& role,
                                              const VSlots& vs, f32x4 (&acc)[HShape<T, DH>::NACC],
+                                             f32x4 (&low)[HShape<T, DH>::NACC],
                                              f32x4 (&zacc)[HShape<T, DH>::NZ], float& nrm) {
   using S = HShape<T, DH>;
+  using R = HRing<T, DH, VST>;
+  constexpr bool Z = VST > 0;
   constexpr int ISS = S::NI < kHWaves ? S::NI : kHWaves;  // waves that issue tile loads
   constexpr int OWN = S::NI / ISS;
   const uint32_t nrec = (uint32_t)((((int64_t)(DH - 1) * ld + d) * S::ES + 15) & ~int64_t(15));
@@ -178,7 +198,7 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
     return t0 + (i >= n_whole ? i : u >= n_whole ? u - n_whole : u);
   };
   const int sr = lane >> 3, p = lane & 7;
-  uint8_t* vring = ring + S::NST * S::STAGE;
+  uint8_t* vring = ring + R::NST * S::STAGE;
   const __amdgpu_buffer_rsrc_t vrsrc = make_rsrc(vs.rows, Z ? (uint32_t)vs.heads * (uint32_t)d * 4u : 0u);
   const bool vec = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(vs.rows) & 15) == 0;
   const int rpi = vec ? 64 / S::VCH : 16 / S::VCH > 0 ? 16 / S::VCH : 1;   // start-vector rows per load instruction
@@ -186,7 +206,7 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
   const int vfirst = (wv + 2) & 3;                                         // this wave's: vfirst, vfirst + 4
   const int vown = nvi > vfirst + 4 ? 2 : nvi > vfirst ? 1 : 0;
   auto issue = [&](int i) {
-    const int slot = i % S::NST, t = tile_at(i);
+    const int slot = i % R::NST, t = tile_at(i);
     if (wv < ISS) {
       uint8_t* dst = ring + slot * S::STAGE;
       const uint32_t col = (uint32_t)t * 128u;
@@ -203,7 +223,7 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
         const int ln = vec ? lane : lane >> 2;  // 16-byte slot of this lane within the instruction
         const int row = x * rpi + ln / S::VCH, c = (ln % S::VCH) ^ vswz<S>(row);
         const uint32_t voff = (uint32_t)row * (uint32_t)d * 4u + (uint32_t)t * S::VROW + 16u * (uint32_t)c;
-        uint8_t* dst = vring + slot * S::VST;
+        uint8_t* dst = vring + slot * VST;
         if (vec)
           __builtin_amdgcn_raw_ptr_buffer_load_lds(vrsrc, (lds_void*)(dst + 1024 * x), 16, voff, 0, 0, 0);
         else
@@ -214,7 +234,7 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
   };
 
 #pragma unroll 1
-  for (int i = 0; i < S::NST - 1; ++i)
+  for (int i = 0; i < R::NST - 1; ++i)
     if (i < n) issue(i);
   // Two-level sums: the products of about n / 16 tiles (fp32, four times the
   // instructions per tile: n / 32) are summed from zero and then added to the
@@ -224,35 +244,45 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
   // chain over all columns the error of v was 2.5e-6 (d = 768, fp32, 20
   // iterations) against 2e-7 in the sweeps.
   const int flush = S::ES == 2 ? (n + 15) / 16 : (n + 31) / 32;
-  f32x4 cur[S::NACC], err[S::NACC], zcur[S::NZ];
+  f32x4 cur[S::NACC], err[S::NACC], zcur[S::NZ], zerr[S::NZ];
 #pragma unroll
   for (int x = 0; x < S::NACC; ++x) cur[x] = err[x] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int x = 0; x < S::NZ; ++x) zcur[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int x = 0; x < S::NZ; ++x) zcur[x] = zerr[x] = f32x4{0.f, 0.f, 0.f, 0.f};
   auto add_up = [](f32x4& total, f32x4& part, f32x4& lost) {
     const f32x4 sum = total + part, b = sum - total;
     lost += (total - (sum - b)) + (part - b);
     total = sum;
     part = f32x4{0.f, 0.f, 0.f, 0.f};
   };
+  // fp32 and d_h <= 64: sums of half a tile (error of v at d = 768, 20
+  // iterations, 3.3e-7 -> 2.8e-7)
+  auto half_tile = [&](int kc) {
+    if constexpr (S::LOW && S::ES == 4) {
+      if (kc == 0) {
+#pragma unroll
+        for (int x = 0; x < S::NACC; ++x) add_up(acc[x], cur[x], err[x]);
+      }
+    }
+  };
   int left = flush;
   auto body = [&](int i, auto ragged_tag) {
     constexpr bool RAGGED = decltype(ragged_tag)::value;
     // this wave's part of tile i has landed (the loads of NST - 2 later tiles may be outstanding)
-    if (i + S::NST - 2 < n) {
+    if (i + R::NST - 2 < n) {
       if (Z && vown == 2)
-        wait_vm<(S::NST - 2) * (OWN + 2)>();
+        wait_vm<(R::NST - 2) * (OWN + 2)>();
       else if (Z && vown == 1)
-        wait_vm<(S::NST - 2) * (OWN + 1)>();
+        wait_vm<(R::NST - 2) * (OWN + 1)>();
       else
-        wait_vm<(S::NST - 2) * OWN>();
+        wait_vm<(R::NST - 2) * OWN>();
     } else {
       wait_vm<0>();
     }
     bare_barrier();  // every part of tile i, and tile i - 1 fully read
-    if (i + S::NST - 1 < n) issue(i + S::NST - 1);
+    if (i + R::NST - 1 < n) issue(i + R::NST - 1);
     const int t = tile_at(i);
-    const uint8_t* tile = ring + (i % S::NST) * S::STAGE;
+    const uint8_t* tile = ring + (i % R::NST) * S::STAGE;
     auto chunk = [&](int rb, int kc) {
       u32x4 x = stage_chunk(tile, 16 * rb + s, 4 * kc + q);
       if constexpr (RAGGED) mask_chunk<S::ES>(x, d - (t * S::TC + (4 * kc + q) * S::VEC));
@@ -270,6 +300,7 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
 #pragma unroll
           for (int b = a; b < S::NR; ++b)
             cur[tri_index<S::NR>(a, b)] = gram_mfma<T>(fr[a], fr[b], cur[tri_index<S::NR>(a, b)]);
+        half_tile(kc);
       }
     }
     if (role.rect) {
@@ -288,10 +319,11 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
 #pragma unroll
               for (int b = 0; b < S::NC; ++b)
                 cur[a * S::NC + b] = gram_mfma<T>(fa[a], fb[b], cur[a * S::NC + b]);
-              }
+            half_tile(kc);
+          }
         }
         if constexpr (Z) {
-          const uint8_t* vt = vring + (i % S::NST) * S::VST;
+          const uint8_t* vt = vring + (i % R::NST) * VST;
           const int head = s / vs.np, part = s % vs.np;
           const int cols = d - (t * S::TC + (4 * kc + q) * S::VEC);  // columns left from this chunk on
           u32x4 bv;
@@ -342,9 +374,13 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
       }
       if constexpr (Z) {
 #pragma unroll
-        for (int x = 0; x < S::NZ; ++x) {  // a start: no error of it is repeated
-          zacc[x] += zcur[x];
-          zcur[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int x = 0; x < S::NZ; ++x) {
+          if constexpr (S::LOW) {
+            add_up(zacc[x], zcur[x], zerr[x]);
+          } else {  // no registers for the errors
+            zacc[x] += zcur[x];
+            zcur[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+          }
         }
       }
     }
@@ -353,7 +389,15 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
   for (int i = 0; i < n_whole; ++i) body(i, std::false_type{});
   if (n_whole < n) body(n - 1, std::true_type{});
 #pragma unroll
-  for (int x = 0; x < S::NACC; ++x) acc[x] += err[x];
+  for (int x = 0; x < S::NACC; ++x) {
+    const f32x4 sum = acc[x] + err[x];
+    low[x] = (acc[x] - sum) + err[x];
+    acc[x] = sum;
+  }
+  if constexpr (Z && S::LOW) {
+#pragma unroll
+    for (int x = 0; x < S::NZ; ++x) zacc[x] += zerr[x];
+  }
   __syncthreads();  // the ring is free again
 }
 
@@ -363,41 +407,65 @@ __device__ __forceinline__ int z_row_block(const Role<S>& role, int i) {
   return i < S::NC ? role.row(i) : role.c0 + i - S::NC;
 }
 
-// This wave's blocks of G into the whole symmetric matrix gl (LDS, pitch P).
+// This wave's blocks of G into the whole symmetric matrix gl (LDS, pitch P;
+// the low parts in a second one behind it).
 template <typename T, int DH>
 __device__ __forceinline__ void blocks_to_lds(const Role<HShape<T, DH>>& role,
-                                              const f32x4 (&acc)[HShape<T, DH>::NACC], float* gl, int lane) {
+                                              const f32x4 (&acc)[HShape<T, DH>::NACC],
+                                              const f32x4 (&low)[HShape<T, DH>::NACC], float* gl, int lane) {
   using S = HShape<T, DH>;
   const int q = lane >> 4, s = lane & 15;
-  auto put = [&](int bi, int bj, const f32x4& x, bool mirror) {
+  auto put = [&](int bi, int bj, int i, bool mirror) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int r = 16 * bi + 4 * q + e, c = 16 * bj + s;
-      gl[r * S::P + c] = x[e];
-      if (mirror) gl[c * S::P + r] = x[e];
+      gl[r * S::P + c] = acc[i][e];
+      if (mirror) gl[c * S::P + r] = acc[i][e];
+      if constexpr (S::LOW) {
+        gl[(DH + r) * S::P + c] = low[i][e];
+        if (mirror) gl[(DH + c) * S::P + r] = low[i][e];
+      }
     }
   };
   if (role.tri) {
 #pragma unroll
     for (int a = 0; a < S::NR; ++a)
 #pragma unroll
-      for (int b = a; b < S::NR; ++b) put(role.r0 + a, role.r0 + b, acc[tri_index<S::NR>(a, b)], a != b);
+      for (int b = a; b < S::NR; ++b) put(role.r0 + a, role.r0 + b, tri_index<S::NR>(a, b), a != b);
   } else if (S::RB > 1 && role.rect) {
 #pragma unroll
     for (int a = 0; a < S::NR; ++a)
 #pragma unroll
-      for (int b = 0; b < S::NC; ++b) put(role.row(a), role.c0 + b, acc[a * S::NC + b], true);
+      for (int b = 0; b < S::NC; ++b) put(role.row(a), role.c0 + b, a * S::NC + b, true);
   }
 }
 
-// Thread t = 16 R + C takes rows RPT R .. + RPT - 1 and columns C, C + 16, ..
-// of the matrix in gl; thread t < DH also its diagonal element.  Returns
-// whether the whole diagonal lies in the range where Gram products neither
-// under- nor overflow.
+// How the threads share a Gram matrix in the iteration.  d_h 128: thread t =
+// 16 R + C takes rows 8 R .. + 7 and columns C, C + 16, ..; below, where the
+// elements are doubles and a sum over lanes costs three instructions a step,
+// TPR threads take one row, thread t = TPR R + C columns 2 C + 2 TPR j and
+// their right neighbours (d_h 16: column C).
 template <int DH>
-__device__ __forceinline__ bool lds_to_regs(const float* gl, float* diag, float (&reg)[DH / 16][DH / 16]) {
-  constexpr int P = DH + 1, RPT = DH / 16;
-  const int t = threadIdx.x, R = t >> 4, C = t & 15;
+struct Iter {
+  static constexpr bool LOW = HShape<float, DH>::LOW;
+  using Num = std::conditional_t<LOW, double, float>;
+  static constexpr int TPR = LOW ? kHThreads / DH : 16;  // threads per row
+  static constexpr int ROWS = LOW ? 1 : DH / 16;         // rows and columns per thread
+  static constexpr int COLS = DH / TPR;
+  using Mat = Num[ROWS][COLS];
+  __device__ static __forceinline__ int col(int C, int j) {
+    return LOW && COLS > 1 ? 2 * C + 2 * TPR * (j >> 1) + (j & 1) : C + 16 * j;
+  }
+};
+
+// This thread's part of the matrix in gl; thread t < DH also takes its
+// diagonal element.  Returns whether the whole diagonal lies in the range
+// where Gram products neither under- nor overflow.
+template <int DH>
+__device__ __forceinline__ bool lds_to_regs(const float* gl, float* diag, typename Iter<DH>::Mat& reg) {
+  using I = Iter<DH>;
+  constexpr int P = DH + 1;
+  const int t = threadIdx.x, R = t / I::TPR, C = t % I::TPR;
   bool bad = false;
   if (t < DH) {
     const float x = gl[t * P + t];
@@ -405,25 +473,59 @@ __device__ __forceinline__ bool lds_to_regs(const float* gl, float* diag, float 
     bad = !(x >= kGramMin && x <= kGramMax);
   }
 #pragma unroll
-  for (int i = 0; i < RPT; ++i)
+  for (int i = 0; i < I::ROWS; ++i)
 #pragma unroll
-    for (int j = 0; j < RPT; ++j) reg[i][j] = gl[(RPT * R + i) * P + C + 16 * j];
+    for (int j = 0; j < I::COLS; ++j) {
+      reg[i][j] = gl[(I::ROWS * R + i) * P + I::col(C, j)];
+      if constexpr (I::LOW) reg[i][j] += gl[(DH + R) * P + I::col(C, j)];
+    }
   return __syncthreads_or(bad) == 0;  // gl is read out too
 }
 
-// out[i] = sum_c G[RPT R + i][c] x[c], complete in every lane of the DPP row.
-template <int RPT>
-__device__ __forceinline__ void matvec(const float (&g)[RPT][RPT], const float* x, int C, float (&out)[RPT]) {
-  float xv[RPT];
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double x) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, false);
+  return x + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// out[i] = sum_c G[ROWS R + i][c] x[c], complete in every lane that shares the row.
+template <int DH>
+__device__ __forceinline__ void matvec(const typename Iter<DH>::Mat& g, const typename Iter<DH>::Num* x, int C,
+                                       typename Iter<DH>::Num (&out)[Iter<DH>::ROWS]) {
+  using I = Iter<DH>;
+  typename I::Num xv[I::COLS];
 #pragma unroll
-  for (int j = 0; j < RPT; ++j) xv[j] = x[C + 16 * j];
+  for (int j = 0; j < I::COLS; ++j) xv[j] = x[I::col(C, j)];
+  if constexpr (I::LOW) {
+    double a0 = 0., a1 = 0.;
 #pragma unroll
-  for (int i = 0; i < RPT; ++i) {
-    float a = 0.f;
+    for (int j = 0; j < I::COLS; j += 2) {
+      a0 = fma(g[0][j], xv[j], a0);
+      if constexpr (I::COLS > 1) a1 = fma(g[0][j + 1], xv[j + 1], a1);
+    }
+    double a = a0 + a1;  // the steps of row16_sum, as many as TPR lanes take
+    a = dpp_add<0xB1>(a);
+    a = dpp_add<0x4E>(a);
+    if constexpr (I::TPR > 4) a = dpp_add<0x141>(a);
+    if constexpr (I::TPR > 8) a = dpp_add<0x140>(a);
+    out[0] = a;
+  } else {
 #pragma unroll
-    for (int j = 0; j < RPT; ++j) a = fmaf(g[i][j], xv[j], a);
-    out[i] = row16_sum(a);
+    for (int i = 0; i < I::ROWS; ++i) {
+      float a = 0.f;
+#pragma unroll
+      for (int j = 0; j < I::COLS; ++j) a = fmaf(g[i][j], xv[j], a);
+      out[i] = row16_sum(a);
+    }
   }
+}
+
+// Sum over the wave of a value that only the C == 0 lanes hold.
+template <int DH>
+__device__ __forceinline__ float rows_sum(float x) {
+  return c0_lanes_sum(Iter<DH>::TPR < 16 ? row16_sum(x) : x);
 }
 
 // One pass over a d_h x d row block R by the workgroup: w = R^T x, out = R w
@@ -519,23 +621,28 @@ __device__ __forceinline__ void z0_to_lds(const Role<HShape<T, DH>>& role, const
 }
 
 // This wave's blocks of G to memory, in the block order and lane layout of
-// tri_index and the matrix-core output.
+// tri_index and the matrix-core output, the low parts behind all of them.
 template <typename T, int DH>
 __device__ __forceinline__ void blocks_to_memory(const Role<HShape<T, DH>>& role,
-                                                 const f32x4 (&acc)[HShape<T, DH>::NACC], float* dst, int lane) {
+                                                 const f32x4 (&acc)[HShape<T, DH>::NACC],
+                                                 const f32x4 (&low)[HShape<T, DH>::NACC], float* dst, int lane) {
   using S = HShape<T, DH>;
   f32x4* out = reinterpret_cast<f32x4*>(dst) + lane;
+  auto put = [&](int b, int i) {
+    out[b * 64] = acc[i];
+    if constexpr (S::LOW) out[(S::NB + b) * 64] = low[i];
+  };
   if (role.tri) {
 #pragma unroll
     for (int x = 0; x < S::NR; ++x)
 #pragma unroll
       for (int y = x; y < S::NR; ++y)
-        out[tri_index<S::RB>(role.r0 + x, role.r0 + y) * 64] = acc[tri_index<S::NR>(x, y)];
+        put(tri_index<S::RB>(role.r0 + x, role.r0 + y), tri_index<S::NR>(x, y));
   } else if (S::RB > 1 && role.rect) {
 #pragma unroll
     for (int x = 0; x < S::NR; ++x)
 #pragma unroll
-      for (int y = 0; y < S::NC; ++y) out[tri_index<S::RB>(role.row(x), role.c0 + y) * 64] = acc[x * S::NC + y];
+      for (int y = 0; y < S::NC; ++y) put(tri_index<S::RB>(role.row(x), role.c0 + y), x * S::NC + y);
   }
 }
 
@@ -554,18 +661,26 @@ __device__ __forceinline__ void memory_to_lds(const float* src, int strips, floa
     }
     const int bj = bi + (b - start);
     f32x4 y = in[x], lost = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (S::LOW) lost = in[S::NB * 64 + x];
 #pragma unroll 4
     for (int st = 1; st < strips; ++st) {  // two-sum, as in stream_block
-      const f32x4 p = in[(size_t)st * S::NB * 64 + x], sum = y + p, b = sum - y;
+      const f32x4 p = in[(size_t)st * (S::MAT / 4) + x], sum = y + p, b = sum - y;
       lost += (y - (sum - b)) + (p - b);
+      if constexpr (S::LOW) lost += in[(size_t)st * (S::MAT / 4) + S::NB * 64 + x];
       y = sum;
     }
-    y += lost;
+    const f32x4 sum = y + lost;
+    lost = (y - sum) + lost;
+    y = sum;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int r = 16 * bi + 4 * (ln >> 4) + e, c = 16 * bj + (ln & 15);
       gl[r * S::P + c] = y[e];
       if (bi != bj) gl[c * S::P + r] = y[e];
+      if constexpr (S::LOW) {
+        gl[(DH + r) * S::P + c] = lost[e];
+        if (bi != bj) gl[(DH + c) * S::P + r] = lost[e];
+      }
     }
   }
   __syncthreads();
@@ -575,14 +690,18 @@ __device__ __forceinline__ void memory_to_lds(const float* src, int strips, floa
 // the launch, then (query head, column strip) where the query matrices are
 // split over workgroups too (a.sq > 0).
 template <typename T, int DH>
-__global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(2))) units_kernel(HeadArgs a) {
+__global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(HShape<T, DH>::EU)))
+units_kernel(HeadArgs a) {
   using S = HShape<T, DH>;
-  __shared__ __attribute__((aligned(16))) uint8_t big[S::RING];
+  constexpr int RING = HRing<T, DH, kVKeys>::BYTES > HRing<T, DH, 0>::BYTES ? HRing<T, DH, kVKeys>::BYTES
+                                                                            : HRing<T, DH, 0>::BYTES;
+  static_assert(RING >= 16 * DH * 4, "the z0 slots fit the ring");
+  __shared__ __attribute__((aligned(16))) uint8_t big[RING];
   __shared__ float nv[16];
   const int lane = threadIdx.x & 63, wv = uni((int)(threadIdx.x >> 6));
   const Role<S> role(wv);
   const int n_tiles = (a.d + S::TC - 1) / S::TC;
-  f32x4 acc[S::NACC], zacc[S::NZ];
+  f32x4 acc[S::NACC], low[S::NACC], zacc[S::NZ];
 #pragma unroll
   for (int i = 0; i < S::NACC; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -594,9 +713,9 @@ __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(
     const int h = a.head0 + hl;
     const char* blk = uni(a.mats[h / a.n_q]) + (int64_t)(h % a.n_q) * DH * a.ld * S::ES;
     const int t0 = strip * a.tps_q, t1 = min(t0 + a.tps_q, n_tiles);
-    stream_block<T, DH, false, true>(blk, a.ld, a.d, t0, t1, item, big, wv, lane, role, VSlots{nullptr, 0, 1}, acc,
-                                     zacc, nrm);
-    blocks_to_memory<T, DH>(role, acc, a.gq + (size_t)(hl * a.sq + strip) * S::NB * 256, lane);
+    stream_block<T, DH, 0, true>(blk, a.ld, a.d, t0, t1, item, big, wv, lane, role, VSlots{nullptr, 0, 1}, acc, low,
+                                 zacc, nrm);
+    blocks_to_memory<T, DH>(role, acc, low, a.gq + (size_t)(hl * a.sq + strip) * S::MAT, lane);
     return;
   }
   const int strip = item % a.sk, ch = item / a.sk % a.nch, ul = item / (a.sk * a.nch);
@@ -607,10 +726,10 @@ __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(
   const VSlots vs{a.v + (size_t)(a.head0 + h0) * a.d, nvalid, a.np};
   const int t0 = strip * a.tps_k, t1 = min(t0 + a.tps_k, n_tiles);
   if (ch == 0) {
-    stream_block<T, DH, true, true>(blk, a.ld, a.d, t0, t1, item, big, wv, lane, role, vs, acc, zacc, nrm);
-    blocks_to_memory<T, DH>(role, acc, a.gk + (size_t)(ul * a.sk + strip) * S::NB * 256, lane);
+    stream_block<T, DH, kVKeys, true>(blk, a.ld, a.d, t0, t1, item, big, wv, lane, role, vs, acc, low, zacc, nrm);
+    blocks_to_memory<T, DH>(role, acc, low, a.gk + (size_t)(ul * a.sk + strip) * S::MAT, lane);
   } else {
-    stream_block<T, DH, true, false>(blk, a.ld, a.d, t0, t1, item, big, wv, lane, role, vs, acc, zacc, nrm);
+    stream_block<T, DH, kVKeys, false>(blk, a.ld, a.d, t0, t1, item, big, wv, lane, role, vs, acc, low, zacc, nrm);
   }
   float* zl = reinterpret_cast<float*>(big);
   z0_to_lds<T, DH>(role, zacc, nrm, wv, lane, a.np, zl, nv);
@@ -630,23 +749,28 @@ __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(
 enum { H_OWN = 0, H_KEYS = 1, H_SPLIT = 2 };
 
 template <typename T, int DH, int SRC>
-__global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(2))) heads_kernel(HeadArgs a) {
+__global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(HShape<T, DH>::EU)))
+heads_kernel(HeadArgs a) {
   using S = HShape<T, DH>;
-  constexpr int RPT = S::RPT;
-  __shared__ __attribute__((aligned(16))) uint8_t big[SRC == H_SPLIT ? DH * S::P * 4 : S::BIG];
+  using I = Iter<DH>;
+  constexpr int RPT = I::ROWS;
+  constexpr int RING0 = HRing<T, DH, 0>::BYTES, RINGV = HRing<T, DH, kVOwn>::BYTES;
+  constexpr int RING = SRC == H_SPLIT ? 0 : SRC == H_OWN && RINGV > RING0 ? RINGV : RING0;
+  __shared__ __attribute__((aligned(16))) uint8_t big[RING > S::GL ? RING : S::GL];
   __shared__ float z0[DH], tb[DH], wb[DH], dq[DH], dk[DH];
+  __shared__ __attribute__((aligned(16))) typename I::Num tv[DH], yv[DH];  // the iteration's t and w (last step: y)
   __shared__ float nv[16], red[4][kHWaves];
   float* gl = reinterpret_cast<float*>(big);
   const int t = threadIdx.x, lane = t & 63, wv = uni(t >> 6);
-  const int R = t >> 4, C = t & 15;
+  const int R = t / I::TPR, C = t % I::TPR;
   const int hl = blockIdx.x, h = a.head0 + hl;
   const int layer = h / a.n_q, hq = h % a.n_q, j = hq / a.g;
   const char* qblk = uni(a.mats[layer]) + (int64_t)hq * DH * a.ld * S::ES;
   const char* kblk = uni(a.mats[a.L + layer]) + (int64_t)j * DH * a.ld * S::ES;
   const int n_tiles = (a.d + S::TC - 1) / S::TC;
   const Role<S> role(wv);
-  f32x4 acc[S::NACC], zacc[S::NZ];
-  float gq[RPT][RPT], gk[RPT][RPT];
+  f32x4 acc[S::NACC], low[S::NACC], zacc[S::NZ];
+  typename I::Mat gq, gk;
   float nrm = 0.f, n2v = 0.f, zr = 0.f;  // ||v||^2 and, in thread r < d_h, z0[r] ||v||
   auto clear = [&] {
 #pragma unroll
@@ -657,14 +781,14 @@ __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
     for (int i = 0; i < S::NZ; ++i) zacc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     clear();
-    stream_block<T, DH, true, true>(kblk, a.ld, a.d, 0, n_tiles, hl, big, wv, lane, role,
-                                    VSlots{a.v + (size_t)h * a.d, 1, a.np}, acc, zacc, nrm);
+    stream_block<T, DH, kVOwn, true>(kblk, a.ld, a.d, 0, n_tiles, hl, big, wv, lane, role,
+                                     VSlots{a.v + (size_t)h * a.d, 1, a.np}, acc, low, zacc, nrm);
     z0_to_lds<T, DH>(role, zacc, nrm, wv, lane, a.np, gl, nv);
     n2v = nv[0];
     if (t < DH)
       for (int p = 0; p < a.np; ++p) zr += gl[p * DH + t];
     __syncthreads();
-    blocks_to_lds<T, DH>(role, acc, gl, lane);
+    blocks_to_lds<T, DH>(role, acc, low, gl, lane);
     __syncthreads();
     in_range = lds_to_regs<DH>(gl, dk, gk);
   } else {
@@ -681,27 +805,27 @@ __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(
     }
     return;
   }
-  if (t < DH) tb[t] = z0[t] = zr / vn;
+  if (t < DH) tv[t] = z0[t] = zr / vn;
   if constexpr (SRC != H_SPLIT) {
     clear();
-    stream_block<T, DH, false, true>(qblk, a.ld, a.d, 0, n_tiles, hl, big, wv, lane, role, VSlots{nullptr, 0, 1}, acc,
-                                     zacc, nrm);
-    blocks_to_lds<T, DH>(role, acc, gl, lane);
+    stream_block<T, DH, 0, true>(qblk, a.ld, a.d, 0, n_tiles, hl, big, wv, lane, role, VSlots{nullptr, 0, 1}, acc, low,
+                                 zacc, nrm);
+    blocks_to_lds<T, DH>(role, acc, low, gl, lane);
     __syncthreads();
   } else {
-    memory_to_lds<T, DH>(a.gq + (size_t)hl * a.sq * S::NB * 256, a.sq, gl);
+    memory_to_lds<T, DH>(a.gq + (size_t)hl * a.sq * S::MAT, a.sq, gl);
   }
   in_range = lds_to_regs<DH>(gl, dq, gq) && in_range;
   if constexpr (SRC != H_OWN) {
-    memory_to_lds<T, DH>(a.gk + (size_t)(layer * a.n_kv + j - a.unit0) * a.sk * S::NB * 256, a.sk, gl);
+    memory_to_lds<T, DH>(a.gk + (size_t)(layer * a.n_kv + j - a.unit0) * a.sk * S::MAT, a.sk, gl);
     in_range = lds_to_regs<DH>(gl, dk, gk) && in_range;
   }
 
   float* fin = a.w.fin + (size_t)h * 2 * DH;
-  auto finish = [&](int k, float sig, const float* z, float zs, const float* y, float rn) {
+  auto finish = [&](int k, float sig, const auto* z, float zs, const auto* y, float rn) {
     if (t < DH) {
-      fin[t] = z[t] * zs;
-      fin[DH + t] = a.round_y ? y[t] : y[t] * rn;
+      fin[t] = (float)(z[t] * zs);
+      fin[DH + t] = a.round_y ? (float)y[t] : (float)(y[t] * rn);
     }
     if (t == 0) {
       a.sigma[h] = sig;
@@ -711,11 +835,11 @@ __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(
   };
   // y = w / sigma of the last step, in place; with round_y as the final W_K
   // sweep will take it, so that ||K^T y|| is the norm of what that sweep writes
-  auto last_y = [&](float inv) {
+  auto last_y = [&](auto* w, float inv) {
     if (t < DH) {
-      const float y = wb[t] * inv;
+      const float y = (float)(w[t] * inv);
       const float hi = (float)(__bf16)y;
-      wb[t] = a.round_y ? hi + (float)(__bf16)(y - hi) : y;
+      w[t] = a.round_y ? hi + (float)(__bf16)(y - hi) : y;
     }
     __syncthreads();
   };
@@ -730,62 +854,77 @@ __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(
       dqr[i] = dq[RPT * R + i];
       dkr[i] = dk[RPT * R + i];
     }
-    float zscale = 1.f, prev = 0.f, out[RPT];
+    float zscale = 1.f, prev = 0.f;
+    typename I::Num out[RPT];
+    bool ok = true;
+    // Each product is formed on the unscaled vector before the sums of the
+    // step that made it are looked at: their way through LDS, the square root
+    // and the division run beside it.
 #pragma unroll 1
     for (int k = 1;; ++k) {
-      // w = G_Q z with z = zscale * tb
-      matvec<RPT>(gq, tb, C, out);
+      // w = G_Q z with z = zscale * tv
+      matvec<DH>(gq, tv, C, out);
+      if (k > 1) {
+        const float n2 = sum_waves<kHWaves>(red[2]);
+        ok = n2 >= kCancel * sum_waves<kHWaves>(red[3]) && n2 >= kTiny;
+        zscale = 1.0f / sqrtf(n2);
+      }
+      if (!ok) break;
       float part = 0.f, bound = 0.f;
       if (C == 0) {
 #pragma unroll
         for (int i = 0; i < RPT; ++i) {
-          const float wr = out[i] * zscale, zr = tb[RPT * R + i] * zscale;
-          part = fmaf(zr, wr, part);
+          const typename I::Num wr = out[i] * zscale;
+          const float zr = (float)(tv[RPT * R + i] * zscale);
+          part = fmaf(zr, (float)wr, part);
           bound = fmaf(zr * zr, dqr[i], bound);
-          wb[RPT * R + i] = wr;
+          yv[RPT * R + i] = wr;
         }
       }
-      part = c0_lanes_sum(part);
-      bound = c0_lanes_sum(bound);
+      part = rows_sum<DH>(part);
+      bound = rows_sum<DH>(bound);
       if (lane == 0) {
         red[0][wv] = part;
         red[1][wv] = bound;
       }
       __syncthreads();
+      // t = G_K y with y = w / sigma
+      matvec<DH>(gk, yv, C, out);
       const float s2 = sum_waves<kHWaves>(red[0]);
       if (!(s2 >= kCancel * sum_waves<kHWaves>(red[1])) || !(s2 >= kTiny)) break;
       const float sig = sqrtf(s2), inv_sig = 1.0f / sig;
       const bool last = stop(k, sig, prev);
-      // t = G_K y with y = w / sigma
-      if (last) last_y(inv_sig);
+      if (last) {
+        __syncthreads();
+        last_y(yv, inv_sig);
+        matvec<DH>(gk, yv, C, out);
+      }
       const float inv = last ? 1.f : inv_sig;
-      matvec<RPT>(gk, wb, C, out);
       part = 0.f;
       bound = 0.f;
       if (C == 0) {
 #pragma unroll
         for (int i = 0; i < RPT; ++i) {
-          const float tr = out[i] * inv, yr = wb[RPT * R + i] * inv;
-          part = fmaf(yr, tr, part);
+          const typename I::Num tr = out[i] * inv;
+          const float yr = (float)(yv[RPT * R + i] * inv);
+          part = fmaf(yr, (float)tr, part);
           bound = fmaf(yr * yr, dkr[i], bound);
-          if (!last) tb[RPT * R + i] = tr;
+          if (!last) tv[RPT * R + i] = tr;
         }
       }
-      part = c0_lanes_sum(part);
-      bound = c0_lanes_sum(bound);
+      part = rows_sum<DH>(part);
+      bound = rows_sum<DH>(bound);
       if (lane == 0) {
         red[2][wv] = part;
         red[3][wv] = bound;
       }
       __syncthreads();
-      const float n2 = sum_waves<kHWaves>(red[2]);
-      if (!(n2 >= kCancel * sum_waves<kHWaves>(red[3])) || !(n2 >= kTiny)) break;
-      const float rn = 1.0f / sqrtf(n2);
       if (last) {
-        finish(k, sig, tb, zscale * inv_sig, wb, rn);
+        const float n2 = sum_waves<kHWaves>(red[2]);
+        if (!(n2 >= kCancel * sum_waves<kHWaves>(red[3])) || !(n2 >= kTiny)) break;
+        finish(k, sig, tv, zscale * inv_sig, yv, 1.0f / sqrtf(n2));
         return;
       }
-      zscale = rn;
       prev = sig;
     }
     __syncthreads();
@@ -811,7 +950,7 @@ __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(
     const bool last = stop(k, sig, prev);
     const float inv = 1.0f / sig;
     if (last) {
-      last_y(inv);
+      last_y(wb, inv);
     } else {
       if (t < DH) wb[t] *= inv;
       __syncthreads();

@@ -182,7 +182,10 @@ bool fused_call(const Plan& pl, int dtype, int n_iter) {
 // go through in several pairs, each long enough to hide its launches.
 constexpr size_t kGkBytes = size_t(26) << 20;
 constexpr int kSplitHeads = 256;     // below this many heads their query matrices are split over workgroups
-constexpr int kSplitTarget = 384;    // ... into about this many (with about 256 for the key heads)
+constexpr int kSplitTarget = 384;    // ... into about this many (with kSplitKeys for the key heads)
+constexpr int kSplitKeys = 256;
+constexpr int kSplitTargetLow = 640;  // d_h <= 64: four workgroups per compute unit
+constexpr int kSplitKeysLow = 384;
 constexpr int kKeyTarget = 512;      // workgroups aimed for over the key heads: two per compute unit
 
 // The one-workgroup-per-head form: column strips, and its buffers, which
@@ -196,11 +199,12 @@ void plan_heads(const sn_shape* s, Plan& pl, size_t sweep0, int64_t slack, size_
   const bool split = pl.H < kSplitHeads;
   pl.h_sq = pl.h_sk = 1;
   pl.h_tps_q = pl.h_tps_k = tiles;
-  if (split) strips(tiles, pl.H, 0, kSplitTarget, true, &pl.h_sq, &pl.h_tps_q);
-  if (split || g > 1) strips(tiles, n_units, 0, split ? kSplitTarget - 128 : kKeyTarget, true, &pl.h_sk, &pl.h_tps_k);
+  const int split_q = dh <= 64 ? kSplitTargetLow : kSplitTarget, split_k = dh <= 64 ? kSplitKeysLow : kSplitKeys;
+  if (split) strips(tiles, pl.H, 0, split_q, true, &pl.h_sq, &pl.h_tps_q);
+  if (split || g > 1) strips(tiles, n_units, 0, split ? split_k : kKeyTarget, true, &pl.h_sk, &pl.h_tps_k);
   if (!split) pl.h_sq = 0;
   const size_t fin = (H * 2 * dh * 4 + 255) & ~size_t(255);
-  const size_t mat = (dh / 16) * (dh / 16 + 1) / 2 * 1024;
+  const size_t mat = (dh / 16) * (dh / 16 + 1) / 2 * (dh <= 64 ? 2048 : 1024);  // two floats per element below d_h 128
   const size_t per_unit = split || g > 1 ? (pl.h_sk + g * pl.h_sq) * mat + g * pl.h_sk * (dh + 1) * 4 : 0;
   const size_t room = *off - sweep0;  // >= fin: the sweeps keep three or more d_h-vectors per head
   size_t most = std::max(kGkBytes, room - fin);

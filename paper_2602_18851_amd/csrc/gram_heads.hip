@@ -16,11 +16,11 @@
 //     z / sigma and y of the last step with 1 / ||K^T y||, which the final sweeps
 //     map to u and v, already normalised.
 // Against n_iter pairs of sweeps, whole calls on one box: 70B GQA shape, 30
-// iterations 54.2 -> 2.46 ms; Llama-2-7B shape 10.5 -> 0.66 ms; GPT-2 XL shape
-// with u 2.55 -> 0.26 ms; GPT-2 small, 20 iterations 405 -> 81 us; 5
+// iterations 54.2 -> 2.38 ms; Llama-2-7B shape 10.5 -> 0.65 ms; GPT-2 XL shape
+// with u 2.55 -> 0.25 ms; GPT-2 small, 20 iterations 405 -> 80 us; 5
 // iterations of 144 heads, d 3001, 261 -> 70 us.  Against the strip-wise Gram
 // form (gram.hip: one wave per Gram matrix, all matrices through memory) the
-// 70B call went from 3.28 to 2.46 ms.
+// 70B call went from 3.28 to 2.38 ms.
 //
 // Streaming.  The workgroup's four waves share a ring of row tiles (d_h rows
 // x 128 bytes) in LDS, filled by buffer loads straight to LDS; one bare
@@ -859,7 +859,10 @@ heads_kernel(HeadArgs a) {
     bool ok = true;
     // Each product is formed on the unscaled vector before the sums of the
     // step that made it are looked at: their way through LDS, the square root
-    // and the division run beside it.
+    // and the division run beside it.  In steps that cannot be the last only
+    // the scale of the vectors depends on those two, and an instruction's 1 ulp
+    // is enough.
+    auto may_end = [&](int k) { return a.tol > 0.f || k >= a.n_iter; };
 #pragma unroll 1
     for (int k = 1;; ++k) {
       // w = G_Q z with z = zscale * tv
@@ -867,7 +870,7 @@ heads_kernel(HeadArgs a) {
       if (k > 1) {
         const float n2 = sum_waves<kHWaves>(red[2]);
         ok = n2 >= kCancel * sum_waves<kHWaves>(red[3]) && n2 >= kTiny;
-        zscale = 1.0f / sqrtf(n2);
+        zscale = may_end(k) ? 1.0f / sqrtf(n2) : __builtin_amdgcn_rsqf(n2);
       }
       if (!ok) break;
       float part = 0.f, bound = 0.f;
@@ -892,8 +895,15 @@ heads_kernel(HeadArgs a) {
       matvec<DH>(gk, yv, C, out);
       const float s2 = sum_waves<kHWaves>(red[0]);
       if (!(s2 >= kCancel * sum_waves<kHWaves>(red[1])) || !(s2 >= kTiny)) break;
-      const float sig = sqrtf(s2), inv_sig = 1.0f / sig;
-      const bool last = stop(k, sig, prev);
+      float sig = 0.f, inv_sig;
+      bool last = false;
+      if (may_end(k)) {
+        sig = sqrtf(s2);
+        inv_sig = 1.0f / sig;
+        last = stop(k, sig, prev);
+      } else {
+        inv_sig = __builtin_amdgcn_rsqf(s2);
+      }
       if (last) {
         __syncthreads();
         last_y(yv, inv_sig);
@@ -1036,11 +1046,8 @@ void launch_t(int dh, const HeadArgs& a, bool units, hipStream_t st) {
 }  // namespace
 
 void launch_heads(bool bf16, int head_dim, bool units, hipStream_t st, HeadArgs a) {
-  // slots of a z0 operand: three bf16 parts per head (24 bits, 5 heads); two
-  // (16 bits, 8 heads) only where they save an operand and the grouped sweeps
-  // keep no more either (d_h 64 and 128); fp32 weights take v as it is
-  a.np = !bf16 ? 1 : a.g > 5 && head_dim >= 64 ? 2 : 3;
-  a.hps = 16 / a.np;
+  a.hps = heads_per_operand(bf16, head_dim, a.g);
+  a.np = !bf16 ? 1 : a.hps == 8 ? 2 : 3;
   a.nch = (a.g + a.hps - 1) / a.hps;
   if (bf16)
     launch_t<uint16_t>(head_dim, a, units, st);

@@ -262,6 +262,12 @@ void launch_tail_lists(const SweepArgs& a, int slot, int gc, int n_units, const 
 void launch_gram(bool bf16, int head_dim, int n_items, hipStream_t st, const GramArgs& g);
 void launch_gram_iterate(int head_dim, int heads, hipStream_t st, const IterArgs& a);
 // units: the units_kernel of the pair (none where a head's workgroup reads both its matrices), else heads_kernel
+// Query heads per z0 operand of 16 slots.  bf16 weights: three bf16 parts of v
+// per head (24 bits, 5 heads); two (16 bits, 8 heads) only where they save an
+// operand and the grouped sweeps keep no more either (d_h 64 and 128); fp32
+// weights take v as it is.
+inline int heads_per_operand(bool bf16, int head_dim, int g) { return !bf16 ? 16 : g > 5 && head_dim >= 64 ? 8 : 5; }
+
 void launch_heads(bool bf16, int head_dim, bool units, hipStream_t st, HeadArgs a);
 void launch_heads_finalize(int layers, hipStream_t st, const FinArgs& f);
 void launch_layer_sweep(bool bf16, int head_dim, int mode, int n_items, hipStream_t st, const LayerArgs& a);

@@ -178,15 +178,33 @@ bool fused_call(const Plan& pl, int dtype, int n_iter) {
 }
 
 // Bytes of Gram matrices one launch pair of the one-workgroup-per-head form
-// works on: all 640 key heads of the 70B GQA shape (23.6 MB); larger shapes
+// works on: all 640 key heads of the 70B GQA shape (53 MB in two strips); larger shapes
 // go through in several pairs, each long enough to hide its launches.
-constexpr size_t kGkBytes = size_t(26) << 20;
+constexpr size_t kGkBytes = size_t(56) << 20;
 constexpr int kSplitHeads = 256;     // below this many heads their query matrices are split over workgroups
 constexpr int kSplitTarget = 384;    // ... into about this many (with kSplitKeys for the key heads)
 constexpr int kSplitKeys = 256;
 constexpr int kSplitTargetLow = 640;  // d_h <= 64: four workgroups per compute unit
 constexpr int kSplitKeysLow = 384;
-constexpr int kKeyTarget = 512;      // workgroups aimed for over the key heads: two per compute unit
+
+// Column strips of the key heads where every query head has a workgroup of its
+// own: the fewest rounds of workgroups over the chip (`slots` at a time),
+// against the strips' Gram matrices, which every query head reads: in units of
+// streaming one head, rounds(s) / s + (query rounds) s (matrix / head bytes).
+// 70B GQA shape, 640 key heads on 512 slots: one strip takes two rounds, two
+// strips one and a half (units_kernel 474 -> 419 us, the call 2.46 -> 2.38 ms).
+int key_strips(int64_t units, int64_t heads, int slots, double mat_ratio, int tiles) {
+  int best = 1;
+  double cost = 1e30;
+  for (int s = 1; s <= std::min(32, std::max(1, tiles / kMinTilesPerStrip)); ++s) {
+    const double c = (double)ceil_div(units * s, slots) / s + (double)ceil_div(heads, slots) * s * mat_ratio;
+    if (c < cost) {
+      cost = c;
+      best = s;
+    }
+  }
+  return best;
+}
 
 // The one-workgroup-per-head form: column strips, and its buffers, which
 // share the bytes of the sweeps' partials, sweep0 .. *off (a call uses one or
@@ -201,16 +219,24 @@ void plan_heads(const sn_shape* s, Plan& pl, size_t sweep0, int64_t slack, size_
   pl.h_tps_q = pl.h_tps_k = tiles;
   const int split_q = dh <= 64 ? kSplitTargetLow : kSplitTarget, split_k = dh <= 64 ? kSplitKeysLow : kSplitKeys;
   if (split) strips(tiles, pl.H, 0, split_q, true, &pl.h_sq, &pl.h_tps_q);
-  if (split || g > 1) strips(tiles, n_units, 0, split ? split_k : kKeyTarget, true, &pl.h_sk, &pl.h_tps_k);
+  const size_t mat = (dh / 16) * (dh / 16 + 1) / 2 * (dh <= 64 ? 2048 : 1024);  // two floats per element below d_h 128
+  if (split) {
+    strips(tiles, n_units, 0, split_k, true, &pl.h_sk, &pl.h_tps_k);
+  } else if (g > 1) {
+    const int64_t chunks = ceil_div(g, heads_per_operand(s->dtype == SN_BF16, (int)dh, (int)g));
+    const double ratio = (double)mat / ((double)dh * s->d_model * esize(s->dtype));
+    const int want = key_strips(n_units * chunks, pl.H, dh <= 64 ? 1024 : 512, ratio, tiles);
+    strips(tiles, n_units, want, 0, true, &pl.h_sk, &pl.h_tps_k);
+  }
   if (!split) pl.h_sq = 0;
   const size_t fin = (H * 2 * dh * 4 + 255) & ~size_t(255);
-  const size_t mat = (dh / 16) * (dh / 16 + 1) / 2 * (dh <= 64 ? 2048 : 1024);  // two floats per element below d_h 128
   const size_t per_unit = split || g > 1 ? (pl.h_sk + g * pl.h_sq) * mat + g * pl.h_sk * (dh + 1) * 4 : 0;
   const size_t room = *off - sweep0;  // >= fin: the sweeps keep three or more d_h-vectors per head
   size_t most = std::max(kGkBytes, room - fin);
   if (slack >= 0) most = std::min(most, room - fin + (size_t)slack);
   pl.h_units = per_unit ? (int)std::min(n_units, (most - std::min<size_t>(most, 1024)) / per_unit) : (int)n_units;
   pl.heads = pl.h_units > 0;
+  if (pl.heads) pl.h_units = ceil_div(n_units, ceil_div(n_units, pl.h_units));  // pairs of equal length
   size_t o = sweep0;
   auto take = [&](size_t bytes) {
     const size_t r = o;

@@ -15,6 +15,7 @@ struct ProjArgs {
   int64_t ld_w;
   int32_t layers, seq, d, nq_cols, nk_cols;  // nq_cols = n_q d_h, nk_cols = n_kv d_h
   int32_t tiles_m, tiles_n;                  // per layer (set by sn_launch_proj)
+  int32_t tiles_nq, tiles_nk;                // ... where Q and K features have tiles of their own
   uint16_t* qh;  // [L][seq][nq_cols] bf16 planes: Q = hi + lo
   uint16_t* ql;
   uint16_t* kh;  // [L][seq][nk_cols]

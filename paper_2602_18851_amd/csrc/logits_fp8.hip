@@ -43,6 +43,8 @@ __device__ __forceinline__ void mask_bf16(u32x4& q, int nval) {
     q[e] &= (2 * e < nval ? 0x0000ffffu : 0u) | (2 * e + 1 < nval ? 0xffff0000u : 0u);
 }
 
+__device__ __forceinline__ uint16_t bf16_bits(float x) { return __builtin_bit_cast(uint16_t, (__bf16)x); }
+
 // The bf16 values of a and b (rounded to nearest even) in one word, by one conversion.
 __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -76,9 +78,7 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
 // one barrier per step that waits for all loads: 70B GQA shape, 1024 tokens,
 // 10.2 -> 9.7 ms, the matrix cores busy 73% of the cycles instead of 64%.  The
 // clock falls by 7% meanwhile (1.70 -> 1.58 GHz): the kernel is bound by power,
-// at 1.28 PFLOP/s.  GPT-2 XL shape, 999 tokens (25 steps): the whole call
-// 1.15 -> 1.12 ms, with one sequence of Q and K features (13 tiles a layer in
-// place of 14) and whole lines written.  Workgroups that walk over tiles, the
+// at 1.28 PFLOP/s.  Workgroups that walk over tiles, the
 // next tile's loads in flight across the epilogue, lose the tiles' common
 // start on an XCD: 10.9 ms.  Nothing is read or refilled too early:
 //   - data of phase P were requested in phase P - 7; every wave waits at the
@@ -92,6 +92,7 @@ constexpr int kPT = 256;                      // projection workgroup tile
 constexpr int kPWaves = 8;
 constexpr int kPHalf = 128 * 128;             // bytes of a half tile
 constexpr int kPStageBytes = 4 * kPHalf;      // A0, A1, B0, B1 of one 64-column step
+constexpr int kPLongRow = 3072;               // columns from which on this kernel runs
 constexpr int kPInFlight = 12;                // loads of a wave outstanding across a barrier
 
 __device__ __forceinline__ void proj_fence() { asm volatile("" ::: "memory"); }
@@ -295,6 +296,95 @@ __global__ void __launch_bounds__(64 * kPWaves) __attribute__((amdgpu_waves_per_
       *reinterpret_cast<uint2*>(lo[j] + off) = make_uint2(l2[0], l2[1]);
     }
   }
+}
+
+// The projection for rows of few steps (see sn_launch_proj): the same tiles
+// and waves, Q and K features in tiles of their own, two stages of a whole step
+// and one barrier per step.  A tile has less to fill and drain around its
+// steps, which the four phases do not win back in a short row.
+__global__ void __launch_bounds__(64 * kPWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) proj_short_kernel(ProjArgs a) {
+  __shared__ __attribute__((aligned(16))) uint8_t stage[2][kPStageBytes];
+  const int lane = threadIdx.x & 63;
+  const int wv = uni((int)(threadIdx.x >> 6));
+  const int q = lane >> 4, s = lane & 15;
+  const int per_xcd = gridDim.x / 8;
+  const int tq = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  const int tiles_q = a.tiles_m * a.tiles_nq, per_layer = tiles_q + a.tiles_m * a.tiles_nk;
+  if (tq >= a.layers * per_layer) return;  // whole workgroup
+  const int layer = tq / per_layer, t = tq % per_layer;
+  const bool isq = t < tiles_q;
+  const int tt = isq ? t : t - tiles_q;
+  const int bm = tt % a.tiles_m, bn = tt / a.tiles_m;
+  const int ncols = isq ? a.nq_cols : a.nk_cols;
+
+  // this wave stages rows 32 wv .. 32 wv + 31 of the A (token) and B (weight) tiles
+  const int am = bm * kPT + 32 * wv, bnr = bn * kPT + 32 * wv;
+  const char* abase = uni(a.x[layer]) + (int64_t)am * a.ld_x * 2;
+  const char* bbase = uni(isq ? a.wq[layer] : a.wk[layer]) + (int64_t)bnr * a.ld_w * 2;
+  const int64_t a_len = am < a.seq ? (((int64_t)(a.seq - 1 - am) * a.ld_x + a.d) * 2 + 15) & ~int64_t(15) : 0;
+  const int64_t b_len = bnr < ncols ? (((int64_t)(ncols - 1 - bnr) * a.ld_w + a.d) * 2 + 15) & ~int64_t(15) : 0;
+  const __amdgpu_buffer_rsrc_t ra = make_rsrc(abase, (uint32_t)a_len);
+  const __amdgpu_buffer_rsrc_t rb_ = make_rsrc(bbase, (uint32_t)b_len);
+  const uint32_t a_rb = (uint32_t)(a.ld_x * 2), b_rb = (uint32_t)(a.ld_w * 2);
+  auto issue = [&](int k, int st) {
+    stage_issue<32, 0>(ra, stage[st] + 4096 * wv, (uint32_t)(k * 128), a_rb, lane);
+    stage_issue<32, 0>(rb_, stage[st] + kPT * 128 + 4096 * wv, (uint32_t)(k * 128), b_rb, lane);
+  };
+
+  const int wm = wv >> 2, wn = wv & 3;  // 2 x 4 waves of 128 x 64
+  f32x4 acc[8][4];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int n_k = (a.d + 63) / 64, n_full = a.d / 64;
+  issue(0, 0);
+#pragma unroll 1
+  for (int k = 0; k < n_k; ++k) {
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's part of step k is in LDS
+    __syncthreads();                // every part, and step k - 1 fully read
+    if (k + 1 < n_k) issue(k + 1, (k + 1) & 1);
+    const uint8_t* sa = stage[k & 1];
+    const uint8_t* sb = sa + kPT * 128;
+#pragma unroll
+    for (int kc = 0; kc < 2; ++kc) {
+      u32x4 fa[8], fb[4];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) fa[r] = stage_chunk(sa, 128 * wm + 16 * r + s, 4 * kc + q);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) fb[r] = stage_chunk(sb, 64 * wn + 16 * r + s, 4 * kc + q);
+      if (k >= n_full) {  // the ragged last step: zero columns >= d
+        const int nval = a.d - (k * 64 + 32 * kc + 8 * q);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) mask_bf16(fa[r], nval);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mask_bf16(fb[r], nval);
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = mfma(fa[i], fb[j], acc[i][j]);
+    }
+  }
+
+  const int m0 = bm * kPT + 128 * wm, n0 = bn * kPT + 64 * wn;
+  const size_t plane = (size_t)layer * a.seq * ncols;
+  uint16_t* hi = (isq ? a.qh : a.kh) + plane;
+  uint16_t* lo = (isq ? a.ql : a.kl) + plane;
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int m = m0 + 16 * i + 4 * q + e, n = n0 + 16 * j + s;
+        if (m < a.seq && n < ncols) {
+          const float x = acc[i][j][e];
+          const __bf16 h = (__bf16)x;
+          hi[(size_t)m * ncols + n] = __builtin_bit_cast(uint16_t, h);
+          lo[(size_t)m * ncols + n] = bf16_bits(x - (float)h);
+        }
+      }
 }
 
 // Logits of all layers in one launch.  A workgroup owns 128 queries of one
@@ -592,9 +682,20 @@ void sn_launch_zero_stats(float* max_abs, int32_t* n_over, int n, hipStream_t st
 void sn_launch_proj(const ProjArgs& args, hipStream_t st) {
   ProjArgs a = args;
   a.tiles_m = (a.seq + kPT - 1) / kPT;
-  a.tiles_n = (a.nq_cols + a.nk_cols + kPT - 1) / kPT;
-  const int tiles = a.layers * a.tiles_m * a.tiles_n;
-  proj_kernel<<<dim3(((tiles + 7) / 8) * 8), 64 * kPWaves, 0, st>>>(a);
+  // Calls with the four-phase kernel against one barrier per step: d 8192 (80
+  // layers) 13.4 vs 14.1 ms, (2 layers) 475 vs 502 us, d 4096 1.22 vs 1.25 ms; d
+  // 2048 214 vs 206 us, d 800 544 vs 507 us, d 256 66 vs 58 us.  The line lies
+  // between 2048 and 4096.
+  if (a.d >= kPLongRow) {
+    a.tiles_n = (a.nq_cols + a.nk_cols + kPT - 1) / kPT;
+    const int tiles = a.layers * a.tiles_m * a.tiles_n;
+    proj_kernel<<<dim3(((tiles + 7) / 8) * 8), 64 * kPWaves, 0, st>>>(a);
+  } else {
+    a.tiles_nq = (a.nq_cols + kPT - 1) / kPT;
+    a.tiles_nk = (a.nk_cols + kPT - 1) / kPT;
+    const int tiles = a.layers * a.tiles_m * (a.tiles_nq + a.tiles_nk);
+    proj_short_kernel<<<dim3(((tiles + 7) / 8) * 8), 64 * kPWaves, 0, st>>>(a);
+  }
 }
 
 void sn_launch_logits(const LogitArgs& a, int head_dim, hipStream_t st) {

@@ -1,6 +1,7 @@
 """The projection of the FP8 consumer at the edges of its tiles (256 tokens x
 256 features, steps of 64 columns, two ahead) and where the Q features end
-inside a tile: codes and statistics against the float64 oracle, within the
+inside a tile, below and above the width from which on the pipelined kernel
+runs (3072): codes and statistics against the float64 oracle, within the
 bands that test_gpu_fp8 derives.  Columns past d hold NaN."""
 
 import numpy as np
@@ -26,6 +27,12 @@ CASES = [
     ("two-steps", 128, 8, 128, 12, 3, 32),             # Q ends inside the second tile
     ("three-steps-ragged", 200, 0, 300, 5, 5, 64),     # Q ends at 320: inside a wave's part
     ("four-steps-ragged", 250, 14, 255, 3, 1, 128),    # Q ends at 384, K at 512
+    ("last-short", 3071, 1, 130, 2, 1, 64),
+    ("long-one-tile", 3072, 0, 256, 6, 2, 32),
+    ("long-ragged-step", 3073, 7, 257, 3, 1, 16),
+    ("long-odd-steps", 3136, 8, 1, 12, 3, 32),         # 49 steps, one token
+    ("long-ragged-even-steps", 3160, 0, 300, 5, 5, 64),
+    ("long-three-tiles", 3200, 8, 255, 3, 1, 128),
 ]
 
 

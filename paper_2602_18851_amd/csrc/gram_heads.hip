@@ -65,10 +65,9 @@ struct HShape {
   static constexpr int VEC = 16 / ES;
   static constexpr int TC = 128 / ES;               // columns per tile
   static constexpr int RB = DH / 16, NB = RB * (RB + 1) / 2;
-  static constexpr int STAGE = DH * 128;            // bytes of one tile
+  static constexpr int STAGE = tile_bytes(DH);
   static constexpr int VROW = TC * 4;               // bytes of one start vector's columns of a tile
   static constexpr int VCH = VROW / 16;             // ... in 16-byte chunks
-  static constexpr int NI = DH / 8;                 // 1 KB load instructions per tile
   static constexpr int NR = RB > 1 ? RB / 2 : 1;    // row blocks of a diagonal triangle
   static constexpr int NC = RB >= 4 ? RB / 4 : 1;   // column blocks of an off-diagonal half
   static constexpr int NTRI = NR * (NR + 1) / 2;
@@ -85,15 +84,11 @@ struct HShape {
   static constexpr int EU = DH == 128 ? 2 : 4;                 // workgroups per compute unit (waves per SIMD)
 };
 
-// The ring of a stream with VST bytes of start vectors beside each tile.  Two
-// workgroups per compute unit with d_h 128, whose registers allow no more; four
-// of at most 38 KB below: a workgroup that iterates streams nothing, and the
-// others have to fill the memory pipe meanwhile.
+// The ring of a stream with VST bytes of start vectors beside each tile.
 template <typename T, int DH, int VST>
 struct HRing {
   using S = HShape<T, DH>;
-  static constexpr int FIT = (DH == 128 ? 73728 : 38912) / (S::STAGE + VST);
-  static constexpr int NST = FIT < 8 ? FIT : 8;  // slots
+  static constexpr int NST = ring_slots(DH, VST);  // slots
   static constexpr int BYTES = NST * (S::STAGE + VST);
 };
 constexpr int kVKeys = 2048;  // start vectors of a tile: 8 heads (bf16) or 16 (fp32)
@@ -122,9 +117,19 @@ __device__ __forceinline__ void bare_barrier() {
   lds_fence();
 }
 
+// At most N vector-memory operations outstanding and every LDS read complete.
 template <int N>
-__device__ __forceinline__ void wait_vm() {  // at most N vector-memory operations outstanding
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+__device__ __forceinline__ void wait_vm() {
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((N >> 4) << 14));
+}
+
+// wait_vm for a wave that requests `own` <= MAX loads per tile (wave-uniform).
+template <int NST, int MAX>
+__device__ __forceinline__ void wait_ahead(int own) {
+  if constexpr (MAX > 0) {
+    if (own < MAX) return wait_ahead<NST, MAX - 1>(own);
+  }
+  wait_vm<outstanding_ahead(NST, MAX)>();
 }
 
 template <typename T>
@@ -181,8 +186,7 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
   using S = HShape<T, DH>;
   using R = HRing<T, DH, VST>;
   constexpr bool Z = VST > 0;
-  constexpr int ISS = S::NI < kHWaves ? S::NI : kHWaves;  // waves that issue tile loads
-  constexpr int OWN = S::NI / ISS;
+  constexpr int OWN = tile_loads(DH, 0);
   const uint32_t nrec = (uint32_t)((((int64_t)(DH - 1) * ld + d) * S::ES + 15) & ~int64_t(15));
   const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(blk, nrec);
   const uint32_t row_bytes = (uint32_t)(ld * S::ES);
@@ -201,13 +205,11 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
   uint8_t* vring = ring + R::NST * S::STAGE;
   const __amdgpu_buffer_rsrc_t vrsrc = make_rsrc(vs.rows, Z ? (uint32_t)vs.heads * (uint32_t)d * 4u : 0u);
   const bool vec = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(vs.rows) & 15) == 0;
-  const int rpi = vec ? 64 / S::VCH : 16 / S::VCH > 0 ? 16 / S::VCH : 1;   // start-vector rows per load instruction
-  const int nvi = Z ? (vs.heads + rpi - 1) / rpi : 0;                      // load instructions of a tile's rows
-  const int vfirst = (wv + 2) & 3;                                         // this wave's: vfirst, vfirst + 4
-  const int vown = nvi > vfirst + 4 ? 2 : nvi > vfirst ? 1 : 0;
+  const int rpi = vector_rows_per_load(S::ES, vec), nvi = Z ? vector_instructions(S::ES, vec, vs.heads) : 0;
+  const int t_own = tile_loads(DH, wv), own = t_own + (Z ? vector_loads(nvi, wv) : 0);
   auto issue = [&](int i) {
     const int slot = i % R::NST, t = tile_at(i);
-    if (wv < ISS) {
+    if (t_own > 0) {
       uint8_t* dst = ring + slot * S::STAGE;
       const uint32_t col = (uint32_t)t * 128u;
 #pragma unroll
@@ -219,7 +221,7 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
       }
     }
     if constexpr (Z) {
-      for (int x = vfirst; x < nvi; x += 4) {
+      for (int x = vector_first(wv); x < nvi; x += kHWaves) {
         const int ln = vec ? lane : lane >> 2;  // 16-byte slot of this lane within the instruction
         const int row = x * rpi + ln / S::VCH, c = (ln % S::VCH) ^ vswz<S>(row);
         const uint32_t voff = (uint32_t)row * (uint32_t)d * 4u + (uint32_t)t * S::VROW + 16u * (uint32_t)c;
@@ -269,16 +271,10 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
   auto body = [&](int i, auto ragged_tag) {
     constexpr bool RAGGED = decltype(ragged_tag)::value;
     // this wave's part of tile i has landed (the loads of NST - 2 later tiles may be outstanding)
-    if (i + R::NST - 2 < n) {
-      if (Z && vown == 2)
-        wait_vm<(R::NST - 2) * (OWN + 2)>();
-      else if (Z && vown == 1)
-        wait_vm<(R::NST - 2) * (OWN + 1)>();
-      else
-        wait_vm<(R::NST - 2) * OWN>();
-    } else {
+    if (i + R::NST - 2 < n)
+      wait_ahead<R::NST, OWN + (Z ? 2 : 0)>(own);
+    else
       wait_vm<0>();
-    }
     bare_barrier();  // every part of tile i, and tile i - 1 fully read
     if (i + R::NST - 1 < n) issue(i + R::NST - 1);
     const int t = tile_at(i);

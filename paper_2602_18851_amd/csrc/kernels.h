@@ -8,6 +8,8 @@
 
 #include <cstdint>
 
+#include "stream_loads.h"
+
 namespace sn {
 
 constexpr int kWaves = 4;             // waves per workgroup
@@ -28,7 +30,6 @@ constexpr int kMWaves = 2;                 // waves per workgroup
 constexpr int kMTileC = 64;                // columns per tile: 128-byte row segments
 constexpr int kGWaves = 4;                 // waves per workgroup of the Gram sweep
 constexpr int kGTargetItems = 4096;        // Gram work items aimed for (about two waves per SIMD)
-constexpr int kHWaves = 4;                 // waves per workgroup of the one-workgroup-per-head Gram form
 constexpr int kLFWaves = 16;               // most waves of a one-pass layer sweep (one workgroup per CU then)
 constexpr int kLFRowsPerWave = 64;         // rows each wave holds of a column tile
 constexpr int kLFRows = kLFWaves * kLFRowsPerWave;

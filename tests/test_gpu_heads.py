@@ -40,6 +40,12 @@ CASES = [
     ("keys-dh64", 4, 200, 0, 32, 2, 64, "bf16"),              # 256 heads: Q by one workgroup, K by another
     ("keys-dh32-f32", 2, 257, 3, 9, 16, 32, "f32"),
     ("keys-dh128-chunks", 4, 64, 0, 200, 2, 128, "bf16"),     # more key heads than one launch pair takes
+    # d_h 16, where two of the four waves request no rows, and ten or more tiles per strip
+    ("dh16-own-10-tiles", 2, 640, 0, 128, 1, 16, "bf16"),
+    ("dh16-own-11-tiles-f32", 2, 331, 1, 128, 1, 16, "f32"),      # unaligned rows of v
+    ("dh16-5-heads-10-tiles", 1, 4480, 0, 50, 5, 16, "bf16"),     # 7 strips; wave 3 requests start vectors too
+    ("dh16-5-heads-11-tiles", 1, 4483, 5, 50, 5, 16, "bf16"),     # unaligned rows of v
+    ("dh16-12-heads-10-tiles-f32", 1, 6080, 0, 20, 12, 16, "f32"),
 ]
 
 

@@ -184,9 +184,11 @@ SN_API int spectral_step(sn_ctx* ctx, const void* const* wq_layers, const void* 
  * arguments as for spectral_step, whose results it gives bit for bit.  Its
  * workspace and layer-pointer table live in a static device array of
  * 32 MiB that each device holds from the first call on it until the process
- * ends; a shape whose workspace (spectral_workspace_bytes) plus 4 n_layers
- * pointers, rounded up to 256 bytes, does not fit is rejected with
- * SN_EINVAL before anything is queued.  The call allocates nothing (no
+ * ends; a shape whose workspace without the Gram form's matrices, plus 4
+ * n_layers pointers rounded up to 256 bytes, does not fit is rejected with
+ * SN_EINVAL before anything is queued.  The Gram form takes what is left, in
+ * launches over as many key heads as fit; a shape of which not even one key
+ * head fits runs the sweeps, here and with a context.  The call allocates nothing (no
  * hipMalloc, hipFree, event or allocating library routine).  Every call on
  * a device shares that device's array, which keeps the last call's
  * contents: calls that overlap on one device (queued on different streams,

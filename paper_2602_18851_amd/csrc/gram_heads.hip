@@ -178,7 +178,7 @@ __device__ __forceinline__ int vswz(int i) {
 }
 
 template <typename T, int DH, int VST, bool GRAM>
-__device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d, int t0, int t1, int seed,
+__device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d, int t0, int t1, uint32_t seed,
                                              uint8_t* ring, int wv, int lane, const Role<HShape<T, DH>>& role,
                                              const VSlots& vs, f32x4 (&acc)[HShape<T, DH>::NACC],
                                              f32x4 (&low)[HShape<T, DH>::NACC],
@@ -196,7 +196,7 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
   // whole tiles from a staggered start, as in the sweeps; the ragged last tile
   // of the block (columns past d) comes last, in a copy of the loop body
   const int n_whole = min(t1, d / S::TC) - t0;
-  const int rot = n_whole > 0 ? (int)((((uint32_t)seed * 2654435761u) >> 16) % (uint32_t)n_whole) : 0;
+  const int rot = n_whole > 0 ? (int)(((seed * 2654435761u) >> 16) % (uint32_t)n_whole) : 0;
   auto tile_at = [&](int i) {
     const int u = rot + i;
     return t0 + (i >= n_whole ? i : u >= n_whole ? u - n_whole : u);
@@ -682,6 +682,13 @@ __device__ __forceinline__ void memory_to_lds(const float* src, int strips, floa
   __syncthreads();
 }
 
+// Where a head's (or key head and chunk's) strip starts in its tiles: by its
+// place in the model, not in the launch, so that the order of its sums does not
+// depend on how many key heads a launch pair covers.
+__device__ __forceinline__ uint32_t tile_seed(int head, int strips, int strip) {
+  return (uint32_t)head * (uint32_t)strips + (uint32_t)strip;
+}
+
 // Items: (key head, chunk of query heads, column strip) for the key heads of
 // the launch, then (query head, column strip) where the query matrices are
 // split over workgroups too (a.sq > 0).
@@ -709,7 +716,7 @@ units_kernel(HeadArgs a) {
     const int h = a.head0 + hl;
     const char* blk = uni(a.mats[h / a.n_q]) + (int64_t)(h % a.n_q) * DH * a.ld * S::ES;
     const int t0 = strip * a.tps_q, t1 = min(t0 + a.tps_q, n_tiles);
-    stream_block<T, DH, 0, true>(blk, a.ld, a.d, t0, t1, item, big, wv, lane, role, VSlots{nullptr, 0, 1}, acc, low,
+    stream_block<T, DH, 0, true>(blk, a.ld, a.d, t0, t1, tile_seed(h, a.sq, strip), big, wv, lane, role, VSlots{nullptr, 0, 1}, acc, low,
                                  zacc, nrm);
     blocks_to_memory<T, DH>(role, acc, low, a.gq + (size_t)(hl * a.sq + strip) * S::MAT, lane);
     return;
@@ -721,11 +728,12 @@ units_kernel(HeadArgs a) {
   const char* blk = uni(a.mats[a.L + layer]) + (int64_t)j * DH * a.ld * S::ES;
   const VSlots vs{a.v + (size_t)(a.head0 + h0) * a.d, nvalid, a.np};
   const int t0 = strip * a.tps_k, t1 = min(t0 + a.tps_k, n_tiles);
+  const uint32_t seed = tile_seed(unit * a.nch + ch, a.sk, strip);
   if (ch == 0) {
-    stream_block<T, DH, kVKeys, true>(blk, a.ld, a.d, t0, t1, item, big, wv, lane, role, vs, acc, low, zacc, nrm);
+    stream_block<T, DH, kVKeys, true>(blk, a.ld, a.d, t0, t1, seed, big, wv, lane, role, vs, acc, low, zacc, nrm);
     blocks_to_memory<T, DH>(role, acc, low, a.gk + (size_t)(ul * a.sk + strip) * S::MAT, lane);
   } else {
-    stream_block<T, DH, kVKeys, false>(blk, a.ld, a.d, t0, t1, item, big, wv, lane, role, vs, acc, low, zacc, nrm);
+    stream_block<T, DH, kVKeys, false>(blk, a.ld, a.d, t0, t1, seed, big, wv, lane, role, vs, acc, low, zacc, nrm);
   }
   float* zl = reinterpret_cast<float*>(big);
   z0_to_lds<T, DH>(role, zacc, nrm, wv, lane, a.np, zl, nv);
@@ -777,7 +785,7 @@ heads_kernel(HeadArgs a) {
 #pragma unroll
     for (int i = 0; i < S::NZ; ++i) zacc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     clear();
-    stream_block<T, DH, kVOwn, true>(kblk, a.ld, a.d, 0, n_tiles, hl, big, wv, lane, role,
+    stream_block<T, DH, kVOwn, true>(kblk, a.ld, a.d, 0, n_tiles, tile_seed(h, 1, 0), big, wv, lane, role,
                                      VSlots{a.v + (size_t)h * a.d, 1, a.np}, acc, low, zacc, nrm);
     z0_to_lds<T, DH>(role, zacc, nrm, wv, lane, a.np, gl, nv);
     n2v = nv[0];
@@ -804,7 +812,7 @@ heads_kernel(HeadArgs a) {
   if (t < DH) tv[t] = z0[t] = zr / vn;
   if constexpr (SRC != H_SPLIT) {
     clear();
-    stream_block<T, DH, 0, true>(qblk, a.ld, a.d, 0, n_tiles, hl, big, wv, lane, role, VSlots{nullptr, 0, 1}, acc, low,
+    stream_block<T, DH, 0, true>(qblk, a.ld, a.d, 0, n_tiles, tile_seed(h, 1, 0), big, wv, lane, role, VSlots{nullptr, 0, 1}, acc, low,
                                  zacc, nrm);
     blocks_to_lds<T, DH>(role, acc, low, gl, lane);
     __syncthreads();

@@ -209,8 +209,12 @@ int key_strips(int64_t units, int64_t heads, int slots, double mat_ratio, int ti
 // The one-workgroup-per-head form: column strips, and its buffers, which
 // share the bytes of the sweeps' partials, sweep0 .. *off (a call uses one or
 // the other), and go past their end where those are smaller.
-// `slack` >= 0: they may add at most that many bytes to the workspace.  The
-// results do not depend on it, only how many key heads a launch pair covers.
+// `slack`: they may add at most that many bytes to the workspace (kAnySlack: as
+// many as kGkBytes allows).  The results do not depend on it, only how many key
+// heads a launch pair covers: the strips and a head's order of summation are
+// the same for any slack, and whether the form runs at all is make_plan's.
+constexpr int64_t kAnySlack = INT64_MAX, kNoHeads = -1;
+
 void plan_heads(const sn_shape* s, Plan& pl, size_t sweep0, int64_t slack, size_t* off) {
   const size_t H = pl.H, dh = s->head_dim, g = pl.g, n_units = (size_t)s->n_layers * s->n_kv_heads;
   const int tiles = ceil_div((int64_t)s->d_model * esize(s->dtype), 128);
@@ -233,7 +237,7 @@ void plan_heads(const sn_shape* s, Plan& pl, size_t sweep0, int64_t slack, size_
   const size_t per_unit = split || g > 1 ? (pl.h_sk + g * pl.h_sq) * mat + g * pl.h_sk * (dh + 1) * 4 : 0;
   const size_t room = *off - sweep0;  // >= fin: the sweeps keep three or more d_h-vectors per head
   size_t most = std::max(kGkBytes, room - fin);
-  if (slack >= 0) most = std::min(most, room - fin + (size_t)slack);
+  if (slack != kAnySlack) most = std::min(most, room - fin + (size_t)slack);
   pl.h_units = per_unit ? (int)std::min(n_units, (most - std::min<size_t>(most, 1024)) / per_unit) : (int)n_units;
   pl.heads = pl.h_units > 0;
   if (pl.heads) pl.h_units = ceil_div(n_units, ceil_div(n_units, pl.h_units));  // pairs of equal length
@@ -254,8 +258,9 @@ void plan_heads(const sn_shape* s, Plan& pl, size_t sweep0, int64_t slack, size_
   *off = std::max(*off, o);
 }
 
-// `slack`: see plan_heads.
-Plan make_plan(const sn_shape* s, const sn_params* p, int64_t slack = -1) {
+// The plan with at most `slack` bytes for the one-workgroup-per-head form
+// beside the sweeps' (see plan_heads; kNoHeads: without it).
+Plan plan_with(const sn_shape* s, const sn_params* p, int64_t slack) {
   Plan pl{};
   const int dh = s->head_dim;
   pl.H = s->n_layers * s->n_q_heads;
@@ -308,7 +313,7 @@ Plan make_plan(const sn_shape* s, const sn_params* p, int64_t slack = -1) {
   const size_t sweep0 = off;
   pl.off_zp = take(2 * H * pl.s_k * dh * 4);
   pl.off_yp = take(H * pl.s_q * dh * 4);
-  if (dh >= 16) plan_heads(s, pl, sweep0, slack, &off);
+  if (dh >= 16 && slack != kNoHeads) plan_heads(s, pl, sweep0, slack, &off);
   if (pl.tail) {
     const size_t nkvh = (size_t)s->n_layers * s->n_kv_heads;
     pl.off_zs = take(H * 4);
@@ -357,6 +362,31 @@ Plan make_plan(const sn_shape* s, const sn_params* p, int64_t slack = -1) {
   }
   pl.bytes = off;
   return pl;
+}
+
+// The static scratch of spectral_step_noalloc, and what its pointer table takes.
+constexpr size_t kScratchBytes = size_t(32) << 20;
+size_t table_bytes(int layers) { return ((size_t)4 * layers * sizeof(void*) + 255) & ~size_t(255); }
+
+// The plan of a call without a context: the sweeps' workspace has to fit the
+// scratch (else *need says what it takes), the rest is the heads form's.
+bool plan_scratch(const sn_shape* s, const sn_params* p, Plan* pl, size_t* need) {
+  sn_params q = *p;
+  q.flags &= ~SN_FLAG_LAYER;  // only reserves space for spectral_step_layer
+  *need = table_bytes(s->n_layers) + plan_with(s, &q, kNoHeads).bytes;
+  if (*need > kScratchBytes) return false;
+  *pl = plan_with(s, &q, (int64_t)(kScratchBytes - *need));
+  return true;
+}
+
+// The plan of a context.  A shape whose sweeps fit the scratch while the
+// matrices of even one key head do not go beside them runs the sweeps in both
+// calls, which give the same bits.
+Plan make_plan(const sn_shape* s, const sn_params* p) {
+  Plan tight{};
+  size_t need = 0;
+  const bool sweeps = s->head_dim >= 16 && plan_scratch(s, p, &tight, &need) && !tight.heads;
+  return plan_with(s, p, sweeps ? kNoHeads : kAnySlack);
 }
 
 struct ProfRec {
@@ -1056,7 +1086,6 @@ SN_API int spectral_step(sn_ctx* c, const void* const* wq_layers, const void* co
 // kernel).
 namespace {
 
-constexpr size_t kScratchBytes = size_t(32) << 20;
 constexpr int kMaxDevices = 64;
 
 static __device__ __attribute__((aligned(256))) uint8_t scratch[kScratchBytes];
@@ -1095,15 +1124,10 @@ SN_API int spectral_step_noalloc(const sn_shape* shape, const sn_params* params,
   c.shape = *shape;
   if (c.shape.ld == 0) c.shape.ld = shape->d_model;
   c.params = *params;
-  c.params.flags &= ~SN_FLAG_LAYER;  // only reserves space for spectral_step_layer
-  c.plan = make_plan(&c.shape, &c.params, 0);
-  const int L = c.shape.n_layers;
-  const size_t tab_bytes = ((size_t)4 * L * sizeof(void*) + 255) & ~size_t(255);
-  const size_t need = tab_bytes + c.plan.bytes;
-  if (need > kScratchBytes)
+  size_t need = 0;
+  if (!plan_scratch(&c.shape, params, &c.plan, &need))
     return fail(SN_EINVAL, "this shape needs " + std::to_string(need) + " bytes of scratch; spectral_step_noalloc " +
                                "holds at most " + std::to_string(kScratchBytes) + " (use spectral_init / spectral_step)");
-  c.plan = make_plan(&c.shape, &c.params, (int64_t)(kScratchBytes - need));
   SN_HIP(hipGetDevice(&c.device));
   char* base = nullptr;
   if ((rc = scratch_on_device(c.device, &base)) != SN_OK) return rc;
@@ -1111,7 +1135,7 @@ SN_API int spectral_step_noalloc(const sn_shape* shape, const sn_params* params,
   c.owns_ws = false;
   c.cache_table = false;
   c.d_tab = reinterpret_cast<const void**>(base);
-  c.ws = base + tab_bytes;
+  c.ws = base + table_bytes(c.shape.n_layers);
   bind_workspace(&c);
   if ((rc = update_table(&c, wq_layers, wk_layers)) != SN_OK) return rc;
   return step_body(&c, v, u, n_iter, sigma, scale, iters);

@@ -39,7 +39,7 @@ CASES = [
     ("own-dh64-f32", 4, 203, 1, 65, 1, 64, "f32"),
     ("keys-dh64", 4, 200, 0, 32, 2, 64, "bf16"),              # 256 heads: Q by one workgroup, K by another
     ("keys-dh32-f32", 2, 257, 3, 9, 16, 32, "f32"),
-    ("keys-dh128-chunks", 4, 64, 0, 200, 2, 128, "bf16"),     # more key heads than one launch pair takes
+    ("keys-dh128-chunks", 4, 64, 0, 480, 2, 128, "bf16"),     # more key heads than one launch pair takes
     # d_h 16, where two of the four waves request no rows, and ten or more tiles per strip
     ("dh16-own-10-tiles", 2, 640, 0, 128, 1, 16, "bf16"),
     ("dh16-own-11-tiles-f32", 2, 331, 1, 128, 1, 16, "f32"),      # unaligned rows of v
@@ -136,17 +136,30 @@ def test_values_outside_the_range_of_gram_products():
     _check(_run(wl, wq.cuda(), wk.cuda(), v0), ref, "heads")
 
 
-def test_noalloc_gives_the_same_bits_in_several_launch_pairs():
+NOALLOC_CASES = [
+    # (id, layers, d, n_kv, group, d_h, dtype): 8 to 66 tiles per strip, so that a head's tile order shows
+    ("pairs", 4, 512, 240, 2, 128, "bf16"),                # Gram matrices of 960 key heads: more than the scratch
+    ("pairs-8-heads", 30, 1024, 32, 8, 128, "bf16"),
+    ("one-key-head", 1, 16384, 1, 8, 128, "bf16"),         # split into strips; a single unit takes most of the scratch
+    ("one-wide-key-head", 1, 65536, 1, 8, 128, "bf16"),
+    ("split", 2, 2112, 3, 4, 64, "f32"),
+]
+
+
+@pytest.mark.parametrize("layers,d,n_kv,group,dh,dtype", [c[1:] for c in NOALLOC_CASES],
+                         ids=[c[0] for c in NOALLOC_CASES])
+def test_noalloc_gives_the_same_bits(layers, d, n_kv, group, dh, dtype):
     """The static scratch leaves room for fewer key heads per launch pair than
-    a context; the results do not depend on it."""
-    wl = _workload(4, 64, 200, 2, 128, "bf16")
+    a context, down to one; the results do not depend on it."""
+    wl = _workload(layers, d, n_kv, group, dh, dtype)
     gq, gk = all_weights(wl, "cuda")
     v0 = start_vectors(wl, "cuda")
     ref = _run(wl, gq, gk, v0)
     v, u = v0.clone(), torch.empty_like(v0)
     sigma = torch.empty(wl.n_layers, wl.n_q, device="cuda")
     scale, iters = torch.empty(wl.n_layers, device="cuda"), torch.empty(sigma.shape, dtype=torch.int32, device="cuda")
-    shape = sp.sn_shape(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, sp.SN_BF16, 0)
+    shape = sp.sn_shape(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim,
+                        sp.SN_BF16 if dtype == "bf16" else sp.SN_F32, 0)
     sp.spectral_step_noalloc(shape, sp.sn_params(wl.alpha, 0.8, 448.0, 0.0, 0, 0, 0),
                              [t.data_ptr() for t in gq.unbind(0)], [t.data_ptr() for t in gk.unbind(0)], v.data_ptr(),
                              u.data_ptr(), wl.n_iter, sigma.data_ptr(), scale.data_ptr(), iters.data_ptr(),
@@ -154,6 +167,27 @@ def test_noalloc_gives_the_same_bits_in_several_launch_pairs():
     torch.cuda.synchronize()
     for k, t in dict(v=v, u=u, sigma=sigma, scale=scale, iters=iters).items():
         np.testing.assert_array_equal(t.cpu().double().numpy(), ref[k], err_msg=k)
+
+
+def test_context_of_several_launch_pairs():
+    """More key heads than one launch pair takes: the launch counts say so, and
+    the heads of each pair agree with the same heads in a context of their own."""
+    wl = _workload(4, 512, 480, 2, 128, "bf16", n_iter=3)
+    gq, gk = all_weights(wl, "cuda")
+    v0 = start_vectors(wl, "cuda")
+    est = Spectral(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha)
+    est.profile(True)
+    v = v0.clone()
+    sigma, _, _ = est.step(gq, gk, v, wl.n_iter)
+    torch.cuda.synchronize()
+    prof = est.profile_read()
+    est.close()
+    assert prof["gram_sweep"][1] == prof["gram_iterate"][1] >= 2, prof
+    for l in range(wl.n_layers):
+        one = _run(wl.replace(n_layers=1), gq[l:l + 1], gk[l:l + 1], v0[l:l + 1])
+        # another layer count may take other column strips and another tile order
+        np.testing.assert_allclose(sigma[l].cpu().double().numpy(), one["sigma"][0], rtol=SIGMA_TOL)
+        assert np.linalg.norm(v[l].cpu().double().numpy() - one["v"][0], axis=-1).max() <= VEC_TOL
 
 
 def test_tolerance_calls_over_64_mib_of_weights():

@@ -16,11 +16,9 @@
 //     z / sigma and y of the last step with 1 / ||K^T y||, which the final sweeps
 //     map to u and v, already normalised.
 // Against n_iter pairs of sweeps, whole calls on one box: 70B GQA shape, 30
-// iterations 54.2 -> 2.38 ms; Llama-2-7B shape 10.5 -> 0.65 ms; GPT-2 XL shape
-// with u 2.55 -> 0.25 ms; GPT-2 small, 20 iterations 405 -> 80 us; 5
-// iterations of 144 heads, d 3001, 261 -> 70 us.  Against the strip-wise Gram
-// form (gram.hip: one wave per Gram matrix, all matrices through memory) the
-// 70B call went from 3.28 to 2.38 ms.
+// iterations 56.3 -> 2.49 ms; Llama-2-7B shape 10.5 -> 0.79 ms; GPT-2 XL shape
+// with u 2.56 -> 0.25 ms; GPT-2 small, 20 iterations 405 -> 72 us; 5
+// iterations of 144 heads, d 3001, 261 -> 68 us.
 //
 // Streaming.  The workgroup's four waves share a ring of row tiles (d_h rows
 // x 128 bytes) in LDS, filled by buffer loads straight to LDS; one bare
@@ -34,10 +32,11 @@
 // blocks.
 //
 // Precision.  z^T G z rounds relative to b = sum_i z_i^2 G_ii, a sweep of Q
-// relative to sqrt(b): a head whose rows nearly cancel in Q^T z (or K^T y)
-// would lose digits here that the sweeps keep.  Every step therefore compares
-// sigma^2 and ||v'||^2 with b; a head that falls under kCancel * b, whose
-// Gram diagonal is near the ends of the float range, or whose values are not
+// relative to sqrt(b), and an error in G repeats in every step, where those of
+// the sweeps differ.  So G's sums and (but for I_HALVES, below) the iteration are
+// in double, with the sweeps' accuracy down to sigma^2 near b / 4.  Every step compares
+// its products with b; a head whose rows cancel further in Q^T z or K^T y, whose
+// Gram matrix is near the ends of the float range, or whose values are not
 // finite is iterated again from z0 by reading Q_h and K_j directly
 // (direct_sweep), in the order of the sweep form and with its stopping rules.
 #include <hip/hip_runtime.h>
@@ -52,12 +51,28 @@ namespace sn {
 namespace {
 
 constexpr int kHThreads = 64 * kHWaves;
-// sigma^2 = z^T G z carries about 1e-7 b of rounding: at b / 16 sigma keeps a
-// relative error of about 1e-6, what the grouped sweeps' bf16 halves leave.
-// Rows that do not cancel have sigma^2 near b or above.
-constexpr float kCancel = 1.f / 16.f;
-constexpr float kGramMin = 1e-26f, kGramMax = 1e34f;  // diagonal range where no product under- or overflows
-constexpr float kTiny = 1e-30f;                       // smallest sigma^2, ||v'||^2 taken from Gram products
+// How a head is iterated.  An error in G repeats in every step, where those of a
+// sweep differ, so G has to be better than the sweeps' 32 bits: its sums are
+// formed in double, and I_ROWS (d_h <= 64; threads hold rows of G) and I_BLOCKS
+// (d_h 128; each wave holds the blocks it accumulated) iterate in double too.
+// I_HALVES is I_ROWS with G and the vectors in float, for d_h 128 where the final
+// W_K sweep takes vectors in two bf16 halves (2^-17), as the sweeps of such
+// groups do in every step (their v errs by 6e-6).
+enum { I_ROWS = 0, I_BLOCKS = 1, I_HALVES = 2 };
+
+// An error E in G, of rows E_i. ~ eps sqrt(G_ii) (sqrt(G_jj))_j, turns w = G z by
+// |E z| / |w|, about eps sqrt(b tr(G)) / |w| with b = sum_i z_i^2 G_ii, and
+// sigma^2 = z^T w by eps b / sigma^2.  Rows that do not cancel have r = sqrt(d_h /
+// (b tr(G))) |w| near 1 or above, and sigma^2 / b too.  Every step needs r (it steers
+// v), the reported one sigma^2 / b as well; a head below is iterated on its
+// weights.  Errors of v after 20 steps with all heads kept, against the sweeps:
+// I_ROWS (d 768) r 0.55 2.1e-7 (3.3e-7), 0.25 7.4e-7 (3.5e-7), 0.08 2.9e-6
+// (4.8e-7); I_BLOCKS (d 1024) 2.4e-7 (4.2e-7), 7.4e-7 (4.4e-7), 3.2e-6 (6.1e-7);
+// I_HALVES (d 4096, 8 heads) 4.0e-6 (6.1e-6), 8.2e-6 (5.7e-6), 2.8e-5 (6.6e-6).
+// Errors of sigma reach the sweeps' at sigma^2 / b near 0.2.
+constexpr float kCancelVec = 0.45f, kCancelSigma = 0.25f;
+constexpr float kTinyRow = 0x1p-40f;                  // least diagonal element, of a trace in [1, 4)
+constexpr float kGramMin = 1e-26f, kGramMax = 1e34f;  // trace of which the products neither under- nor overflow
 
 template <typename T, int DH>
 struct HShape {
@@ -74,13 +89,7 @@ struct HShape {
   static constexpr int NACC = NTRI > NR * NC ? NTRI : NR * NC;
   static constexpr int NZ = RB >= 4 ? RB / 2 : RB;  // row blocks of z0 per wave (2 and 3, or 2 alone)
   static constexpr int P = DH + 1;                  // LDS row pitch of a whole Gram matrix
-  // d_h <= 64: a Gram matrix is kept as two floats per element and the
-  // iteration runs in double.  An error in G repeats in every step, where those
-  // of a sweep differ: with G and the vectors in float the error of v was 4.2e-7
-  // (d 768, fp32, 20 iterations), against 2.2e-7 of the sweeps.
-  static constexpr bool LOW = DH <= 64;
-  static constexpr int MAT = (LOW ? 2 : 1) * NB * 256;         // floats of a Gram matrix in memory
-  static constexpr int GL = (LOW ? 2 : 1) * DH * P * 4;        // bytes of a whole one in LDS
+  static constexpr int MAT = NB * 256;              // elements of a Gram matrix in memory
   static constexpr int EU = DH == 128 ? 2 : 4;                 // workgroups per compute unit (waves per SIMD)
 };
 
@@ -132,16 +141,34 @@ __device__ __forceinline__ void wait_ahead(int own) {
   wait_vm<outstanding_ahead(NST, MAX)>();
 }
 
+// part + the products of one 16-byte chunk of each operand's rows.
 template <typename T>
-__device__ __forceinline__ f32x4 gram_mfma(const u32x4& a, const u32x4& b, f32x4 c) {
-  if constexpr (sizeof(T) == 2) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+__device__ __forceinline__ f32x4 gram_mfma(const u32x4& a, const u32x4& b, const f32x4& part, int e = 0) {
+  if constexpr (sizeof(T) == 2)
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), part, 0,
                                                    0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[e]), __uint_as_float(b[e]), part, 0, 0, 0);
+}
+
+__device__ __forceinline__ void add_double(const f32x4& part, double (&total)[4]) {
+#pragma unroll
+  for (int x = 0; x < 4; ++x) total[x] += (double)part[x];
+}
+
+// total += those products.  Every matrix-core instruction (fp32: two of 4
+// columns each) starts from zero and its sums are added up in double: what is
+// left of the rounding is that within them.
+template <typename T>
+__device__ __forceinline__ void gram_add(const u32x4& a, const u32x4& b, double (&total)[4]) {
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (sizeof(T) == 2) {
+    add_double(gram_mfma<T>(a, b, zero), total);
   } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[e]), __uint_as_float(b[e]), c, 0, 0, 0);
-    return c;
+    for (int e = 0; e < 4; e += 2) add_double(gram_mfma<T>(a, b, gram_mfma<T>(a, b, zero, e), e + 1), total);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) asm volatile("" : "+v"(total[x]));  // the additions stay by their products
   }
 }
 
@@ -166,23 +193,22 @@ struct VSlots {
 };
 
 // Streams tiles t0 .. t1 - 1 of one d_h x d row block through the ring and
-// accumulates this wave's blocks of R R^T (GRAM), as acc + low; with start
+// accumulates this wave's blocks of R R^T (GRAM; CHAIN: the sums of about n / 16
+// tiles in float, for a G that is rounded to float in the end); with start
 // vectors (VST > 0) also its row blocks of z0 and the sums of squares of its
-// slot's columns.  The start vectors'
-// columns ride in the ring beside their tile (chunk c of head i at slot
-// c ^ vswz(i)), as 16-byte loads where their alignment allows, else as 4-byte
-// ones.
+// slot's columns.  The start vectors' columns ride in the ring beside their tile
+// (chunk c of head i at slot c ^ vswz(i)), as 16-byte loads where their alignment
+// allows, else as 4-byte ones.
 template <typename S>
 __device__ __forceinline__ int vswz(int i) {
   return S::ES == 2 ? 2 * (i & 7) : i & 7;
 }
 
-template <typename T, int DH, int VST, bool GRAM>
+template <typename T, int DH, int VST, bool GRAM, bool CHAIN = false>
 __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d, int t0, int t1, uint32_t seed,
                                              uint8_t* ring, int wv, int lane, const Role<HShape<T, DH>>& role,
-                                             const VSlots& vs, f32x4 (&acc)[HShape<T, DH>::NACC],
-                                             f32x4 (&low)[HShape<T, DH>::NACC],
-                                             f32x4 (&zacc)[HShape<T, DH>::NZ], float& nrm) {
+                                             const VSlots& vs, double (&acc)[HShape<T, DH>::NACC][4],
+                                             double (&zacc)[HShape<T, DH>::NZ][4], float& nrm) {
   using S = HShape<T, DH>;
   using R = HRing<T, DH, VST>;
   constexpr bool Z = VST > 0;
@@ -238,36 +264,17 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
 #pragma unroll 1
   for (int i = 0; i < R::NST - 1; ++i)
     if (i < n) issue(i);
-  // Two-level sums: the products of about n / 16 tiles (fp32, four times the
-  // instructions per tile: n / 32) are summed from zero and then added to the
-  // totals with the rounding error of that addition kept (two-sum).  One
-  // accumulation of the matrix cores errs by 0.57 ulp rms, and unlike an error
-  // within a sweep one in G or z0 is not averaged over the iterations: with one
-  // chain over all columns the error of v was 2.5e-6 (d = 768, fp32, 20
-  // iterations) against 2e-7 in the sweeps.
-  const int flush = S::ES == 2 ? (n + 15) / 16 : (n + 31) / 32;
-  f32x4 cur[S::NACC], err[S::NACC], zcur[S::NZ], zerr[S::NZ];
-#pragma unroll
-  for (int x = 0; x < S::NACC; ++x) cur[x] = err[x] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int x = 0; x < S::NZ; ++x) zcur[x] = zerr[x] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto add_up = [](f32x4& total, f32x4& part, f32x4& lost) {
-    const f32x4 sum = total + part, b = sum - total;
-    lost += (total - (sum - b)) + (part - b);
-    total = sum;
-    part = f32x4{0.f, 0.f, 0.f, 0.f};
-  };
-  // fp32 and d_h <= 64: sums of half a tile (error of v at d = 768, 20
-  // iterations, 3.3e-7 -> 2.8e-7)
-  auto half_tile = [&](int kc) {
-    if constexpr (S::LOW && S::ES == 4) {
-      if (kc == 0) {
-#pragma unroll
-        for (int x = 0; x < S::NACC; ++x) add_up(acc[x], cur[x], err[x]);
-      }
+  f32x4 cur[CHAIN ? S::NACC : 1] = {};
+  const int flush = (n + 15) / 16;
+  int left = flush;
+  auto add = [&](const u32x4& a, const u32x4& b, int i) {  // the products of block i
+    if constexpr (CHAIN) {
+      static_assert(S::ES == 2, "bf16 weights");
+      cur[i] = gram_mfma<T>(a, b, cur[i]);
+    } else {
+      gram_add<T>(a, b, acc[i]);
     }
   };
-  int left = flush;
   auto body = [&](int i, auto ragged_tag) {
     constexpr bool RAGGED = decltype(ragged_tag)::value;
     // this wave's part of tile i has landed (the loads of NST - 2 later tiles may be outstanding)
@@ -294,9 +301,7 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
 #pragma unroll
         for (int a = 0; a < S::NR; ++a)
 #pragma unroll
-          for (int b = a; b < S::NR; ++b)
-            cur[tri_index<S::NR>(a, b)] = gram_mfma<T>(fr[a], fr[b], cur[tri_index<S::NR>(a, b)]);
-        half_tile(kc);
+          for (int b = a; b < S::NR; ++b) add(fr[a], fr[b], tri_index<S::NR>(a, b));
       }
     }
     if (role.rect) {
@@ -313,9 +318,7 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
 #pragma unroll
             for (int a = 0; a < S::NR; ++a)
 #pragma unroll
-              for (int b = 0; b < S::NC; ++b)
-                cur[a * S::NC + b] = gram_mfma<T>(fa[a], fb[b], cur[a * S::NC + b]);
-            half_tile(kc);
+              for (int b = 0; b < S::NC; ++b) add(fa[a], fb[b], a * S::NC + b);
           }
         }
         if constexpr (Z) {
@@ -354,29 +357,21 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
             }
           }
 #pragma unroll
-          for (int a = 0; a < S::NC; ++a) zcur[a] = gram_mfma<T>(fa[a], bv, zcur[a]);
+          for (int a = 0; a < S::NC; ++a) gram_add<T>(fa[a], bv, zacc[a]);
           if constexpr (S::RB > 1) {
 #pragma unroll
-            for (int b = 0; b < S::NC; ++b) zcur[S::NC + b] = gram_mfma<T>(fb[b], bv, zcur[S::NC + b]);
+            for (int b = 0; b < S::NC; ++b) gram_add<T>(fb[b], bv, zacc[S::NC + b]);
           }
         }
       }
     }
-    if (--left == 0 || i + 1 == n) {
-      left = flush;
-      if constexpr (GRAM) {
+    if constexpr (CHAIN) {
+      if (--left == 0 || i + 1 == n) {
+        left = flush;
 #pragma unroll
-        for (int x = 0; x < S::NACC; ++x) add_up(acc[x], cur[x], err[x]);
-      }
-      if constexpr (Z) {
-#pragma unroll
-        for (int x = 0; x < S::NZ; ++x) {
-          if constexpr (S::LOW) {
-            add_up(zacc[x], zcur[x], zerr[x]);
-          } else {  // no registers for the errors
-            zacc[x] += zcur[x];
-            zcur[x] = f32x4{0.f, 0.f, 0.f, 0.f};
-          }
+        for (int x = 0; x < S::NACC; ++x) {
+          add_double(cur[x], acc[x]);
+          cur[x] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
       }
     }
@@ -384,16 +379,6 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
 #pragma unroll 1
   for (int i = 0; i < n_whole; ++i) body(i, std::false_type{});
   if (n_whole < n) body(n - 1, std::true_type{});
-#pragma unroll
-  for (int x = 0; x < S::NACC; ++x) {
-    const f32x4 sum = acc[x] + err[x];
-    low[x] = (acc[x] - sum) + err[x];
-    acc[x] = sum;
-  }
-  if constexpr (Z && S::LOW) {
-#pragma unroll
-    for (int x = 0; x < S::NZ; ++x) zacc[x] += zerr[x];
-  }
   __syncthreads();  // the ring is free again
 }
 
@@ -403,24 +388,18 @@ __device__ __forceinline__ int z_row_block(const Role<S>& role, int i) {
   return i < S::NC ? role.row(i) : role.c0 + i - S::NC;
 }
 
-// This wave's blocks of G into the whole symmetric matrix gl (LDS, pitch P;
-// the low parts in a second one behind it).
-template <typename T, int DH>
+// This wave's blocks of G into the whole symmetric matrix gl (LDS, pitch P).
+template <typename T, int DH, typename N>
 __device__ __forceinline__ void blocks_to_lds(const Role<HShape<T, DH>>& role,
-                                              const f32x4 (&acc)[HShape<T, DH>::NACC],
-                                              const f32x4 (&low)[HShape<T, DH>::NACC], float* gl, int lane) {
+                                              const double (&acc)[HShape<T, DH>::NACC][4], N* gl, int lane) {
   using S = HShape<T, DH>;
   const int q = lane >> 4, s = lane & 15;
   auto put = [&](int bi, int bj, int i, bool mirror) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int r = 16 * bi + 4 * q + e, c = 16 * bj + s;
-      gl[r * S::P + c] = acc[i][e];
-      if (mirror) gl[c * S::P + r] = acc[i][e];
-      if constexpr (S::LOW) {
-        gl[(DH + r) * S::P + c] = low[i][e];
-        if (mirror) gl[(DH + c) * S::P + r] = low[i][e];
-      }
+      gl[r * S::P + c] = (N)acc[i][e];
+      if (mirror) gl[c * S::P + r] = (N)acc[i][e];
     }
   };
   if (role.tri) {
@@ -436,70 +415,126 @@ __device__ __forceinline__ void blocks_to_lds(const Role<HShape<T, DH>>& role,
   }
 }
 
-// How the threads share a Gram matrix in the iteration.  d_h 128: thread t =
-// 16 R + C takes rows 8 R .. + 7 and columns C, C + 16, ..; below, where the
-// elements are doubles and a sum over lanes costs three instructions a step,
-// TPR threads take one row, thread t = TPR R + C columns 2 C + 2 TPR j and
-// their right neighbours (d_h 16: column C).
-template <int DH>
+// A Gram matrix in the registers of the workgroup.  I_ROWS: TPR threads take one
+// row, thread t = TPR R + C columns 2 C + 2 TPR j and their right neighbours (d_h
+// 16: column C).  I_HALVES: thread t = 16 R + C rows 8 R .. + 7 and columns C, C +
+// 16, ..  I_BLOCKS: each wave its blocks (36 of 64: G is symmetric), as they left
+// the matrix cores, a lane's four elements of a block in the order e ^ (s mod 4);
+// whole rows of doubles would not fit.
+template <typename T, int DH, int MODE>
 struct Iter {
-  static constexpr bool LOW = HShape<float, DH>::LOW;
-  using Num = std::conditional_t<LOW, double, float>;
-  static constexpr int TPR = LOW ? kHThreads / DH : 16;  // threads per row
-  static constexpr int ROWS = LOW ? 1 : DH / 16;         // rows and columns per thread
-  static constexpr int COLS = DH / TPR;
-  using Mat = Num[ROWS][COLS];
+  using S = HShape<T, DH>;
+  static constexpr bool BLOCKS = MODE == I_BLOCKS;
+  using Num = std::conditional_t<MODE == I_HALVES, float, double>;
+  static constexpr int TPR = BLOCKS ? 1 : MODE == I_HALVES ? 16 : kHThreads / DH;  // threads per row of a product
+  static constexpr int ROWS = MODE == I_HALVES ? DH / 16 : 1, COLS = DH / TPR;
+  using Mat = std::conditional_t<BLOCKS, double[S::NACC][4], Num[ROWS][BLOCKS ? 1 : COLS]>;
+  static constexpr int GL = BLOCKS ? 4 * DH * 8 : DH * S::P * (int)sizeof(Num);  // LDS bytes of a whole G, or of a product's partials
   __device__ static __forceinline__ int col(int C, int j) {
-    return LOW && COLS > 1 ? 2 * C + 2 * TPR * (j >> 1) + (j & 1) : C + 16 * j;
+    return MODE == I_HALVES ? C + 16 * j : COLS > 1 ? 2 * C + 2 * TPR * (j >> 1) + (j & 1) : C;
   }
 };
 
-// This thread's part of the matrix in gl; thread t < DH also takes its
-// diagonal element.  Returns whether the whole diagonal lies in the range
-// where Gram products neither under- nor overflow.
-template <int DH>
-__device__ __forceinline__ bool lds_to_regs(const float* gl, float* diag, typename Iter<DH>::Mat& reg) {
-  using I = Iter<DH>;
+// This thread's part of the whole matrix in gl; thread t < DH also takes its
+// diagonal element.
+template <typename T, int DH, int MODE>
+__device__ __forceinline__ void lds_to_regs(const typename Iter<T, DH, MODE>::Num* gl, float* diag,
+                                            typename Iter<T, DH, MODE>::Mat& reg) {
+  using I = Iter<T, DH, MODE>;
   constexpr int P = DH + 1;
   const int t = threadIdx.x, R = t / I::TPR, C = t % I::TPR;
-  bool bad = false;
-  if (t < DH) {
-    const float x = gl[t * P + t];
-    diag[t] = x;
-    bad = !(x >= kGramMin && x <= kGramMax);
-  }
+  if (t < DH) diag[t] = (float)gl[t * P + t];
 #pragma unroll
   for (int i = 0; i < I::ROWS; ++i)
 #pragma unroll
-    for (int j = 0; j < I::COLS; ++j) {
-      reg[i][j] = gl[(I::ROWS * R + i) * P + I::col(C, j)];
-      if constexpr (I::LOW) reg[i][j] += gl[(DH + R) * P + I::col(C, j)];
-    }
-  return __syncthreads_or(bad) == 0;  // gl is read out too
+    for (int j = 0; j < I::COLS; ++j) reg[i][j] = gl[(I::ROWS * R + i) * P + I::col(C, j)];
+  __syncthreads();  // gl is read out
 }
 
+// The diagonal of the matrix whose blocks the waves hold, and each lane's order of
+// a block's elements (I_BLOCKS).
+template <typename S>
+__device__ __forceinline__ void blocks_diag(const Role<S>& role, double (&g)[S::NACC][4], float* diag, int lane) {
+  const int q = lane >> 4, s = lane & 15;
+  const bool b0 = s & 1, b1 = s & 2;
+#pragma unroll
+  for (int i = 0; i < S::NACC; ++i) {
+    const double y[4] = {b0 ? g[i][1] : g[i][0], b0 ? g[i][0] : g[i][1], b0 ? g[i][3] : g[i][2], b0 ? g[i][2] : g[i][3]};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) g[i][e] = b1 ? y[e ^ 2] : y[e];
+  }
+  if (role.tri && (s >> 2) == q) {
+#pragma unroll
+    for (int a = 0; a < S::NR; ++a) diag[16 * (role.r0 + a) + s] = (float)g[tri_index<S::NR>(a, a)][0];
+  }
+  __syncthreads();
+}
+
+// keep + (give of the lane that CTRL names)
+template <int CTRL>
+__device__ __forceinline__ double dpp_take(double keep, double give) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, give);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
+  return keep + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
 template <int CTRL>
 __device__ __forceinline__ double dpp_add(double x) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, x);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, false);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, false);
-  return x + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+  return dpp_take<CTRL>(x, x);
 }
 
-// out[i] = sum_c G[ROWS R + i][c] x[c], complete in every lane that shares the row.
-template <int DH>
-__device__ __forceinline__ void matvec(const typename Iter<DH>::Mat& g, const typename Iter<DH>::Num* x, int C,
-                                       typename Iter<DH>::Num (&out)[Iter<DH>::ROWS]) {
-  using I = Iter<DH>;
-  typename I::Num xv[I::COLS];
+// Where lane s of a DPP row holds y[j] of row j ^ (s mod 4): the sum of row s mod
+// 4 over the 16 lanes.  Each of the first two steps halves what a lane carries.
+__device__ __forceinline__ double row16_sums_of_4(const double (&y)[4]) {
+  double x = dpp_take<0x4E>(dpp_take<0xB1>(y[0], y[1]), dpp_take<0xB1>(y[2], y[3]));
+  x = dpp_add<0x128>(x);  // rotations by 8 and 4 keep s mod 4
+  return dpp_add<0x124>(x);
+}
+
+// Sum over the four lanes s, s + 16, s + 32, s + 48.
+__device__ __forceinline__ double rows4_sum(double x) {
+  // swapped with itself, a register gives both halves (rows) everywhere
+  auto swap_sum = [](double x, auto swap) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const auto lo = swap((uint32_t)b), hi = swap((uint32_t)(b >> 32));
+    return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+           __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+  };
+  x = swap_sum(x, [](uint32_t r) { return __builtin_amdgcn_permlane16_swap(r, r, false, false); });
+  return swap_sum(x, [](uint32_t r) { return __builtin_amdgcn_permlane32_swap(r, r, false, false); });
+}
+
+// out: this thread's rows of G x, for x in LDS.  I_ROWS and I_HALVES: complete in
+// every thread of a row.  I_BLOCKS: row t in thread t < d_h, with one barrier
+// inside; each block G_IJ off the diagonal gives to the rows of I and, transposed,
+// to those of J, and the waves' partials meet in pp[4][DH], of which the places
+// that no wave writes are zero.
+template <typename T, int DH, int MODE>
+__device__ __forceinline__ void product(const typename Iter<T, DH, MODE>::Mat& g,
+                                        const typename Iter<T, DH, MODE>::Num* x, double* pp,
+                                        const Role<HShape<T, DH>>& role, int wv, int lane,
+                                        typename Iter<T, DH, MODE>::Num (&out)[Iter<T, DH, MODE>::ROWS]) {
+  using S = HShape<T, DH>;
+  using I = Iter<T, DH, MODE>;
+  if constexpr (MODE == I_HALVES) {
+    const int C = threadIdx.x % I::TPR;
+    float xv[I::COLS];
 #pragma unroll
-  for (int j = 0; j < I::COLS; ++j) xv[j] = x[I::col(C, j)];
-  if constexpr (I::LOW) {
+    for (int j = 0; j < I::COLS; ++j) xv[j] = x[I::col(C, j)];
+#pragma unroll
+    for (int i = 0; i < I::ROWS; ++i) {
+      float a = 0.f;
+#pragma unroll
+      for (int j = 0; j < I::COLS; ++j) a = fmaf(g[i][j], xv[j], a);
+      out[i] = row16_sum(a);
+    }
+  } else if constexpr (MODE == I_ROWS) {
+    const int C = threadIdx.x % I::TPR;
     double a0 = 0., a1 = 0.;
 #pragma unroll
     for (int j = 0; j < I::COLS; j += 2) {
-      a0 = fma(g[0][j], xv[j], a0);
-      if constexpr (I::COLS > 1) a1 = fma(g[0][j + 1], xv[j + 1], a1);
+      a0 = fma(g[0][j], x[I::col(C, j)], a0);
+      if constexpr (I::COLS > 1) a1 = fma(g[0][j + 1], x[I::col(C, j + 1)], a1);
     }
     double a = a0 + a1;  // the steps of row16_sum, as many as TPR lanes take
     a = dpp_add<0xB1>(a);
@@ -508,20 +543,81 @@ __device__ __forceinline__ void matvec(const typename Iter<DH>::Mat& g, const ty
     if constexpr (I::TPR > 8) a = dpp_add<0x140>(a);
     out[0] = a;
   } else {
+    asm volatile("" : "+v"(lane));  // addresses formed here, not kept in registers across the iteration
+    const int q = lane >> 4, s = lane & 15;
+    auto rows_of = [&](int bi, double (&xr)[4]) {
 #pragma unroll
-    for (int i = 0; i < I::ROWS; ++i) {
-      float a = 0.f;
+      for (int e = 0; e < 4; ++e) xr[e] = x[16 * bi + 4 * q + (e ^ (s & 3))];
+    };
+    if (role.tri) {  // pp[0]: row sums, pp[1]: column sums
+      double yc[S::NR] = {};
 #pragma unroll
-      for (int j = 0; j < I::COLS; ++j) a = fmaf(g[i][j], xv[j], a);
-      out[i] = row16_sum(a);
+      for (int a = 0; a < S::NR; ++a) {
+        double xr[4], yr[4] = {};
+        rows_of(role.r0 + a, xr);
+#pragma unroll
+        for (int b = a; b < S::NR; ++b) {
+          const double xc = x[16 * (role.r0 + b) + s];
+          const double(&m)[4] = g[tri_index<S::NR>(a, b)];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            yr[e] = fma(m[e], xc, yr[e]);
+            if (b > a) yc[b] = fma(m[e], xr[e], yc[b]);
+          }
+        }
+        const double y = row16_sums_of_4(yr);
+        if (s < 4) pp[16 * (role.r0 + a) + 4 * q + s] = y;
+      }
+#pragma unroll
+      for (int b = 1; b < S::NR; ++b) {
+        const double y = rows4_sum(yc[b]);
+        if (q == b) pp[DH + 16 * (role.r0 + b) + s] = y;
+      }
+    } else {  // pp[2], pp[3]: row sums of waves 2 and 3; their column sums lie in the other half of pp[2]
+      double yc[S::NC] = {};
+#pragma unroll
+      for (int a = 0; a < S::NR; ++a) {
+        double xr[4], yr[4] = {};
+        rows_of(role.row(a), xr);
+#pragma unroll
+        for (int b = 0; b < S::NC; ++b) {
+          const double xc = x[16 * (role.c0 + b) + s];
+          const double(&m)[4] = g[a * S::NC + b];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            yr[e] = fma(m[e], xc, yr[e]);
+            yc[b] = fma(m[e], xr[e], yc[b]);
+          }
+        }
+        const double y = row16_sums_of_4(yr);
+        if (s < 4) pp[wv * DH + 16 * role.row(a) + 4 * q + s] = y;
+      }
+#pragma unroll
+      for (int b = 0; b < S::NC; ++b) {
+        const double y = rows4_sum(yc[b]);
+        if (q == b) pp[2 * DH + 16 * (role.c0 + b) + s] = y;
+      }
     }
+    __syncthreads();
+    const int t = threadIdx.x;
+    out[0] = t < DH ? (pp[t] + pp[DH + t]) + (pp[2 * DH + t] + pp[3 * DH + t]) : 0.;
   }
 }
 
-// Sum over the wave of a value that only the C == 0 lanes hold.
-template <int DH>
-__device__ __forceinline__ float rows_sum(float x) {
-  return c0_lanes_sum(Iter<DH>::TPR < 16 ? row16_sum(x) : x);
+template <int CTRL>
+__device__ __forceinline__ float dpp_take(float keep, float give) {
+  return keep + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, give), CTRL, 0xF, 0xF, true));
+}
+
+// Sum over the lanes of a wave that are equal mod MOD (4, 8 or 16).
+template <int MOD>
+__device__ __forceinline__ float lanes_sum(float x) {
+  if constexpr (MOD < 16) x = dpp_take<0x128>(x, x);  // rotations by 8 and 4
+  if constexpr (MOD < 8) x = dpp_take<0x124>(x, x);
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 // One pass over a d_h x d row block R by the workgroup: w = R^T x, out = R w
@@ -596,17 +692,18 @@ __device__ __forceinline__ float direct_sweep(const char* blk, int64_t ld, int d
 }
 
 // Sums the parts of each head's z0 slot (slots of head i: i np .. + np - 1)
-// from zacc through LDS (16 slots x d_h floats at zl) and the squared norms of
+// from zacc through LDS (16 slots x d_h doubles at zl) and the squared norms of
 // the start vectors into nv[0 .. 16).
 template <typename T, int DH>
-__device__ __forceinline__ void z0_to_lds(const Role<HShape<T, DH>>& role, const f32x4 (&zacc)[HShape<T, DH>::NZ],
-                                          float nrm, int wv, int lane, int np, float* zl, float* nv) {
+__device__ __forceinline__ void z0_to_lds(const Role<HShape<T, DH>>& role, const double (&zacc)[HShape<T, DH>::NZ][4],
+                                          float nrm, int wv, int lane, int np, double* zl, float* nv) {
   using S = HShape<T, DH>;
   const int q = lane >> 4, s = lane & 15;
   if (role.rect) {
 #pragma unroll
     for (int i = 0; i < S::NZ; ++i)
-      *reinterpret_cast<f32x4*>(zl + s * DH + 16 * z_row_block(role, i) + 4 * q) = zacc[i];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) zl[s * DH + 16 * z_row_block(role, i) + 4 * q + e] = zacc[i][e];
   }
   if (wv == 2) {  // both z0 waves read every column; the q lanes of a slot hold disjoint ones
     nrm += __shfl_xor(nrm, 16);
@@ -616,38 +713,61 @@ __device__ __forceinline__ void z0_to_lds(const Role<HShape<T, DH>>& role, const
   __syncthreads();
 }
 
-// This wave's blocks of G to memory, in the block order and lane layout of
-// tri_index and the matrix-core output, the low parts behind all of them.
-template <typename T, int DH>
-__device__ __forceinline__ void blocks_to_memory(const Role<HShape<T, DH>>& role,
-                                                 const f32x4 (&acc)[HShape<T, DH>::NACC],
-                                                 const f32x4 (&low)[HShape<T, DH>::NACC], float* dst, int lane) {
+// f(block of the upper triangle, index into the wave's accumulators) for each of
+// the wave's blocks.  The index is the same in every wave, so that the
+// accumulators stay in registers.
+template <typename T, int DH, typename F>
+__device__ __forceinline__ void each_block(const Role<HShape<T, DH>>& role, F&& f) {
   using S = HShape<T, DH>;
-  f32x4* out = reinterpret_cast<f32x4*>(dst) + lane;
-  auto put = [&](int b, int i) {
-    out[b * 64] = acc[i];
-    if constexpr (S::LOW) out[(S::NB + b) * 64] = low[i];
-  };
-  if (role.tri) {
 #pragma unroll
-    for (int x = 0; x < S::NR; ++x)
+  for (int x = 0; x < S::NR; ++x)
 #pragma unroll
-      for (int y = x; y < S::NR; ++y)
-        put(tri_index<S::RB>(role.r0 + x, role.r0 + y), tri_index<S::NR>(x, y));
-  } else if (S::RB > 1 && role.rect) {
-#pragma unroll
-    for (int x = 0; x < S::NR; ++x)
-#pragma unroll
-      for (int y = 0; y < S::NC; ++y) put(tri_index<S::RB>(role.row(x), role.c0 + y), x * S::NC + y);
-  }
+    for (int y = x; y < S::NR; ++y) {
+      const int i = tri_index<S::NR>(x, y);
+      const bool in_rect = S::RB > 1 && i < S::NR * S::NC && role.rect;
+      if (role.tri || in_rect)
+        f(role.tri ? tri_index<S::RB>(role.r0 + x, role.r0 + y)
+                   : tri_index<S::RB>(role.row(i / S::NC), role.c0 + i % S::NC),
+          i);
+    }
+  static_assert(S::NTRI >= S::NR * S::NC, "the triangle's indices cover the other half's");
 }
 
-// The sum of `strips` Gram matrices written by blocks_to_memory, as a whole
-// symmetric matrix in LDS.
+// This wave's blocks of G to memory, in the block order and lane layout of
+// tri_index and the matrix-core output.
 template <typename T, int DH>
-__device__ __forceinline__ void memory_to_lds(const float* src, int strips, float* gl) {
+__device__ __forceinline__ void blocks_to_memory(const Role<HShape<T, DH>>& role,
+                                                 const double (&acc)[HShape<T, DH>::NACC][4], double* dst, int lane) {
+  each_block<T, DH>(role, [&](int b, int i) {
+    double* out = dst + (b * 64 + lane) * 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out[e] = acc[i][e];
+  });
+}
+
+// The sum of `strips` Gram matrices written by blocks_to_memory: this wave's
+// blocks of it (d_h 128), or a whole symmetric matrix in LDS.
+template <typename T, int DH>
+__device__ __forceinline__ void memory_to_blocks(const Role<HShape<T, DH>>& role, const double* src, int strips,
+                                                 double (&g)[HShape<T, DH>::NACC][4], int lane) {
   using S = HShape<T, DH>;
-  const f32x4* in = reinterpret_cast<const f32x4*>(src);
+  each_block<T, DH>(role, [&](int b, int i) {
+    const double* in = src + (b * 64 + lane) * 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) g[i][e] = in[e];
+  });
+#pragma unroll 1
+  for (int st = 1; st < strips; ++st) {
+    each_block<T, DH>(role, [&](int b, int i) {
+      const double* in = src + (size_t)st * S::MAT + (b * 64 + lane) * 4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) g[i][e] += in[e];
+    });
+  }
+}
+template <typename T, int DH, typename N>
+__device__ __forceinline__ void memory_to_lds(const double* src, int strips, N* gl) {
+  using S = HShape<T, DH>;
   for (int x = threadIdx.x; x < S::NB * 64; x += kHThreads) {
     const int b = x >> 6, ln = x & 63;
     int bi = 0, start = 0;
@@ -656,27 +776,19 @@ __device__ __forceinline__ void memory_to_lds(const float* src, int strips, floa
       ++bi;
     }
     const int bj = bi + (b - start);
-    f32x4 y = in[x], lost = f32x4{0.f, 0.f, 0.f, 0.f};
-    if constexpr (S::LOW) lost = in[S::NB * 64 + x];
+    double y[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] = src[x * 4 + e];
 #pragma unroll 4
-    for (int st = 1; st < strips; ++st) {  // two-sum, as in stream_block
-      const f32x4 p = in[(size_t)st * (S::MAT / 4) + x], sum = y + p, b = sum - y;
-      lost += (y - (sum - b)) + (p - b);
-      if constexpr (S::LOW) lost += in[(size_t)st * (S::MAT / 4) + S::NB * 64 + x];
-      y = sum;
+    for (int st = 1; st < strips; ++st) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) y[e] += src[(size_t)st * S::MAT + x * 4 + e];
     }
-    const f32x4 sum = y + lost;
-    lost = (y - sum) + lost;
-    y = sum;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int r = 16 * bi + 4 * (ln >> 4) + e, c = 16 * bj + (ln & 15);
-      gl[r * S::P + c] = y[e];
-      if (bi != bj) gl[c * S::P + r] = y[e];
-      if constexpr (S::LOW) {
-        gl[(DH + r) * S::P + c] = lost[e];
-        if (bi != bj) gl[(DH + c) * S::P + r] = lost[e];
-      }
+      gl[r * S::P + c] = (N)y[e];
+      if (bi != bj) gl[c * S::P + r] = (N)y[e];
     }
   }
   __syncthreads();
@@ -698,17 +810,13 @@ units_kernel(HeadArgs a) {
   using S = HShape<T, DH>;
   constexpr int RING = HRing<T, DH, kVKeys>::BYTES > HRing<T, DH, 0>::BYTES ? HRing<T, DH, kVKeys>::BYTES
                                                                             : HRing<T, DH, 0>::BYTES;
-  static_assert(RING >= 16 * DH * 4, "the z0 slots fit the ring");
+  static_assert(RING >= 16 * DH * 8, "the z0 slots fit the ring");
   __shared__ __attribute__((aligned(16))) uint8_t big[RING];
   __shared__ float nv[16];
   const int lane = threadIdx.x & 63, wv = uni((int)(threadIdx.x >> 6));
   const Role<S> role(wv);
   const int n_tiles = (a.d + S::TC - 1) / S::TC;
-  f32x4 acc[S::NACC], low[S::NACC], zacc[S::NZ];
-#pragma unroll
-  for (int i = 0; i < S::NACC; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int i = 0; i < S::NZ; ++i) zacc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  double acc[S::NACC][4] = {}, zacc[S::NZ][4] = {};
   float nrm = 0.f;
   const int item = blockIdx.x, n_key = a.units * a.nch * a.sk;
   if (item >= n_key) {
@@ -716,9 +824,9 @@ units_kernel(HeadArgs a) {
     const int h = a.head0 + hl;
     const char* blk = uni(a.mats[h / a.n_q]) + (int64_t)(h % a.n_q) * DH * a.ld * S::ES;
     const int t0 = strip * a.tps_q, t1 = min(t0 + a.tps_q, n_tiles);
-    stream_block<T, DH, 0, true>(blk, a.ld, a.d, t0, t1, tile_seed(h, a.sq, strip), big, wv, lane, role, VSlots{nullptr, 0, 1}, acc, low,
-                                 zacc, nrm);
-    blocks_to_memory<T, DH>(role, acc, low, a.gq + (size_t)(hl * a.sq + strip) * S::MAT, lane);
+    stream_block<T, DH, 0, true>(blk, a.ld, a.d, t0, t1, tile_seed(h, a.sq, strip), big, wv, lane, role, VSlots{nullptr, 0, 1}, acc, zacc,
+                                 nrm);
+    blocks_to_memory<T, DH>(role, acc, a.gq + (size_t)(hl * a.sq + strip) * S::MAT, lane);
     return;
   }
   const int strip = item % a.sk, ch = item / a.sk % a.nch, ul = item / (a.sk * a.nch);
@@ -730,19 +838,19 @@ units_kernel(HeadArgs a) {
   const int t0 = strip * a.tps_k, t1 = min(t0 + a.tps_k, n_tiles);
   const uint32_t seed = tile_seed(unit * a.nch + ch, a.sk, strip);
   if (ch == 0) {
-    stream_block<T, DH, kVKeys, true>(blk, a.ld, a.d, t0, t1, seed, big, wv, lane, role, vs, acc, low, zacc, nrm);
-    blocks_to_memory<T, DH>(role, acc, low, a.gk + (size_t)(ul * a.sk + strip) * S::MAT, lane);
+    stream_block<T, DH, kVKeys, true>(blk, a.ld, a.d, t0, t1, seed, big, wv, lane, role, vs, acc, zacc, nrm);
+    blocks_to_memory<T, DH>(role, acc, a.gk + (size_t)(ul * a.sk + strip) * S::MAT, lane);
   } else {
-    stream_block<T, DH, kVKeys, false>(blk, a.ld, a.d, t0, t1, seed, big, wv, lane, role, vs, acc, low, zacc, nrm);
+    stream_block<T, DH, kVKeys, false>(blk, a.ld, a.d, t0, t1, seed, big, wv, lane, role, vs, acc, zacc, nrm);
   }
-  float* zl = reinterpret_cast<float*>(big);
+  double* zl = reinterpret_cast<double*>(big);
   z0_to_lds<T, DH>(role, zacc, nrm, wv, lane, a.np, zl, nv);
   for (int x = threadIdx.x; x < nvalid * DH; x += kHThreads) {
     const int i = x / DH, r = x % DH;
-    float z = 0.f;
+    double z = 0.;
     for (int p = 0; p < a.np; ++p) z += zl[(i * a.np + p) * DH + r];
     const size_t o = (size_t)(h0 + i) * a.sk + strip;
-    a.zp[o * DH + r] = z;
+    a.zp[o * DH + r] = (float)z;
     if (r == 0) a.zn[o] = nv[i];
   }
 }
@@ -752,53 +860,77 @@ units_kernel(HeadArgs a) {
 // here.  H_SPLIT: both from units_kernel.
 enum { H_OWN = 0, H_KEYS = 1, H_SPLIT = 2 };
 
-template <typename T, int DH, int SRC>
+template <typename T, int DH, int SRC, int MODE>
 __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(HShape<T, DH>::EU)))
 heads_kernel(HeadArgs a) {
   using S = HShape<T, DH>;
-  using I = Iter<DH>;
-  constexpr int RPT = I::ROWS;
+  using I = Iter<T, DH, MODE>;
+  using Num = typename I::Num;
   constexpr int RING0 = HRing<T, DH, 0>::BYTES, RINGV = HRing<T, DH, kVOwn>::BYTES;
   constexpr int RING = SRC == H_SPLIT ? 0 : SRC == H_OWN && RINGV > RING0 ? RINGV : RING0;
-  __shared__ __attribute__((aligned(16))) uint8_t big[RING > S::GL ? RING : S::GL];
-  __shared__ float z0[DH], tb[DH], wb[DH], dq[DH], dk[DH];
-  __shared__ __attribute__((aligned(16))) typename I::Num tv[DH], yv[DH];  // the iteration's t and w (last step: y)
-  __shared__ float nv[16], red[4][kHWaves];
-  float* gl = reinterpret_cast<float*>(big);
+  __shared__ __attribute__((aligned(16))) uint8_t big[RING > I::GL ? RING : I::GL];
+  __shared__ float z0[DH], tb[DH], wb[DH], dq[DH], dk[DH], nv[16], red[2][3][kHWaves];
+  __shared__ __attribute__((aligned(16))) Num vec[2][DH];
+  Num *tv = vec[0], *yv = vec[1];  // the iteration's t and w (last step: y)
+  Num* gl = reinterpret_cast<Num*>(big);
+  double* pp = reinterpret_cast<double*>(big);
   const int t = threadIdx.x, lane = t & 63, wv = uni(t >> 6);
-  const int R = t / I::TPR, C = t % I::TPR;
+  const bool own = I::BLOCKS ? t < DH : t % I::TPR == 0;  // has rows row0 .. of a product
+  const int row0 = I::BLOCKS ? t : I::ROWS * (t / I::TPR);
   const int hl = blockIdx.x, h = a.head0 + hl;
   const int layer = h / a.n_q, hq = h % a.n_q, j = hq / a.g;
   const char* qblk = uni(a.mats[layer]) + (int64_t)hq * DH * a.ld * S::ES;
   const char* kblk = uni(a.mats[a.L + layer]) + (int64_t)j * DH * a.ld * S::ES;
   const int n_tiles = (a.d + S::TC - 1) / S::TC;
   const Role<S> role(wv);
-  f32x4 acc[S::NACC], low[S::NACC], zacc[S::NZ];
+  double acc[S::NACC][4], zacc[S::NZ][4];
   typename I::Mat gq, gk;
-  float nrm = 0.f, n2v = 0.f, zr = 0.f;  // ||v||^2 and, in thread r < d_h, z0[r] ||v||
-  auto clear = [&] {
+  float nrm = 0.f, n2v = 0.f;
+  double zr = 0.;  // ||v||^2 and, in thread r < d_h, z0[r] ||v||
+  auto clear = [](auto& m) {
 #pragma unroll
-    for (int i = 0; i < S::NACC; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (auto& b : m)
+#pragma unroll
+      for (double& x : b) x = 0.;
   };
-  bool in_range = true;
-  if constexpr (SRC == H_OWN) {
+  // the matrix whose blocks acc holds, in registers, and its diagonal
+  auto take = [&](typename I::Mat& g, float* diag) {
+    if constexpr (!I::BLOCKS) {
+      blocks_to_lds<T, DH>(role, acc, gl, lane);
+      __syncthreads();
+      lds_to_regs<T, DH, MODE>(gl, diag, g);
+    } else {
 #pragma unroll
-    for (int i = 0; i < S::NZ; ++i) zacc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    clear();
+      for (int i = 0; i < S::NACC; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) g[i][e] = acc[i][e];
+      blocks_diag<S>(role, g, diag, lane);
+    }
+  };
+  auto load = [&](const double* src, int strips, typename I::Mat& g, float* diag) {
+    if constexpr (!I::BLOCKS) {
+      memory_to_lds<T, DH>(src, strips, gl);
+      lds_to_regs<T, DH, MODE>(gl, diag, g);
+    } else {
+      memory_to_blocks<T, DH>(role, src, strips, g, lane);
+      blocks_diag<S>(role, g, diag, lane);
+    }
+  };
+  if constexpr (SRC == H_OWN) {
+    clear(zacc);
+    clear(acc);
     stream_block<T, DH, kVOwn, true>(kblk, a.ld, a.d, 0, n_tiles, tile_seed(h, 1, 0), big, wv, lane, role,
-                                     VSlots{a.v + (size_t)h * a.d, 1, a.np}, acc, low, zacc, nrm);
-    z0_to_lds<T, DH>(role, zacc, nrm, wv, lane, a.np, gl, nv);
+                                     VSlots{a.v + (size_t)h * a.d, 1, a.np}, acc, zacc, nrm);
+    z0_to_lds<T, DH>(role, zacc, nrm, wv, lane, a.np, pp, nv);
     n2v = nv[0];
     if (t < DH)
-      for (int p = 0; p < a.np; ++p) zr += gl[p * DH + t];
+      for (int p = 0; p < a.np; ++p) zr += pp[p * DH + t];
     __syncthreads();
-    blocks_to_lds<T, DH>(role, acc, low, gl, lane);
-    __syncthreads();
-    in_range = lds_to_regs<DH>(gl, dk, gk);
+    take(gk, dk);
   } else {
     for (int st = 0; st < a.sk; ++st) n2v += a.zn[(size_t)hl * a.sk + st];
     if (t < DH)
-      for (int st = 0; st < a.sk; ++st) zr += a.zp[((size_t)hl * a.sk + st) * DH + t];
+      for (int st = 0; st < a.sk; ++st) zr += (double)a.zp[((size_t)hl * a.sk + st) * DH + t];
   }
   const float vn = sqrtf(n2v);
   if (t == 0) a.w.vnorm0[h] = vn;
@@ -809,27 +941,41 @@ heads_kernel(HeadArgs a) {
     }
     return;
   }
-  if (t < DH) tv[t] = z0[t] = zr / vn;
+  zr /= (double)vn;
+  if (t < DH) z0[t] = (float)zr;
   if constexpr (SRC != H_SPLIT) {
-    clear();
-    stream_block<T, DH, 0, true>(qblk, a.ld, a.d, 0, n_tiles, tile_seed(h, 1, 0), big, wv, lane, role, VSlots{nullptr, 0, 1}, acc, low,
-                                 zacc, nrm);
-    blocks_to_lds<T, DH>(role, acc, low, gl, lane);
-    __syncthreads();
+    clear(acc);
+    stream_block<T, DH, 0, true, MODE == I_HALVES>(qblk, a.ld, a.d, 0, n_tiles, tile_seed(h, 1, 0), big, wv, lane, role,
+                                 VSlots{nullptr, 0, 1}, acc, zacc, nrm);
+    take(gq, dq);
   } else {
-    memory_to_lds<T, DH>(a.gq + (size_t)hl * a.sq * S::MAT, a.sq, gl);
+    load(a.gq + (size_t)hl * a.sq * S::MAT, a.sq, gq, dq);
   }
-  in_range = lds_to_regs<DH>(gl, dq, gq) && in_range;
-  if constexpr (SRC != H_OWN) {
-    memory_to_lds<T, DH>(a.gk + (size_t)(layer * a.n_kv + j - a.unit0) * a.sk * S::MAT, a.sk, gl);
-    in_range = lds_to_regs<DH>(gl, dk, gk) && in_range;
-  }
+  if constexpr (SRC != H_OWN)
+    load(a.gk + (size_t)(layer * a.n_kv + j - a.unit0) * a.sk * S::MAT, a.sk, gk, dk);
+
+  // The iteration runs on G_Q / fq^2 and G_K / fk^2, fq and fk powers of two
+  // that take the traces (trq, trk) to [1, 4): its values then stay in range
+  // whatever the weights' size.
+  auto scale_of = [&](const float* diag, float* f, float* tr) {
+    float x = diag[lane % DH];
+    if constexpr (DH > 64) x += diag[lane + 64];
+    const float sum = c0_lanes_sum(row16_sum(x)) * (DH < 64 ? DH / 64.f : 1.f);
+    *f = 1.f;
+    if (!(sum >= kGramMin && sum <= kGramMax)) return false;
+    const int e = ilogbf(sum) >> 1;
+    *f = ldexpf(1.f, e);
+    *tr = ldexpf(sum, -2 * e);
+    return true;
+  };
+  float fq, fk, trq = 0.f, trk = 0.f;
+  const bool in_range = scale_of(dq, &fq, &trq) & scale_of(dk, &fk, &trk);
 
   float* fin = a.w.fin + (size_t)h * 2 * DH;
-  auto finish = [&](int k, float sig, const auto* z, float zs, const auto* y, float rn) {
+  auto finish = [&](int k, float sig, const auto* z, float zs, const auto* y, float ys, float rn) {
     if (t < DH) {
       fin[t] = (float)(z[t] * zs);
-      fin[DH + t] = a.round_y ? (float)y[t] : (float)(y[t] * rn);
+      fin[DH + t] = a.round_y ? (float)(y[t] * ys) : (float)(y[t] * ys * rn);
     }
     if (t == 0) {
       a.sigma[h] = sig;
@@ -852,15 +998,68 @@ heads_kernel(HeadArgs a) {
   };
 
   if (in_range) {
-    float dqr[RPT], dkr[RPT];
+    const Num sq = (Num)1 / ((Num)fq * (Num)fq), sk = (Num)1 / ((Num)fk * (Num)fk);
 #pragma unroll
-    for (int i = 0; i < RPT; ++i) {
-      dqr[i] = dq[RPT * R + i];
-      dkr[i] = dk[RPT * R + i];
+    for (auto& b : gq)
+#pragma unroll
+      for (Num& x : b) x *= sq;
+#pragma unroll
+    for (auto& b : gk)
+#pragma unroll
+      for (Num& x : b) x *= sk;
+    // Three sums over the rows follow each product: z^T w (lanes with C mod 4 = 0),
+    // the rounding bound z_i^2 G_ii (1) and w^2 (2), each lane adding up its own.
+    const int c = lane & 3;
+    float dqr[I::ROWS], dkr[I::ROWS];
+#pragma unroll
+    for (int i = 0; i < I::ROWS; ++i) {
+      const bool mine = I::BLOCKS ? t < DH : c == 1;
+      dqr[i] = mine ? fmaxf(dq[row0 + i] * (float)sq, kTinyRow) : 1.f;
+      dkr[i] = mine ? fmaxf(dk[row0 + i] * (float)sk, kTinyRow) : 1.f;
     }
-    float zscale = 1.f, prev = 0.f;
-    typename I::Num out[RPT];
-    bool ok = true;
+    if (t < DH) tv[t] = (Num)(zr / fk);
+    if constexpr (I::BLOCKS) {
+      for (int i = t; i < 4 * DH; i += kHThreads) pp[i] = 0.;
+    }
+    __syncthreads();
+    float prev = 0.f, zscale = 1.f;
+    Num out[I::ROWS];
+    // After a product out of the vector x (LDS), both times `by`: its rows to y
+    // (unless null), and the sums over the wave's rows.
+    auto sums = [&](int to, const Num* x, Num* y, float by, const float (&diag)[I::ROWS]) {
+      float sum = 0.f;
+      if constexpr (I::BLOCKS) {
+        if (own) {
+          const Num w = out[0] * by, z = x[row0] * by;
+          const float wf = (float)w, zf = (float)z;
+          const float v[3] = {zf * wf, zf * zf * diag[0], wf * wf};
+          // v[j ^ c] at j, so that a lane keeps v[c] and gives the others away
+          const bool b0 = c & 1, b1 = c & 2;
+          const float p[4] = {b0 ? v[1] : v[0], b0 ? v[0] : v[1], b0 ? 0.f : v[2], b0 ? v[2] : 0.f};
+          const float lo = dpp_take<0xB1>(b1 ? p[2] : p[0], b1 ? p[3] : p[1]);
+          const float hi = dpp_take<0xB1>(b1 ? p[0] : p[2], b1 ? p[1] : p[3]);
+          sum = dpp_take<0x4E>(lo, hi);
+          if (y) y[row0] = w;
+        }
+        sum = lanes_sum<4>(sum);
+      } else {
+#pragma unroll
+        for (int i = 0; i < I::ROWS; ++i) {
+          const Num w = out[i] * by, z = x[row0 + i] * by;
+          const float wf = (float)w, zf = (float)z;
+          sum = fmaf((c == 2 ? wf : zf) * diag[i], c == 1 ? zf : wf, sum);
+          if (own && y) y[row0 + i] = w;
+        }
+        sum = lanes_sum<I::TPR>(sum);
+      }
+      if (lane < 3) red[to][lane][wv] = sum;
+    };
+    auto dot_of = [&](int from) { return sum_waves<kHWaves>(red[from][0]); };
+    // Whether the products just summed up may be used.
+    auto exact_enough = [&](int from, float tr, float dot, bool reported) {
+      const float bound = sum_waves<kHWaves>(red[from][1]), ww = sum_waves<kHWaves>(red[from][2]);
+      return dot > 0.f && DH * ww >= kCancelVec * kCancelVec * bound * tr && (!reported || dot >= kCancelSigma * bound);
+    };
     // Each product is formed on the unscaled vector before the sums of the
     // step that made it are looked at: their way through LDS, the square root
     // and the division run beside it.  In steps that cannot be the last only
@@ -870,35 +1069,17 @@ heads_kernel(HeadArgs a) {
 #pragma unroll 1
     for (int k = 1;; ++k) {
       // w = G_Q z with z = zscale * tv
-      matvec<DH>(gq, tv, C, out);
+      product<T, DH, MODE>(gq, tv, pp, role, wv, lane, out);
       if (k > 1) {
-        const float n2 = sum_waves<kHWaves>(red[2]);
-        ok = n2 >= kCancel * sum_waves<kHWaves>(red[3]) && n2 >= kTiny;
+        const float n2 = dot_of(1);
+        if (!exact_enough(1, trk, n2, false)) break;
         zscale = may_end(k) ? 1.0f / sqrtf(n2) : __builtin_amdgcn_rsqf(n2);
       }
-      if (!ok) break;
-      float part = 0.f, bound = 0.f;
-      if (C == 0) {
-#pragma unroll
-        for (int i = 0; i < RPT; ++i) {
-          const typename I::Num wr = out[i] * zscale;
-          const float zr = (float)(tv[RPT * R + i] * zscale);
-          part = fmaf(zr, (float)wr, part);
-          bound = fmaf(zr * zr, dqr[i], bound);
-          yv[RPT * R + i] = wr;
-        }
-      }
-      part = rows_sum<DH>(part);
-      bound = rows_sum<DH>(bound);
-      if (lane == 0) {
-        red[0][wv] = part;
-        red[1][wv] = bound;
-      }
+      sums(0, tv, yv, zscale, dqr);
       __syncthreads();
       // t = G_K y with y = w / sigma
-      matvec<DH>(gk, yv, C, out);
-      const float s2 = sum_waves<kHWaves>(red[0]);
-      if (!(s2 >= kCancel * sum_waves<kHWaves>(red[1])) || !(s2 >= kTiny)) break;
+      product<T, DH, MODE>(gk, yv, pp, role, wv, lane, out);
+      const float s2 = dot_of(0);
       float sig = 0.f, inv_sig;
       bool last = false;
       if (may_end(k)) {
@@ -908,35 +1089,18 @@ heads_kernel(HeadArgs a) {
       } else {
         inv_sig = __builtin_amdgcn_rsqf(s2);
       }
+      if (!exact_enough(0, trq, s2, last)) break;
       if (last) {
         __syncthreads();
         last_y(yv, inv_sig);
-        matvec<DH>(gk, yv, C, out);
+        product<T, DH, MODE>(gk, yv, pp, role, wv, lane, out);
       }
-      const float inv = last ? 1.f : inv_sig;
-      part = 0.f;
-      bound = 0.f;
-      if (C == 0) {
-#pragma unroll
-        for (int i = 0; i < RPT; ++i) {
-          const typename I::Num tr = out[i] * inv;
-          const float yr = (float)(yv[RPT * R + i] * inv);
-          part = fmaf(yr, (float)tr, part);
-          bound = fmaf(yr * yr, dkr[i], bound);
-          if (!last) tv[RPT * R + i] = tr;
-        }
-      }
-      part = rows_sum<DH>(part);
-      bound = rows_sum<DH>(bound);
-      if (lane == 0) {
-        red[2][wv] = part;
-        red[3][wv] = bound;
-      }
+      sums(1, yv, last ? nullptr : tv, last ? 1.f : inv_sig, dkr);
       __syncthreads();
       if (last) {
-        const float n2 = sum_waves<kHWaves>(red[2]);
-        if (!(n2 >= kCancel * sum_waves<kHWaves>(red[3])) || !(n2 >= kTiny)) break;
-        finish(k, sig, tv, zscale * inv_sig, yv, 1.0f / sqrtf(n2));
+        const float n2 = dot_of(1);
+        if (!exact_enough(1, trk, n2, true)) break;
+        finish(k, sig * fq * fk, tv, zscale * inv_sig / fq, yv, fq, 1.0f / (sqrtf(n2) * fq * fk));
         return;
       }
       prev = sig;
@@ -946,13 +1110,13 @@ heads_kernel(HeadArgs a) {
 
   // the head's rows cancel, or its values leave the range of the Gram
   // products: iterate by reading the weights, from z0
-  float* part = gl;
+  float* part = reinterpret_cast<float*>(big);
   if (t < DH) tb[t] = z0[t];
   __syncthreads();
   float prev = 0.f;
 #pragma unroll 1
   for (int k = 1;; ++k) {
-    const float s2 = direct_sweep<T, DH>(qblk, a.ld, a.d, tb, wb, part, red[0], wv, lane);
+    const float s2 = direct_sweep<T, DH>(qblk, a.ld, a.d, tb, wb, part, red[0][0], wv, lane);
     const float sig = sqrtf(s2);
     if (s2 == 0.f) {  // M v = 0
       if (t == 0) {
@@ -969,10 +1133,10 @@ heads_kernel(HeadArgs a) {
       if (t < DH) wb[t] *= inv;
       __syncthreads();
     }
-    const float n2 = direct_sweep<T, DH>(kblk, a.ld, a.d, wb, dq, part, red[0], wv, lane);
+    const float n2 = direct_sweep<T, DH>(kblk, a.ld, a.d, wb, dq, part, red[0][0], wv, lane);
     const float rn = 1.0f / sqrtf(n2);
     if (last) {
-      finish(k, sig, tb, inv, wb, rn);
+      finish(k, sig, tb, inv, wb, 1.f, rn);
       return;
     }
     if (t < DH) tb[t] = dq[t] * rn;
@@ -1024,17 +1188,30 @@ __global__ void __launch_bounds__(kThreads) heads_finalize_kernel(FinArgs f) {
   }
 }
 
+template <typename T, int DH, int MODE>
+void launch_mode(const HeadArgs& a, int heads, hipStream_t st) {
+  if (a.sq > 0)
+    heads_kernel<T, DH, H_SPLIT, MODE><<<dim3(heads), kHThreads, 0, st>>>(a);
+  else if (a.g > 1)
+    heads_kernel<T, DH, H_KEYS, MODE><<<dim3(heads), kHThreads, 0, st>>>(a);
+  else if constexpr (MODE != I_HALVES)
+    heads_kernel<T, DH, H_OWN, MODE><<<dim3(heads), kHThreads, 0, st>>>(a);
+}
+
 template <typename T, int DH>
 void launch_dh(const HeadArgs& a, bool units, hipStream_t st) {
   const int heads = a.units * a.g;
-  if (units)
+  if (units) {
     units_kernel<T, DH><<<dim3(a.units * a.nch * a.sk + heads * a.sq), kHThreads, 0, st>>>(a);
-  else if (a.sq > 0)
-    heads_kernel<T, DH, H_SPLIT><<<dim3(heads), kHThreads, 0, st>>>(a);
-  else if (a.g > 1)
-    heads_kernel<T, DH, H_KEYS><<<dim3(heads), kHThreads, 0, st>>>(a);
-  else
-    heads_kernel<T, DH, H_OWN><<<dim3(heads), kHThreads, 0, st>>>(a);
+    return;
+  }
+  if constexpr (sizeof(T) == 2 && DH == 128) {
+    if (a.round_y) {
+      launch_mode<T, DH, I_HALVES>(a, heads, st);
+      return;
+    }
+  }
+  launch_mode<T, DH, DH <= 64 ? I_ROWS : I_BLOCKS>(a, heads, st);
 }
 
 template <typename T>
@@ -1050,7 +1227,7 @@ void launch_t(int dh, const HeadArgs& a, bool units, hipStream_t st) {
 }  // namespace
 
 void launch_heads(bool bf16, int head_dim, bool units, hipStream_t st, HeadArgs a) {
-  a.hps = heads_per_operand(bf16, head_dim, a.g);
+  a.hps = heads_per_operand(bf16, a.round_y != 0, a.g);
   a.np = !bf16 ? 1 : a.hps == 8 ? 2 : 3;
   a.nch = (a.g + a.hps - 1) / a.hps;
   if (bf16)

@@ -148,8 +148,8 @@ struct HeadArgs {
   int32_t n_iter;
   float tol;
   const float* v;
-  float* gk;                // [units][sk][NB][64][4]: G_K partials, blocks as in GramArgs::gp
-  float* gq;                // [heads][sq][NB][64][4]: G_Q partials
+  double* gk;               // [units][sk][NB][64][4]: G_K partials, blocks as in GramArgs::gp
+  double* gq;               // [heads][sq][NB][64][4]: G_Q partials
   float* zp;                // [heads][sk][DH]: partials of K_j v
   float* zn;                // [heads][sk]: partials of ||v||^2
   Work w;                   // fin, vnorm0 and sig
@@ -265,9 +265,9 @@ void launch_gram_iterate(int head_dim, int heads, hipStream_t st, const IterArgs
 // units: the units_kernel of the pair (none where a head's workgroup reads both its matrices), else heads_kernel
 // Query heads per z0 operand of 16 slots.  bf16 weights: three bf16 parts of v
 // per head (24 bits, 5 heads); two (16 bits, 8 heads) only where they save an
-// operand and the grouped sweeps keep no more either (d_h 64 and 128); fp32
-// weights take v as it is.
-inline int heads_per_operand(bool bf16, int head_dim, int g) { return !bf16 ? 16 : g > 5 && head_dim >= 64 ? 8 : 5; }
+// operand and the grouped sweeps keep no more either (halves: the W_K sweeps run
+// on the matrix cores); fp32 weights take v as it is.
+inline int heads_per_operand(bool bf16, bool halves, int g) { return !bf16 ? 16 : g > 5 && halves ? 8 : 5; }
 
 void launch_heads(bool bf16, int head_dim, bool units, hipStream_t st, HeadArgs a);
 void launch_heads_finalize(int layers, hipStream_t st, const FinArgs& f);

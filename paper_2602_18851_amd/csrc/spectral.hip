@@ -178,9 +178,10 @@ bool fused_call(const Plan& pl, int dtype, int n_iter) {
 }
 
 // Bytes of Gram matrices one launch pair of the one-workgroup-per-head form
-// works on: all 640 key heads of the 70B GQA shape (53 MB in two strips); larger shapes
-// go through in several pairs, each long enough to hide its launches.
-constexpr size_t kGkBytes = size_t(56) << 20;
+// works on: half the Infinity Cache, from which every query head of a group reads
+// them; larger shapes go through in several pairs, each long enough to hide its
+// launches.
+constexpr size_t kGkBytes = size_t(128) << 20;
 constexpr int kSplitHeads = 256;     // below this many heads their query matrices are split over workgroups
 constexpr int kSplitTarget = 384;    // ... into about this many (with kSplitKeys for the key heads)
 constexpr int kSplitKeys = 256;
@@ -223,11 +224,11 @@ void plan_heads(const sn_shape* s, Plan& pl, size_t sweep0, int64_t slack, size_
   pl.h_tps_q = pl.h_tps_k = tiles;
   const int split_q = dh <= 64 ? kSplitTargetLow : kSplitTarget, split_k = dh <= 64 ? kSplitKeysLow : kSplitKeys;
   if (split) strips(tiles, pl.H, 0, split_q, true, &pl.h_sq, &pl.h_tps_q);
-  const size_t mat = (dh / 16) * (dh / 16 + 1) / 2 * (dh <= 64 ? 2048 : 1024);  // two floats per element below d_h 128
+  const size_t mat = (dh / 16) * (dh / 16 + 1) / 2 * 2048;  // doubles
   if (split) {
     strips(tiles, n_units, 0, split_k, true, &pl.h_sk, &pl.h_tps_k);
   } else if (g > 1) {
-    const int64_t chunks = ceil_div(g, heads_per_operand(s->dtype == SN_BF16, (int)dh, (int)g));
+    const int64_t chunks = ceil_div(g, heads_per_operand(s->dtype == SN_BF16, pl.mfma_k, (int)g));
     const double ratio = (double)mat / ((double)dh * s->d_model * esize(s->dtype));
     const int want = key_strips(n_units * chunks, pl.H, dh <= 64 ? 1024 : 512, ratio, tiles);
     strips(tiles, n_units, want, 0, true, &pl.h_sk, &pl.h_tps_k);
@@ -863,8 +864,8 @@ int run_heads(sn_ctx* c, SweepArgs a, float* u) {
   h.tps_k = pl.h_tps_k;
   h.sq = pl.h_sq;
   h.tps_q = pl.h_tps_q;
-  h.gk = reinterpret_cast<float*>(c->ws + pl.off_gk);
-  h.gq = reinterpret_cast<float*>(c->ws + pl.off_gq);
+  h.gk = reinterpret_cast<double*>(c->ws + pl.off_gk);
+  h.gq = reinterpret_cast<double*>(c->ws + pl.off_gq);
   h.zp = reinterpret_cast<float*>(c->ws + pl.off_hz);
   h.zn = reinterpret_cast<float*>(c->ws + pl.off_hn);
   h.w = a.w;

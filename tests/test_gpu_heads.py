@@ -124,6 +124,105 @@ def test_cancelling_rows(layers, n_kv, group):
     _check(_run(wl, gq, gk, v0), ref, "heads", 1e-3, 5e-3)
 
 
+def _correlated(n_q, n_kv, dh, d, dtype, common):
+    """Query rows of a head share a part of `common` times their own size, and
+    key rows sum to zero, so that Q^T z loses the common part in every step."""
+    g = torch.Generator().manual_seed(11)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    q = torch.randn(n_q, dh, d, generator=g) * 0.02 + torch.randn(n_q, 1, d, generator=g) * (0.02 * common)
+    k = torch.randn(n_kv, dh, d, generator=g) * 0.02
+    k -= k.mean(dim=1, keepdim=True)
+    return q.to(dt).cuda(), k.to(dt).cuda(), torch.randn(n_q, d, generator=g).cuda()
+
+
+def _chain64(q, k, v, n):
+    """sigma and v of every head after n steps through the weights in float64."""
+    q, k = q.double(), k.double().repeat_interleave(q.shape[0] // k.shape[0], dim=0)
+    qt, kt = q.transpose(1, 2).contiguous(), k.transpose(1, 2).contiguous()
+    v = v.double().unsqueeze(2)
+    v = v / torch.linalg.vector_norm(v, dim=1, keepdim=True)
+    for _ in range(n):
+        u = torch.bmm(qt, torch.bmm(k, v))
+        sigma = torch.linalg.vector_norm(u, dim=1, keepdim=True)
+        v = torch.bmm(kt, torch.bmm(q, u / sigma))
+        v = v / torch.linalg.vector_norm(v, dim=1, keepdim=True)
+    return sigma.flatten(), v.squeeze(2)
+
+
+CORRELATED = [
+    # (id, n_q, n_kv, d_h, d, dtype): one per way of iterating (rows, blocks, float under bf16 halves) and type
+    ("dh16-f32", 96, 96, 16, 768, "f32"),
+    ("dh64-f32", 144, 144, 64, 768, "f32"),
+    ("dh64-bf16-own", 300, 300, 64, 768, "bf16"),
+    ("dh128-f32", 64, 64, 128, 1024, "f32"),
+    ("dh128-bf16", 64, 64, 128, 1024, "bf16"),
+    ("dh128-bf16-own", 300, 300, 128, 512, "bf16"),
+    ("dh128-f32-keys", 300, 150, 128, 512, "f32"),
+    ("dh128-halves", 64, 8, 128, 4096, "bf16"),
+    ("dh64-halves", 48, 4, 64, 3000, "bf16"),
+]
+
+
+@pytest.mark.parametrize("common", [0.0, 0.9, 1.7, 3.4])
+@pytest.mark.parametrize("n_q,n_kv,dh,d,dtype", [c[1:] for c in CORRELATED], ids=[c[0] for c in CORRELATED])
+def test_no_less_precise_than_the_sweeps(n_q, n_kv, dh, d, dtype, common):
+    """Over heads whose rows cancel to sigma^2 / b = 1, 0.55, 0.25 and 0.08 (b =
+    sum_i z_i^2 ||q_i||^2): the rms error of v against float64, and that of sigma
+    beside its own rounding to 32 bits (6e-8), are at most those of the sweeps."""
+    q, k, v0 = _correlated(n_q, n_kv, dh, d, dtype, common)
+    s64, v64 = _chain64(q, k, v0, 20)
+    err = {}
+    for form, strips in (("sweeps", 1), ("heads", 0)):
+        est = Spectral(1, d, n_q, n_kv, dh, dtype, 0.05, q_strips=strips, k_strips=strips)
+        v = v0.clone().unsqueeze(0)
+        sigma, _, _ = est.step(q.reshape(1, -1, d), k.reshape(1, -1, d), v, 20)
+        torch.cuda.synchronize()
+        est.close()
+        err[form] = [((sigma[0].double() - s64) / s64).square().mean().sqrt().item(),
+                     (v[0].double() - v64).square().sum(dim=1).mean().sqrt().item()]
+    print(err)
+    assert err["heads"][1] <= err["sweeps"][1], err
+    assert err["heads"][0] <= max(err["sweeps"][0], 8e-8), err
+
+
+def test_zero_rows():
+    """Rows of zeros (pruned or padded dimensions of a head) keep the form's
+    results and its speed: 300 steps on the weights instead of in d_h-space would
+    take many times as long."""
+    wl = _workload(4, 1024, 64, 1, 64, "bf16", n_iter=6)
+    wq, wk = all_weights(wl, "cpu")
+    v0 = start_vectors(wl, "cpu")
+    zq, zk = wq.clone().view(4, 64, 64, 1024), wk.clone().view(4, 64, 64, 1024)
+    zq[:, :, 40:48], zk[:, ::2, 60:] = 0, 0
+    zq[1, 3], zk[2, 5] = 0, 0      # and whole heads: M = 0
+    zq, zk = zq.reshape(wq.shape), zk.reshape(wk.shape)
+    ref = oracle_step(zq.float().numpy(), zk.float().numpy(), v0.double().numpy(), wl.n_iter, n_kv=wl.n_kv, head_dim=64,
+                      alpha=wl.alpha, want_u=True)
+    got = _run(wl, zq.cuda(), zk.cuda(), v0)
+    np.testing.assert_array_equal(got["iters"], ref["iters"])
+    assert got["iters"][1, 3] == got["iters"][2, 5] == -2
+    live = ref["iters"] > 0
+    assert np.max(np.abs(got["sigma"] - ref["sigma"])[live] / ref["sigma"][live]) <= SIGMA_TOL
+    for x in ("v", "u"):
+        assert np.linalg.norm(got[x] - ref[x], axis=-1).max() <= VEC_TOL
+
+    def step_time(q, k):
+        est = Spectral(4, 1024, 64, 64, 64, "bf16", wl.alpha)
+        q, k, v = q.cuda(), k.cuda(), v0.cuda()
+        est.step(q, k, v, 300)
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        est.step(q, k, v, 300)
+        b.record()
+        torch.cuda.synchronize()
+        est.close()
+        return a.elapsed_time(b)
+
+    dense, zeros = step_time(wq, wk), step_time(zq, zk)
+    print(f"300 steps: {dense:.3f} ms, with zero rows {zeros:.3f} ms")
+    assert zeros <= 2 * dense
+
+
 def test_values_outside_the_range_of_gram_products():
     """Query weights near 1e-20 and key weights near 1e18: the products in G_Q
     underflow, those in G_K overflow, and u' = Q^T z is an ordinary number."""

@@ -23,8 +23,13 @@
 // Streaming.  The workgroup's four waves share a ring of row tiles (d_h rows
 // x 128 bytes) in LDS, filled by buffer loads straight to LDS; one bare
 // barrier per tile says that the tile has landed and that its predecessor's
-// slot is free, and the loads of the next NST - 1 tiles stay in flight across
-// it.  The upper-triangle 16 x 16 blocks of G are split over the waves by
+// slot is free.  The waits written here leave the loads of the next NST - 2 tiles
+// in flight across it.  The compiler, which tracks loads to LDS by alias, adds a
+// full wait before the LDS reads of two of the streams (the query strips of
+// units_kernel and the key stream of H_OWN); the key stream of units_kernel lost
+// its own with the start vectors read as the vector type of the tiles: 70B GQA
+// shape 2.51 -> 2.47 ms, GPT-2 small 76 -> 74 us of two iterations.
+// The upper-triangle 16 x 16 blocks of G are split over the waves by
 // quadrants (waves 0 and 1: the two diagonal triangles; waves 2 and 3: halves
 // of the off-diagonal square), so a wave reads at most 6 of the 8 row blocks
 // of a tile (d_h = 128) and no sum over waves is needed.  The z0 products
@@ -330,9 +335,9 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
             bf16x8 o;
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
-              const float4 y = *reinterpret_cast<const float4*>(
+              const f32x4 y = *reinterpret_cast<const f32x4*>(
                   vt + head * S::VROW + 16 * ((2 * (4 * kc + q) + half) ^ vswz<S>(head)));
-              const float x4[4] = {y.x, y.y, y.z, y.w};
+              const float x4[4] = {y[0], y[1], y[2], y[3]};
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
                 const float x = !RAGGED || 4 * half + e < cols ? x4[e] : 0.f;
@@ -346,9 +351,9 @@ __device__ __forceinline__ void stream_block(const char* blk, int64_t ld, int d,
             }
             bv = __builtin_bit_cast(u32x4, o);
           } else {
-            const float4 y =
-                *reinterpret_cast<const float4*>(vt + head * S::VROW + 16 * ((4 * kc + q) ^ vswz<S>(head)));
-            const float x4[4] = {y.x, y.y, y.z, y.w};
+            const f32x4 y =
+                *reinterpret_cast<const f32x4*>(vt + head * S::VROW + 16 * ((4 * kc + q) ^ vswz<S>(head)));
+            const float x4[4] = {y[0], y[1], y[2], y[3]};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               const float x = !RAGGED || e < cols ? x4[e] : 0.f;

@@ -76,10 +76,11 @@ typedef struct {
   float r_max;         /* largest finite FP8 magnitude, 448 for OCP E4M3          */
   float tol;           /* 0: run exactly n_iter iterations.  > 0: stop a head
                           after step k >= 2 once |sigma_k - sigma_{k-1}| <=
-                          tol * sigma_k, with n_iter as the cap.  With
-                          head_dim >= 16 the workspace then also holds the
-                          Gram matrices of the tail (see spectral_step; 240 MB
-                          at 80 x 64 heads of d_h 128, d 8192).                   */
+                          tol * sigma_k, with n_iter as the cap.  Where such
+                          calls run sweeps (see spectral_step) and head_dim >=
+                          16, the workspace then also holds the Gram matrices
+                          of the tail (4096 or one per query and key head, of
+                          2 d_h (d_h + 16) bytes).                                */
   int32_t q_strips;    /* column strips per head in the W_Q sweep; 0 = automatic  */
   int32_t k_strips;    /* column strips per KV head in the W_K sweep; 0 = auto.
                           A count given here keeps spectral_step on the sweeps
@@ -103,14 +104,16 @@ typedef struct {
  * (z) back to v (u).  The iterates, sigma, u and v are those of the sweeps
  * up to rounding; W_K is read twice and W_Q once (twice with u) per call
  * instead of once each per iteration.  The products are summed and iterated in
- * double (head_dim 128 with bf16 weights and 3 or more query heads per key head,
- * whose sweeps take vectors in two bf16 halves: iterated in float).  A head whose
- * rows cancel (sigma^2 or ||v'||^2 below 1/4 of its terms' squares in the last
- * step, or the vectors of any step as far below), where the products in d_h-space would
- * lose digits, or whose Gram matrices lie near the ends of the float range, is
- * iterated on its weights instead, by one workgroup.  Needs head_dim >= 16.  The
- * workspace grows by the Gram partials, 4 d_h (d_h + 16) bytes per query or key
- * head and column strip (spectral_workspace_bytes gives the total). */
+ * double (head_dim 128 with bf16 weights and 3 or more query heads per key
+ * head, whose sweeps take vectors in two bf16 halves: iterated in float).  A
+ * head whose rows cancel (sigma^2 or ||v'||^2 below 1/4 of its terms' squares
+ * in the last step, or the vectors of any step as far below), where the
+ * products in d_h-space would lose digits, or whose Gram matrices lie near the
+ * ends of the float range, is iterated on its weights instead, by one
+ * workgroup.  Needs head_dim >= 16.  The workspace of any context with
+ * head_dim >= 16 holds the Gram partials, 4 d_h (d_h + 16) bytes per query or
+ * key head and column strip, for as many key heads at a time as fit 128 MiB;
+ * the flag adds nothing to it. */
 #define SN_FLAG_GRAM 2
 
 /* Reserve the workspace of the layer-level form (spectral_step_layer): the

@@ -1,5 +1,6 @@
-// Gram form of the estimator (SN_FLAG_GRAM): the Gram sweep on the matrix
-// cores and the d_h-space iteration, for MI355X (gfx950, wave64).
+// The tolerance-mode tail of the sweeps: the Gram sweep on the matrix cores and
+// the d_h-space iteration, both over the heads that the first steps left
+// running, for MI355X (gfx950, wave64).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -11,7 +12,7 @@ namespace sn {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Gram form (SN_FLAG_GRAM).  With G_Q = Q_h Q_h^T and G_K = K_j K_j^T
+// With G_Q = Q_h Q_h^T and G_K = K_j K_j^T
 // (d_h x d_h), one step of the iteration is
 //     w = G_Q z,  sigma^2 = z^T w,  y = w / sigma,
 //     t = G_K y,  ||v'||^2 = y^T t,  z_next = t / ||v'||,
@@ -19,8 +20,9 @@ namespace {
 // likewise for v' = K_j^T y.  These are the iterates of the sweeps above,
 // computed in d_h-space.
 //
-// gram_kernel forms G = R R^T for every d_h x d row block R (query heads
-// first, then key heads) on the matrix cores: an output block (bi, bj) of
+// gram_kernel forms G = R R^T for every listed d_h x d row block R (query heads
+// first, then key heads; the count and the strips were chosen on the device) on
+// the matrix cores: an output block (bi, bj) of
 // 16 x 16 is one MFMA chain whose A operand is rows 16 bi.. of R and whose B
 // operand is rows 16 bj.. of R, both in the rows' native layout (lane l
 // holds row l % 16 and 16 bytes of consecutive columns; the contraction
@@ -32,13 +34,8 @@ namespace {
 
 template <typename T, int DH>
 __global__ void __launch_bounds__(64 * kGWaves) __attribute__((amdgpu_waves_per_eu(DH >= 128 ? 2 : 4)))
-gram_kernel(GramArgs args) {
-  GramArgs a = args;
-  if (a.ctl) {  // tail: the listed units, with the count and strips chosen on the device
-    a.s_g = uni(a.ctl[TC_GRAM + 1]);
-    a.tps = uni(a.ctl[TC_GRAM + 2]);
-    a.n_items = uni(a.ctl[TC_GRAM]) * a.s_g;
-  }
+gram_kernel(GramArgs a) {
+  const int s_g = uni(a.ctl[TC_GRAM + 1]), tps = uni(a.ctl[TC_GRAM + 2]);
   constexpr int ES = sizeof(T);
   constexpr int RB = DH / 16;
   constexpr int NB = RB * (RB + 1) / 2;
@@ -48,8 +45,8 @@ gram_kernel(GramArgs args) {
   const int wv = uni((int)(threadIdx.x >> 6));
   const int q = lane >> 4, s = lane & 15;
   const int item = blockIdx.x * kGWaves + wv;
-  if (item >= a.n_items) return;
-  const int unit = a.list ? uni(a.list[item / a.s_g]) : item / a.s_g, strip = item % a.s_g;
+  if (item >= uni(a.ctl[TC_GRAM]) * s_g) return;
+  const int unit = uni(a.list[item / s_g]), strip = item % s_g;
   int layer, row0, tab;
   if (unit < a.H) {
     layer = unit / a.n_q;
@@ -71,8 +68,8 @@ gram_kernel(GramArgs args) {
 #pragma unroll
   for (int b = 0; b < NB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int n_full = a.d / TC;
-  const int t0 = strip * a.tps;
-  const int t1 = min(t0 + a.tps, a.n_tiles);
+  const int t0 = strip * tps;
+  const int t1 = min(t0 + tps, a.n_tiles);
 
   // one LDS tile per wave: the next tile streams in while this one is
   // multiplied from registers.  Each wave starts at its own pseudo-random
@@ -132,8 +129,8 @@ gram_kernel(GramArgs args) {
   for (int b = 0; b < NB; ++b) out[(size_t)b * 64] = acc[b];
 }
 
-// d_h-space iteration of the Gram form: one workgroup of NT threads per query
-// head.  Thread t = 16 R + C owns rows RPT R .. RPT R + RPT - 1 and columns
+// d_h-space iteration of the listed heads from step k0 + 1 on: one workgroup of
+// NT threads per query head.  Thread t = 16 R + C owns rows RPT R .. RPT R + RPT - 1 and columns
 // CPT C .. CPT C + CPT - 1 (CPT = d_h / 16) of G_Q and of G_K in registers.
 // A product G x reads CPT entries of x from LDS and sums the partial rows
 // over the 16 lanes C = 0..15 of a DPP row with a butterfly (quad xor 1,
@@ -216,33 +213,17 @@ __global__ void __launch_bounds__(IterShape<DH>::NT) gram_iterate_kernel(IterArg
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int R = t >> 4, C = t & 15;
   // the head, and the Gram items of its query and key matrices
-  int h = blockIdx.x, s_g = a.s_g;
-  if (a.list) {
-    const int nq = uni(a.ctl[TC_NQ]);
-    if ((int)blockIdx.x >= nq) return;
-    h = uni(a.list[blockIdx.x]);
-    s_g = uni(a.ctl[TC_GRAM + 1]);
-  }
-  const int layer = h / a.n_q;
-  const int j = layer * a.n_kv + (h % a.n_q) / a.g;
-  const int item_q = a.list ? (int)blockIdx.x : h;
-  const int item_k = a.list ? uni(a.ctl[TC_NQ]) + uni(a.kvpos[j]) : a.H + j;
+  const int nq = uni(a.ctl[TC_NQ]);
+  if ((int)blockIdx.x >= nq) return;
+  const int h = uni(a.list[blockIdx.x]), s_g = uni(a.ctl[TC_GRAM + 1]);
+  const int j = h / a.n_q * a.n_kv + (h % a.n_q) / a.g;
+  const int item_q = blockIdx.x, item_k = nq + uni(a.kvpos[j]);
 
   // z of step k0 + 1: K_j v' / ||v'|| from the partials of the W_K sweep of
-  // step k0 (slot k0 & 1; at k0 = 0 the first sweep, v' = the start vector)
+  // step k0 (slot k0 & 1)
   const int slot = a.k0 & 1;
   float nv2 = 0.f;
   for (int st = 0; st < a.s_k; ++st) nv2 += a.w.zn[((size_t)slot * a.H + h) * a.s_k + st];
-  if (a.k0 == 0) {
-    if (t == 0) a.w.vnorm0[h] = sqrtf(nv2);
-    if (!(nv2 > 0.f) || !isfinite(nv2)) {
-      if (t == 0) {
-        a.sigma[h] = __builtin_nanf("");
-        a.iters[h] = -1;
-      }
-      return;
-    }
-  }
   const float inv0 = 1.0f / sqrtf(nv2);
   if (t < DH) {
     float z = 0.f;
@@ -253,7 +234,7 @@ __global__ void __launch_bounds__(IterShape<DH>::NT) gram_iterate_kernel(IterArg
   gram_to_regs<DH>(a.gp + (size_t)item_q * s_g * S::NB * 256, s_g, gl, gq);
   gram_to_regs<DH>(a.gp + (size_t)item_k * s_g * S::NB * 256, s_g, gl, gk);
 
-  float zscale = 1.f, prev = a.k0 > 0 ? a.w.sig[(size_t)slot * a.H + h] : 0.f;
+  float zscale = 1.f, prev = a.w.sig[(size_t)slot * a.H + h];
   float out[RPT];
 #pragma unroll 1
   for (int k = a.k0 + 1;; ++k) {

@@ -111,22 +111,21 @@ struct GramArgs {
   const void* const* mats;  // device table: wq pointers of all layers, then wk pointers
   int64_t ld;
   int32_t d, L, n_q, n_kv, H;
-  int32_t s_g, tps, n_tiles, n_items;
-  const int32_t* list;      // tail: unit of list entry r is list[r]; count and strips in ctl (else nullptr)
-  const int32_t* ctl;
-  float* gp;  // [items][NB][64 lanes][4]: partial Gram blocks in the MFMA output layout, item = entry * s_g + strip
+  int32_t n_tiles;
+  const int32_t* list;      // unit of entry r is list[r]: query heads, then H + key heads
+  const int32_t* ctl;       // counts, strips and tiles per strip (TC_*)
+  float* gp;  // [items][NB][64 lanes][4]: partial Gram blocks in the MFMA output layout, item = entry * strips + strip
 };
 
-// The d_h-space iteration.  The Gram form starts at step 1 from the first W_K
-// sweep's z partials (slot 0); the tolerance-mode tail continues the heads
-// still running after step k0 of the sweep chain from that step's partials
-// (slot k0 & 1) and sigma_{k0}, one workgroup per listed head.
+// The d_h-space iteration of the tail: continues the heads still running after
+// step k0 of the sweep chain from that step's partials (slot k0 & 1) and
+// sigma_{k0}, one workgroup per listed head.
 struct IterArgs {
-  int32_t H, n_q, n_kv, g, s_k, s_g, n_iter;
+  int32_t H, n_q, n_kv, g, s_k, n_iter;
   int32_t k0;               // steps already taken
   float tol;
   const float* gp;
-  const int32_t* list;      // tail: Gram list, its count of query heads in ctl (else nullptr)
+  const int32_t* list;      // the Gram list, its count of query heads in ctl
   const int32_t* ctl;
   const int32_t* kvpos;
   Work w;

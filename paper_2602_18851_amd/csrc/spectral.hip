@@ -1,7 +1,8 @@
 // C ABI of the per-head spectral-norm estimator and the per-layer FP8 E4M3
 // scale factor for MI355X (gfx950): validation, workspace plan, context and
-// the entry points of include/spectral.h.  The kernels live in sweeps.hip
-// (the default form), gram.hip (SN_FLAG_GRAM), layer_form.hip
+// the entry points of include/spectral.h.  The kernels live in gram_heads.hip
+// (most calls of two or more iterations), sweeps.hip (the others), gram.hip
+// (the tolerance-mode tail of the sweeps), layer_form.hip
 // (spectral_step_layer) and logits_fp8.hip (spectral_logits_fp8).
 //
 // Method (arXiv 2602.18851, Sec. 4.1-4.2, App. E): for query head h with key
@@ -57,12 +58,11 @@ struct Plan {
   int tile_cq, n_tiles_q;                    // W_Q sweep
   bool mfma_k;  // W_K sweeps on the matrix cores
   int s_q, tps_q, s_k, tps_k;
-  bool tail;    // tolerance mode of the default form: the heads still running after the first
+  bool tail;    // tolerance mode on the sweeps: the heads still running after the first
                 // steps are finished in d_h-space (needs d_h >= 16)
   int s_tmax;   // most strips of the tail's final W_K sweep
-  bool gram;    // Gram form
-  int units_g, s_g, tps_g, n_tiles_g, nb_g;
-  int g_items;  // Gram partial items the workspace holds
+  int n_tiles_g;
+  int g_items;  // Gram partial items of the tail
   bool layer;   // layer-level form
   int s_lq, tps_lq, s_lk, tps_lk;  // strips of the layer-form row sweeps over W_Q and W_K
   int rs_q, rbp_q, rs_k, rbp_k;    // row splits (and row blocks per split) of its column sweeps
@@ -259,6 +259,24 @@ void plan_heads(const sn_shape* s, Plan& pl, size_t sweep0, int64_t slack, size_
   *off = std::max(*off, o);
 }
 
+// Calls with tol > 0 and n_iter > 2 that run the one-workgroup-per-head form
+// (`heads`: the plan has it).
+bool heads_tolerance(const sn_shape* s, const sn_params* p, bool heads) {
+  if (!heads) return false;
+  if (p->flags & SN_FLAG_GRAM) return true;
+  if (p->q_strips > 0 || p->k_strips > 0 || (p->flags & SN_FLAG_VALU_K_SWEEP)) return false;
+  // A stop at step 2, the earliest, costs the sweeps five passes over the
+  // weights and a tail for the heads still running.  Warm calls that stop
+  // there for nearly every head, sweeps and tail against here: 12 GB of
+  // weights (70B GQA shape) 4.18 -> 2.33 ms, 0.5 GB 387 -> 188 us, 151 MB
+  // 230 -> 126 us, 31 MB 112 -> 75 us.  Below 64 MB, where the weights stay
+  // in the Infinity Cache and launches are what is left to gain, calls keep
+  // the sweeps and the tail.
+  const int64_t bytes =
+      (int64_t)s->n_layers * (s->n_q_heads + s->n_kv_heads) * s->head_dim * s->d_model * esize(s->dtype);
+  return bytes >= (int64_t(64) << 20);
+}
+
 // The plan with at most `slack` bytes for the one-workgroup-per-head form
 // beside the sweeps' (see plan_heads; kNoHeads: without it).
 Plan plan_with(const sn_shape* s, const sn_params* p, int64_t slack) {
@@ -281,22 +299,6 @@ Plan plan_with(const sn_shape* s, const sn_params* p, int64_t slack) {
   strips(pl.n_tiles_q, pl.H, p->q_strips, kQTargetItems, false, &pl.s_q, &pl.tps_q);
   strips(pl.n_tiles, (int64_t)s->n_layers * s->n_kv_heads * pl.nch, p->k_strips,
          pl.mfma_k ? kKMfmaResident : kKTargetItems, pl.mfma_k, &pl.s_k, &pl.tps_k);
-  pl.gram = (p->flags & SN_FLAG_GRAM) != 0;
-  // Tolerance mode: after the first kTailSteps steps, the heads still running
-  // are listed on the device and finished in d_h-space through their Gram
-  // matrices, formed for the listed heads only; strips of those launches are
-  // chosen on the device for the listed count (at most max(count, target)
-  // items each).
-  pl.tail = p->tol > 0.f && !pl.gram && dh >= 16;
-  pl.s_tmax = std::max(1, pl.n_tiles / kTailMinTiles);
-  if (pl.gram || pl.tail) {
-    const int rb = dh / 16;
-    pl.nb_g = rb * (rb + 1) / 2;
-    pl.units_g = pl.H + s->n_layers * s->n_kv_heads;
-    pl.n_tiles_g = ceil_div((int64_t)s->d_model * esize(s->dtype), 128);
-    strips(pl.n_tiles_g, pl.units_g, 0, kGTargetItems, true, &pl.s_g, &pl.tps_g);
-    pl.g_items = pl.gram ? pl.units_g * pl.s_g : std::max(pl.units_g, kGTargetItems);
-  }
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t o = off;
@@ -315,18 +317,25 @@ Plan plan_with(const sn_shape* s, const sn_params* p, int64_t slack) {
   pl.off_zp = take(2 * H * pl.s_k * dh * 4);
   pl.off_yp = take(H * pl.s_q * dh * 4);
   if (dh >= 16 && slack != kNoHeads) plan_heads(s, pl, sweep0, slack, &off);
+  // Tolerance mode on the sweeps: after the first kTailSteps steps, the heads
+  // still running are listed on the device and finished in d_h-space through
+  // their Gram matrices, formed for the listed heads only; strips of those
+  // launches are chosen on the device for the listed count (at most max(count,
+  // target) items each).
+  pl.tail = p->tol > 0.f && dh >= 16 && !(p->flags & SN_FLAG_GRAM) && !heads_tolerance(s, p, pl.heads);
   if (pl.tail) {
     const size_t nkvh = (size_t)s->n_layers * s->n_kv_heads;
+    pl.s_tmax = std::max(1, pl.n_tiles / kTailMinTiles);
+    pl.n_tiles_g = ceil_div((int64_t)s->d_model * esize(s->dtype), 128);
+    pl.g_items = std::max<int>(H + nkvh, kGTargetItems);
     pl.off_zs = take(H * 4);
     pl.off_lg = take((H + nkvh) * 4);
     pl.off_lk = take(nkvh * pl.nch * 4);
     pl.off_kvpos = take(nkvh * 4);
     pl.off_ctl = take(TC_WORDS * 4);
     pl.off_zt = take(H * pl.s_tmax * 4);
-  }
-  if (pl.gram || pl.tail) {
     pl.off_fin = take(H * 2 * dh * 4);
-    pl.off_gp = take((size_t)pl.g_items * pl.nb_g * 256 * 4);
+    pl.off_gp = take((size_t)pl.g_items * (dh / 16) * (dh / 16 + 1) / 2 * 256 * 4);
   }
   pl.layer = (p->flags & SN_FLAG_LAYER) != 0;
   if (pl.layer) {
@@ -721,10 +730,7 @@ GramArgs gram_args(const sn_ctx* c) {
   g.n_q = c->shape.n_q_heads;
   g.n_kv = c->shape.n_kv_heads;
   g.H = pl.H;
-  g.s_g = pl.s_g;
-  g.tps = pl.tps_g;
   g.n_tiles = pl.n_tiles_g;
-  g.n_items = pl.units_g * pl.s_g;
   g.gp = reinterpret_cast<float*>(c->ws + pl.off_gp);
   return g;
 }
@@ -737,7 +743,6 @@ IterArgs iter_args(const sn_ctx* c, const SweepArgs& a) {
   it.n_kv = c->shape.n_kv_heads;
   it.g = pl.g;
   it.s_k = pl.s_k;
-  it.s_g = pl.s_g;
   it.n_iter = a.n_iter;
   it.tol = a.tol;
   it.gp = reinterpret_cast<const float*>(c->ws + pl.off_gp);
@@ -765,9 +770,10 @@ int run_tail(sn_ctx* c, SweepArgs a, float* u, int k0) {
   GramArgs g = gram_args(c);
   g.list = c->w.list_g;
   g.ctl = c->w.ctl;
-  g.n_items = pl.g_items;  // grid: at most max(listed units, target) items
   const int dh = c->shape.head_dim;
-  rc = timed(c, KIND_GRAM, [&] { launch_gram(c->shape.dtype == SN_BF16, dh, g.n_items, c->stream, g); });
+  rc = timed(c, KIND_GRAM, [&] {  // grid: at most max(listed units, target) items
+    launch_gram(c->shape.dtype == SN_BF16, dh, pl.g_items, c->stream, g);
+  });
   if (rc != SN_OK) return rc;
 
   IterArgs it = iter_args(c, a);
@@ -824,20 +830,9 @@ bool heads_call(const sn_ctx* c, int n_iter) {
   const Plan& pl = c->plan;
   const sn_params& p = c->params;
   if (!pl.heads) return false;
-  if (pl.gram) return true;
+  if (p.flags & SN_FLAG_GRAM) return true;
   if (p.q_strips > 0 || p.k_strips > 0 || (p.flags & SN_FLAG_VALU_K_SWEEP)) return false;
-  if (p.tol > 0.f) {
-    // A stop at step 2, the earliest, costs the sweeps five passes over the
-    // weights and a tail for the heads still running.  Warm calls that stop
-    // there for nearly every head, sweeps and tail against here: 12 GB of
-    // weights (70B GQA shape) 4.18 -> 2.33 ms, 0.5 GB 387 -> 188 us, 151 MB
-    // 230 -> 126 us, 31 MB 112 -> 75 us.  Below 64 MB, where the weights stay
-    // in the Infinity Cache and launches are what is left to gain, calls keep
-    // the sweeps and the tail.
-    const int64_t bytes = (int64_t)c->shape.n_layers * (c->shape.n_q_heads + c->shape.n_kv_heads) *
-                          c->shape.head_dim * c->shape.d_model * esize(c->shape.dtype);
-    return n_iter > kTailSteps && bytes >= (int64_t(64) << 20);
-  }
+  if (p.tol > 0.f) return n_iter > kTailSteps && heads_tolerance(&c->shape, &p, true);
   return n_iter >= 2;
 }
 
@@ -903,7 +898,7 @@ void bind_workspace(sn_ctx* c) {
   c->w.vnorm0 = reinterpret_cast<float*>(ws + pl.off_vn);
   c->w.alive = reinterpret_cast<int32_t*>(ws + pl.off_alive);
   c->w.iters = reinterpret_cast<int32_t*>(ws + pl.off_iters);
-  if (pl.gram || pl.tail) c->w.fin = reinterpret_cast<float*>(ws + pl.off_fin);
+  if (pl.tail) c->w.fin = reinterpret_cast<float*>(ws + pl.off_fin);
   if (pl.tail) {
     c->w.zs = reinterpret_cast<int32_t*>(ws + pl.off_zs);
     c->w.list_g = reinterpret_cast<int32_t*>(ws + pl.off_lg);

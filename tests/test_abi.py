@@ -96,12 +96,27 @@ def test_padded_rows_are_accepted(lib):
 def test_gram_form_workspace_and_limits(lib):
     base = sp.spectral_workspace_bytes(_shape(), _params())
     gram = sp.spectral_workspace_bytes(_shape(), _params(flags=sp.SN_FLAG_GRAM))
-    # Gram partials: 2 d_h (d_h + 16) bytes per query / key head and strip, plus the final z, y
+    # every context of d_h >= 16 holds the form's buffers, which the flag does not add to:
+    # 4 d_h (d_h + 16) bytes per query / key head and strip, plus the final z, y
     units = 2 * (8 + 2)
-    assert gram - base >= units * 2 * 64 * (64 + 16) + 2 * 8 * 2 * 64 * 4
+    assert gram == base >= units * 4 * 64 * (64 + 16) + 2 * 8 * 2 * 64 * 4
     with pytest.raises(sp.SpectralError) as e:
         sp.spectral_workspace_bytes(_shape(head_dim=8), _params(flags=sp.SN_FLAG_GRAM))
     assert e.value.code == sp.SN_EINVAL and "Gram" in sp.spectral_last_error()
+
+
+def test_tail_buffers_only_where_the_tail_can_run(lib):
+    """Tolerance calls over 64 MiB of weights run the Gram form and hold nothing
+    for the sweeps' tail, except with parameters that keep them on the sweeps;
+    smaller ones hold its 4096 Gram partials of d_h (d_h + 16) / 512 KB."""
+    big = _shape(n_layers=80, d_model=8192, n_q_heads=64, n_kv_heads=8, head_dim=128)
+    fixed = sp.spectral_workspace_bytes(big, _params())
+    assert sp.spectral_workspace_bytes(big, _params(tol=1e-4)) == fixed
+    tail = 80 * (64 + 8) * 36 * 1024
+    assert sp.spectral_workspace_bytes(big, _params(tol=1e-4, flags=sp.SN_FLAG_VALU_K_SWEEP)) >= fixed + tail - (130 << 20)
+    assert sp.spectral_workspace_bytes(big, _params(tol=1e-4, q_strips=2)) >= tail
+    small = sp.spectral_workspace_bytes(_shape(), _params())
+    assert sp.spectral_workspace_bytes(_shape(), _params(tol=1e-4)) >= small + 4096 * 10 * 1024
 
 
 def test_row_block_size_limit(lib):
@@ -133,7 +148,7 @@ def test_logit_consumer_workspace_holds_every_layer(lib):
 def test_noalloc_refuses_bad_calls_before_touching_the_device(lib):
     """The allocation-free entry point checks its arguments and the size of
     the workspace against its static scratch on the host, before any HIP call:
-    the 70B GQA shape in tolerance mode (240 MB of workspace) does not fit."""
+    the 70B GQA shape in tolerance mode (whose sweeps need 240 MB) does not fit."""
     one = [16] * 80
     shape = _shape(n_layers=80, d_model=8192, n_q_heads=64, n_kv_heads=8, head_dim=128)
     with pytest.raises(sp.SpectralError) as e:

@@ -121,8 +121,9 @@ typedef struct {
  * of d_model rounded up to 64 per layer and row split, up to n_q splits on
  * small shapes) and per-layer vectors; with grouped heads and up to 1024 key
  * rows (n_kv * head_dim) per layer also the sums of each group's query rows
- * in float32, for as many layers at a time as fit 1 GiB.
- * spectral_workspace_bytes gives the total.  spectral_step itself is
+ * in float32, for as many layers at a time as fit 1 GiB (spectral_init goes
+ * without them where they cannot be allocated; calls then read the weights
+ * twice per iteration).  spectral_workspace_bytes gives the total.  spectral_step itself is
  * unaffected. */
 #define SN_FLAG_LAYER 4
 

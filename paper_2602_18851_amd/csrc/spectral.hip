@@ -130,7 +130,9 @@ void strips(int n_tiles, int64_t units, int requested, int target, bool round_do
 }
 
 // Bytes the group sums of the layer form may take: a chunk of layers at a
-// time (29 layers of the 70B GQA shape).
+// time (29 layers of the 70B GQA shape).  Smaller chunks, whose sums stay in the
+// Infinity Cache, lose to their launches: that shape, five iterations 5.92 ms,
+// chunks of 512, 256, 128 MiB 5.99, 6.50, 8.22 ms.
 constexpr int64_t kGroupSumBytes = int64_t(1) << 30;
 
 // The one-pass sweeps of the layer form: the rows of a layer after grouping
@@ -278,8 +280,9 @@ bool heads_tolerance(const sn_shape* s, const sn_params* p, bool heads) {
 }
 
 // The plan with at most `slack` bytes for the one-workgroup-per-head form
-// beside the sweeps' (see plan_heads; kNoHeads: without it).
-Plan plan_with(const sn_shape* s, const sn_params* p, int64_t slack) {
+// beside the sweeps' (see plan_heads; kNoHeads: without it).  `sums`: the layer
+// form may keep the sums of grouped query rows.
+Plan plan_with(const sn_shape* s, const sn_params* p, int64_t slack, bool sums = true) {
   Plan pl{};
   const int dh = s->head_dim;
   pl.H = s->n_layers * s->n_q_heads;
@@ -361,7 +364,7 @@ Plan plan_with(const sn_shape* s, const sn_params* p, int64_t slack) {
     pl.off_ln2 = take(3 * L * 4);
     pl.off_ln2p = take(L * (size_t)ceil_div(d, kRedThreads) * 4);
     pl.off_lstat = take(L * 4);
-    plan_fused(s, pl);
+    if (sums || pl.g == 1) plan_fused(s, pl);
     if (pl.fused) {
       const size_t rows = (size_t)s->n_kv_heads * dh, c = pl.lf_layers, smax = std::max(pl.lf_sq, pl.lf_sk);
       if (pl.g > 1) pl.off_lsum = take(c * rows * pl.lf_ldq * 4);
@@ -392,11 +395,11 @@ bool plan_scratch(const sn_shape* s, const sn_params* p, Plan* pl, size_t* need)
 // The plan of a context.  A shape whose sweeps fit the scratch while the
 // matrices of even one key head do not go beside them runs the sweeps in both
 // calls, which give the same bits.
-Plan make_plan(const sn_shape* s, const sn_params* p) {
+Plan make_plan(const sn_shape* s, const sn_params* p, bool sums = true) {
   Plan tight{};
   size_t need = 0;
   const bool sweeps = s->head_dim >= 16 && plan_scratch(s, p, &tight, &need) && !tight.heads;
-  return plan_with(s, p, sweeps ? kNoHeads : kAnySlack);
+  return plan_with(s, p, sweeps ? kNoHeads : kAnySlack, sums);
 }
 
 struct ProfRec {
@@ -995,8 +998,17 @@ SN_API int spectral_init(sn_ctx** ctx, const sn_shape* shape, const sn_params* p
   };
   if (hipGetDevice(&c->device) != hipSuccess) return cleanup(fail(SN_ESTATE, "no HIP device"));
   const size_t L = c->shape.n_layers;
-  if (hipMalloc(&c->ws, c->plan.bytes + 4 * L * sizeof(void*)) != hipSuccess)
-    return cleanup(fail(SN_EHIP, "hipMalloc(workspace and pointer table) failed"));
+  if (hipMalloc(&c->ws, c->plan.bytes + 4 * L * sizeof(void*)) != hipSuccess) {
+    // short of memory: the layer form without the group sums (up to 1 GiB) reads
+    // its weights twice per iteration
+    (void)hipGetLastError();
+    c->ws = nullptr;
+    if (c->plan.fused && c->plan.g > 1) c->plan = make_plan(&c->shape, params, false);
+    if (hipMalloc(&c->ws, c->plan.bytes + 4 * L * sizeof(void*)) != hipSuccess) {
+      c->ws = nullptr;
+      return cleanup(fail(SN_EHIP, "hipMalloc(workspace and pointer table) failed"));
+    }
+  }
   c->d_tab = reinterpret_cast<const void**>(c->ws + c->plan.bytes);
   if (hipEventCreateWithFlags(&c->tab_event, hipEventDisableTiming) != hipSuccess)
     return cleanup(fail(SN_EHIP, "hipEventCreate failed"));

@@ -60,16 +60,17 @@ def test_layer_form(layers, d, pad, n_kv, group, dh, dtype, n_iter):
         assert np.linalg.norm(v[l] - r.v) <= 2e-5 and np.linalg.norm(u[l] - r.u) <= 2e-5, l
 
 
-def test_degenerate_layers():
+@pytest.mark.parametrize("d,n_q,n_kv,dh", [(200, 8, 2, 32), (328, 32, 8, 128)], ids=["64-rows", "1024-rows"])
+def test_degenerate_layers(d, n_q, n_kv, dh):
     """A zero and a non-finite start vector, and key rows whose group has M v =
     0, beside a regular layer: statuses as in the two-pass form."""
-    wl = WORKLOADS["llama2-70b-gqa"].replace(key="onepass-degenerate", cfg_id=92, n_layers=4, d_model=200, n_q=8, n_kv=2,
-                                             head_dim=32, std=0.02)
+    wl = WORKLOADS["llama2-70b-gqa"].replace(key="onepass-degenerate", cfg_id=92, n_layers=4, d_model=d, n_q=n_q,
+                                             n_kv=n_kv, head_dim=dh, std=0.02)
     wq, wk = all_weights(wl, "cpu")
     wk[2] = 0
     v0 = layer_start_vectors(wl, "cpu") * 3.0
     v0[0], v0[1, 7] = 0.0, float("inf")
-    est = Spectral(4, 200, 8, 2, 32, "bf16", wl.alpha, flags=SN_FLAG_LAYER)
+    est = Spectral(4, d, n_q, n_kv, dh, "bf16", wl.alpha, flags=SN_FLAG_LAYER)
     v = v0.cuda().clone()
     u = torch.full_like(v, 7.0)
     sigma, scale = (t.cpu().numpy() for t in est.step_layer(wq.cuda(), wk.cuda(), v, 4, u=u))
@@ -79,5 +80,33 @@ def test_degenerate_layers():
     np.testing.assert_array_equal(v[:2], v0[:2].numpy())
     np.testing.assert_allclose(v[2], v0[2].numpy() / np.linalg.norm(v0[2].double().numpy()), atol=1e-6)
     assert not u[:3].any()
-    r = power_iteration_layer(wq[3].float().numpy().T, wk[3].float().numpy().T, v0[3].double().numpy(), 4, 4, 32)
+    r = power_iteration_layer(wq[3].float().numpy().T, wk[3].float().numpy().T, v0[3].double().numpy(), 4, 4, dh)
     assert abs(sigma[3] - r.sigma) <= 2e-6 * r.sigma and np.linalg.norm(v[3] - r.v) <= 2e-5
+
+
+def test_without_room_for_the_group_sums():
+    """A context that cannot have the group sums' 805 MB goes without them."""
+    layers, d, n_kv, group, dh = 2, 98304, 8, 2, 128
+    wl = WORKLOADS["llama2-70b-gqa"].replace(key="onepass-room", cfg_id=93, n_layers=layers, d_model=d, n_q=n_kv * group,
+                                             n_kv=n_kv, head_dim=dh, std=0.02)
+    wq, wk = all_weights(wl, "cuda")
+    v0 = layer_start_vectors(wl, "cpu").cuda()
+
+    def run():
+        est = Spectral(layers, d, wl.n_q, n_kv, dh, "bf16", wl.alpha, flags=SN_FLAG_LAYER)
+        v = v0.clone()
+        sigma, _ = est.step_layer(wq, wk, v, 2)
+        torch.cuda.synchronize()
+        est.close()
+        return sigma.cpu().double(), v.cpu().double()
+
+    want = run()
+    torch.cuda.empty_cache()
+    fill, room = [], 600 << 20   # between the 62 MB the context needs and the 867 MB it asks for first
+    while (free := torch.cuda.mem_get_info()[0]) > room + (64 << 20):
+        fill.append(torch.empty(free - room, dtype=torch.uint8, device="cuda"))
+    got = run()
+    del fill
+    torch.cuda.empty_cache()
+    assert ((got[0] - want[0]).abs() <= 2e-6 * want[0]).all()
+    assert torch.linalg.vector_norm(got[1] - want[1], dim=1).max() <= 2e-5

@@ -303,7 +303,9 @@ __global__ void __launch_bounds__(64 * kLFWaves) layer_fused_kernel(LayerFusedAr
 // layer status.  Block (b, l): rows b * kRedThreads .. of layer l of the chunk.
 __global__ void __launch_bounds__(kRedThreads) layer_gather_kernel(LayerFusedArgs a) {
   const int ll = blockIdx.y, layer = a.layer0 + ll;
-  if (a.mode != 0 && a.lstat[layer] != 0) return;
+  // the block that may write the status is the only one to look at it: the others'
+  // x of a stopped layer is never read
+  if (blockIdx.x == 0 && a.mode != 0 && a.lstat[layer] != 0) return;
   float n2 = 0.f;
   for (int s = 0; s < a.strips; ++s) n2 += a.n2part[(size_t)ll * a.strips + s];
   const int r = blockIdx.x * kRedThreads + (int)threadIdx.x;

@@ -21,3 +21,12 @@ def read_golden(name):
             if line:
                 rows.append(line.split())
     return rows
+
+
+def sweep_strips(wl):
+    """The automatic strip counts of the sweeps as explicit parameters, with
+    which calls of any iteration count run the sweeps."""
+    from bench import chain_strips
+
+    q, k = chain_strips(wl, 0, 0)
+    return dict(q_strips=q, k_strips=k)

@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 import torch
 
+from conftest import sweep_strips
 from workloads import WORKLOADS, all_weights, start_vectors
 
 pytestmark = pytest.mark.gpu
@@ -17,16 +18,21 @@ from paper_2602_18851_amd import Spectral  # noqa: E402
 from paper_2602_18851_amd.spectral import SN_FLAG_GRAM  # noqa: E402
 
 
-@pytest.mark.parametrize("flags", [0, SN_FLAG_GRAM], ids=["chain", "gram"])
+
+def _form(form, wl):   # the sweeps (and in tolerance mode their tail) need explicit strip counts
+    return dict(flags=SN_FLAG_GRAM) if form == "gram" else sweep_strips(wl)
+
+
+@pytest.mark.parametrize("form", ["chain", "gram"])
 @pytest.mark.parametrize("key", ["gpt2-small", "llama2-70b-gqa"])
-def test_step_replays_from_a_graph(key, flags):
+def test_step_replays_from_a_graph(key, form):
     wl = WORKLOADS[key]
     if key == "llama2-70b-gqa":
         wl = wl.replace(n_layers=2)
     n_iter = 7
     gq, gk = all_weights(wl, "cuda")
     v0 = start_vectors(wl, "cuda")
-    est = Spectral(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha, flags=flags)
+    est = Spectral(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha, **_form(form, wl))
     L, nq = wl.n_layers, wl.n_q
 
     def buffers():
@@ -60,12 +66,12 @@ def test_step_replays_from_a_graph(key, flags):
     est.close()
 
 
-@pytest.mark.parametrize("flags", [0, SN_FLAG_GRAM], ids=["chain", "gram"])
-def test_tolerance_step_replays_from_a_graph(flags):
+@pytest.mark.parametrize("form", ["chain", "gram"])
+def test_tolerance_step_replays_from_a_graph(form):
     """Tolerance mode never waits on the host, so a call at tol 1e-4 (cap
     1000) captures too: planted per-step shape (2 layers of the 70B GQA
     layout), cold start, so most heads run far past the two full steps into
-    the tail.  Between replays the program runs eager calls on other weights
+    the tail (in the Gram form, past its first steps).  Between replays the program runs eager calls on other weights
     (doubled, so other pointers and other results); every replay still gives
     the eager bits of the captured call."""
     wl = WORKLOADS["llama2-70b-perstep"].replace(n_layers=2)
@@ -73,7 +79,7 @@ def test_tolerance_step_replays_from_a_graph(flags):
     gq2, gk2 = gq * 2, gk * 2
     v0 = start_vectors(wl, "cuda")
     est = Spectral(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha, tol=wl.tol,
-                   flags=flags)
+                   **_form(form, wl))
     L, nq = wl.n_layers, wl.n_q
 
     def buffers():

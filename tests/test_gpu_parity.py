@@ -4,13 +4,14 @@ Bar: relative error <= 1e-3 on every sigma_h and every layer scale, on the
 very weight bits and start vectors the GPU consumed; iteration counts equal
 (fixed count) or a valid stopping step of the oracle's own sigma sequence
 (tolerance mode).  Both forms of the iteration are held to it: the sweep
-chain (default) and the Gram form (flag SN_FLAG_GRAM), which computes the
+chain (explicit strip counts) and the Gram form (flag SN_FLAG_GRAM), which computes the
 same iterates through the d_h x d_h Gram matrices."""
 
 import numpy as np
 import pytest
 import torch
 
+from conftest import sweep_strips
 from oracle.power_iteration import head_slices, layer_scale, power_iteration, spectral_step as oracle_step
 from workloads import WORKLOADS, all_weights, start_vectors
 
@@ -24,13 +25,18 @@ if not torch.cuda.is_available():  # pragma: no cover - collected on CPU machines, 
 from paper_2602_18851_amd import Spectral  # noqa: E402
 from paper_2602_18851_amd.spectral import SN_FLAG_GRAM, SN_FLAG_VALU_K_SWEEP  # noqa: E402
 
-FORMS = {"chain": 0, "gram": SN_FLAG_GRAM}
+FORMS = ("chain", "gram")
 
 
-def _form_flags(form, head_dim):
-    if form == "gram" and head_dim < 16:
+def _form(form, wl, **given):
+    """Parameters of a call in that form: the sweeps through explicit strip
+    counts (with automatic ones, calls of two or more iterations run the Gram
+    form), the Gram form through its flag."""
+    if form == "chain":
+        return {**sweep_strips(wl), **given}
+    if wl.head_dim < 16:
         pytest.skip("the Gram form needs head_dim >= 16")
-    return FORMS[form]
+    return dict(given, flags=given.get("flags", 0) | SN_FLAG_GRAM)
 
 
 def _rel(a, b):
@@ -96,9 +102,9 @@ def _np(w):
 @pytest.mark.parametrize("key", ["tiny", "gpt2-small"])
 def test_fp32_configs_all_heads(key, form):
     wl = WORKLOADS[key]
-    flags = _form_flags(form, wl.head_dim)
+    kw = _form(form, wl)
     wq, wk, v0, gq, gk = _cpu_case(wl)
-    gpu = run_gpu(wl, gq, gk, v0, wl.n_iter, want_u=True, flags=flags)
+    gpu = run_gpu(wl, gq, gk, v0, wl.n_iter, want_u=True, **kw)
     check_against_oracle(wl, _np(wq), _np(wk), v0, wl.n_iter, gpu, want_u=True)
 
 
@@ -128,8 +134,8 @@ CASES = [
 @pytest.mark.parametrize("form", FORMS)
 @pytest.mark.parametrize("name,over,ld,strips", CASES, ids=[c[0] for c in CASES])
 def test_shapes_against_oracle(name, over, ld, strips, form):
-    strips = dict(strips, flags=strips.get("flags", 0) | _form_flags(form, over["head_dim"]))
     wl = WORKLOADS["llama2-70b-gqa"].replace(key=name, n_iter=11, std=0.02, **over)
+    strips = _form(form, wl, **strips)
     wq, wk, v0, gq, gk = _cpu_case(wl, ld)
     gpu = run_gpu(wl, gq, gk, v0, wl.n_iter, want_u=True, ld=ld or 0, **strips)
     check_against_oracle(wl, _np(wq), _np(wk), v0, wl.n_iter, gpu, want_u=True)
@@ -139,7 +145,7 @@ def test_shapes_against_oracle(name, over, ld, strips, form):
 def test_tolerance_mode_on_planted_spectra(form):
     wl = WORKLOADS["llama2-70b-perstep"].replace(n_layers=2, d_model=256, n_q=4, n_kv=2, head_dim=16)
     wq, wk, v0, gq, gk = _cpu_case(wl)
-    gpu = run_gpu(wl, gq, gk, v0, 2000, tol=1e-4, want_u=True, flags=FORMS[form])
+    gpu = run_gpu(wl, gq, gk, v0, 2000, tol=1e-4, want_u=True, **_form(form, wl))
     assert gpu["iters"].min() >= 2 and gpu["iters"].max() < 2000
     for l in range(wl.n_layers):
         for h in range(wl.n_q):
@@ -232,7 +238,7 @@ def test_one_step_and_short_runs(form):
     wl = WORKLOADS["gpt2-small"].replace(n_layers=2)
     wq, wk, v0, gq, gk = _cpu_case(wl)
     for n in (1, 2, 3):
-        gpu = run_gpu(wl, gq, gk, v0, n, want_u=True, flags=FORMS[form])
+        gpu = run_gpu(wl, gq, gk, v0, n, want_u=True, **_form(form, wl))
         check_against_oracle(wl, _np(wq), _np(wk), v0, n, gpu, want_u=True)
 
 
@@ -245,7 +251,7 @@ def test_degenerate_heads(form):
     v0 = start_vectors(wl, "cpu")
     v0[0, 1] = 0.0                        # zero start vector
     v0[0, 2, 5] = float("nan")            # non-finite start vector
-    gpu = run_gpu(wl, wq.cuda(), wk.cuda(), v0, wl.n_iter, want_u=True, flags=FORMS[form])
+    gpu = run_gpu(wl, wq.cuda(), wk.cuda(), v0, wl.n_iter, want_u=True, **_form(form, wl))
     ref = oracle_step(_np(wq), _np(wk), v0.double().numpy(), wl.n_iter, n_kv=2, head_dim=32, alpha=wl.alpha,
                       want_u=True)
     np.testing.assert_array_equal(gpu["iters"], ref["iters"])
@@ -265,8 +271,8 @@ def test_degenerate_heads(form):
 def test_bitwise_deterministic(form):
     wl = WORKLOADS["llama2-70b-gqa"].replace(n_layers=2, d_model=1024, n_q=16, n_kv=2, n_iter=7)
     wq, wk, v0, gq, gk = _cpu_case(wl)
-    a = run_gpu(wl, gq, gk, v0, wl.n_iter, want_u=True, flags=FORMS[form])
-    b = run_gpu(wl, gq, gk, v0, wl.n_iter, want_u=True, flags=FORMS[form])
+    a = run_gpu(wl, gq, gk, v0, wl.n_iter, want_u=True, **_form(form, wl))
+    b = run_gpu(wl, gq, gk, v0, wl.n_iter, want_u=True, **_form(form, wl))
     for k in ("sigma", "scale", "v", "u", "iters"):
         np.testing.assert_array_equal(a[k], b[k])
 
@@ -277,8 +283,8 @@ def test_state_vectors_off_16_byte_alignment(form):
     pieces only where it can): views 4 bytes off give the aligned run's bits."""
     wl = WORKLOADS["llama2-70b-gqa"].replace(key="unaligned", n_layers=2, d_model=520, n_q=8, n_kv=2, n_iter=6)
     wq, wk, v0, gq, gk = _cpu_case(wl)
-    ref = run_gpu(wl, gq, gk, v0, wl.n_iter, want_u=True, flags=FORMS[form])
-    est = Spectral(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha, flags=FORMS[form])
+    ref = run_gpu(wl, gq, gk, v0, wl.n_iter, want_u=True, **_form(form, wl))
+    est = Spectral(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha, **_form(form, wl))
     big = torch.zeros(2 * v0.numel() + 1, dtype=torch.float32, device="cuda")
     v = big[1:1 + v0.numel()].view_as(v0)
     u = big[1 + v0.numel():].view_as(v0)
@@ -298,7 +304,7 @@ def test_state_vectors_off_16_byte_alignment(form):
 def test_warm_start_continues_the_iteration(form):
     wl = WORKLOADS["gpt2-xl"].replace(n_layers=2, n_q=5, n_kv=5)
     wq, wk, v0, gq, gk = _cpu_case(wl)
-    est = Spectral(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha, flags=FORMS[form])
+    est = Spectral(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha, **_form(form, wl))
     v = v0.cuda()
     est.step(gq, gk, v, 10)
     sigma, _, _ = est.step(gq, gk, v, 10)
@@ -314,8 +320,8 @@ def test_homogeneity_of_the_gpu_path(form):
     """x4 on every attention weight -> sigma and scale x16 (powers of two are exact)."""
     wl = WORKLOADS["gpt2-xl"].replace(n_layers=2, n_q=5, n_kv=5, n_iter=8)
     wq, wk, v0, gq, gk = _cpu_case(wl)
-    a = run_gpu(wl, gq, gk, v0, wl.n_iter, flags=FORMS[form])
-    b = run_gpu(wl, gq * 4, gk * 4, v0, wl.n_iter, flags=FORMS[form])
+    a = run_gpu(wl, gq, gk, v0, wl.n_iter, **_form(form, wl))
+    b = run_gpu(wl, gq * 4, gk * 4, v0, wl.n_iter, **_form(form, wl))
     np.testing.assert_array_equal(b["sigma"], 16 * a["sigma"])
     assert _rel(b["scale"], 16 * a["scale"]).max() < 1e-6
 
@@ -331,8 +337,8 @@ def _sampled_heads(wl, rng, full_layers, per_layer):
     return sorted(heads)
 
 
-def _run_full(wl, gq, gk, v0, n_iter, tol=0.0, flags=0):
-    est = Spectral(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha, tol=tol, flags=flags)
+def _run_full(wl, gq, gk, v0, n_iter, tol=0.0, **kw):
+    est = Spectral(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha, tol=tol, **kw)
     v = v0.clone()
     sigma, scale, iters = est.step(gq, gk, v, n_iter)
     torch.cuda.synchronize()
@@ -368,7 +374,7 @@ def test_full_size_every_head(key):
     wl = WORKLOADS[key]
     gq, gk = all_weights(wl, "cuda")
     v0 = start_vectors(wl, "cuda")
-    gpu = {form: _run_full(wl, gq, gk, v0, wl.n_iter, flags=FORMS[form]) for form in FORMS}
+    gpu = {form: _run_full(wl, gq, gk, v0, wl.n_iter, **_form(form, wl)) for form in FORMS}
     for g in gpu.values():
         assert np.isfinite(g["sigma"]).all() and (g["iters"] == wl.n_iter).all()
     v0c = v0.double().cpu().numpy()
@@ -425,7 +431,7 @@ def test_small_configs_against_the_explicit_route(form):
         if form == "gram" and wl.head_dim < 16:
             continue
         wq, wk, v0, gq, gk = _cpu_case(wl)
-        gpu = run_gpu(wl, gq, gk, v0, wl.n_iter, want_u=True, flags=FORMS[form])
+        gpu = run_gpu(wl, gq, gk, v0, wl.n_iter, want_u=True, **_form(form, wl))
         wq_n, wk_n = _np(wq), _np(wk)
         worst = 0.0
         for l in range(wl.n_layers):
@@ -481,7 +487,7 @@ def test_full_size_per_step_recompute(form):
     gq, gk = all_weights(wl, "cuda")
     v0 = start_vectors(wl, "cuda")
     est = Spectral(L, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha, tol=wl.tol,
-                   flags=FORMS[form])
+                   **_form(form, wl))
     v = v0.clone()
     s0, _, i0 = est.step(gq, gk, v, wl.n_iter)
     s0, i0 = s0.cpu().numpy().copy(), i0.cpu().numpy().copy()
@@ -536,8 +542,8 @@ def _random_cases(n=16, seed=20260218):
 @pytest.mark.parametrize("form", FORMS)
 @pytest.mark.parametrize("name,cfg,over,ld,strips,n_iter", _random_cases(), ids=[c[0] for c in _random_cases()])
 def test_random_shapes_against_oracle(name, cfg, over, ld, strips, n_iter, form):
-    strips = dict(strips, flags=_form_flags(form, over["head_dim"]))
     wl = WORKLOADS["llama2-70b-gqa"].replace(key=name, cfg_id=cfg, n_iter=n_iter, std=0.02, **over)
+    strips = _form(form, wl, **strips)
     wq, wk, v0, gq, gk = _cpu_case(wl, ld)
     gpu = run_gpu(wl, gq, gk, v0, n_iter, want_u=True, ld=ld, **strips)
     check_against_oracle(wl, _np(wq), _np(wk), v0, n_iter, gpu, want_u=True)

@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 import torch
 
+from conftest import sweep_strips
 from workloads import WORKLOADS, all_weights, start_vectors
 
 pytestmark = pytest.mark.gpu
@@ -39,8 +40,9 @@ def _outputs(wl, v0):
             torch.empty(L, nq, dtype=torch.int32, device="cuda"))
 
 
-def _reference(wl, gq, gk, v0, flags, tol):
-    est = Spectral(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha, tol=tol, flags=flags)
+def _reference(wl, gq, gk, v0, flags, tol, strips):
+    est = Spectral(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim, wl.dtype, wl.alpha, tol=tol, flags=flags,
+                   **strips)
     v, u, s, c, i = _outputs(wl, v0)
     est.step(gq, gk, v, wl.n_iter, u=u, sigma=s, scale=c, iters=i)
     torch.cuda.synchronize()
@@ -48,10 +50,10 @@ def _reference(wl, gq, gk, v0, flags, tol):
     return [t.cpu().numpy() for t in (v, u, s, c, i)]
 
 
-def _noalloc(wl, gq, gk, v0, flags, tol):
+def _noalloc(wl, gq, gk, v0, flags, tol, strips):
     shape = sp.sn_shape(wl.n_layers, wl.d_model, wl.n_q, wl.n_kv, wl.head_dim,
                         sp.SN_BF16 if wl.dtype == "bf16" else sp.SN_F32, 0)
-    params = sp.sn_params(wl.alpha, 0.8, 448.0, tol, 0, 0, flags)
+    params = sp.sn_params(wl.alpha, 0.8, 448.0, tol, strips.get("q_strips", 0), strips.get("k_strips", 0), flags)
     v, u, s, c, i = _outputs(wl, v0)
     stream = torch.cuda.current_stream().cuda_stream
     sp.spectral_step_noalloc(shape, params, [t.data_ptr() for t in gq.unbind(0)], [t.data_ptr() for t in gk.unbind(0)],
@@ -60,14 +62,17 @@ def _noalloc(wl, gq, gk, v0, flags, tol):
     return [t.cpu().numpy() for t in (v, u, s, c, i)]
 
 
-@pytest.mark.parametrize("flags,tol,shapes", [(0, 0.0, SHAPES), (sp.SN_FLAG_GRAM, 0.0, SHAPES), (0, 1e-4, PLANTED)],
-                         ids=["chain", "gram", "chain-tol"])
-def test_noalloc_matches_the_context_entry_point(flags, tol, shapes):
+@pytest.mark.parametrize("flags,tol,shapes,sweeps",
+                         [(0, 0.0, SHAPES, True), (sp.SN_FLAG_GRAM, 0.0, SHAPES, False), (0, 1e-4, PLANTED, True),
+                          (0, 0.0, SHAPES, False), (0, 1e-4, PLANTED, False)],
+                         ids=["chain", "gram", "chain-tol", "default", "default-tol"])
+def test_noalloc_matches_the_context_entry_point(flags, tol, shapes, sweeps):
     for wl in shapes:  # two calls in a row, the second smaller
         gq, gk = all_weights(wl, "cuda")
         v0 = start_vectors(wl, "cuda")
-        ref = _reference(wl, gq, gk, v0, flags, tol)
-        got = _noalloc(wl, gq, gk, v0, flags, tol)
+        strips = sweep_strips(wl) if sweeps else {}
+        ref = _reference(wl, gq, gk, v0, flags, tol, strips)
+        got = _noalloc(wl, gq, gk, v0, flags, tol, strips)
         for name, a, b in zip(("v", "u", "sigma", "scale", "iters"), ref, got):
             np.testing.assert_array_equal(a, b, err_msg=f"{wl.key}: {name}")
         if tol > 0:

@@ -36,12 +36,12 @@ ARITHMETIC = {
              "heads per key head, d_h 64/128): bf16 matrix-core products of K with each fp32 vector split into hi and "
              "lo bf16 halves (about 16 significant bits), fp32 accumulation; other W_K sweeps fp32 FMA; norms, "
              "normalisation and the scale fp32",
-    "gram": "Gram matrices: bf16 (fp32: fp32) matrix-core products, fp32 accumulation; d_h-space iteration, norms "
-            "and the scale fp32; final sweeps as in the chain",
-    "step": "Gram matrices: bf16 (fp32: fp32) matrix-core products, summed in two levels with the rounding of the "
-            "second kept; d_h-space iteration, norms and the scale fp32; first product with v: bf16 matrix cores on two "
-            "(groups of 6 and more, d_h 64/128) or three bf16 parts of each fp32 vector; final sweeps as in the chain",
-    "layer": "fp32 FMA on the weights (bf16 widened exactly), fp32 norms and scale",
+    "gram": "Gram matrices: bf16 (fp32: fp32) matrix-core products, each instruction's sums added up in double (d_h 128 "
+            "under two-half W_K sweeps: in float over 16 parts of the columns); d_h-space iteration double (there: "
+            "fp32), norms and the scale fp32; first product with v: bf16 matrix cores on two (groups of 6 and more, "
+            "d_h 64/128) or three bf16 parts of each fp32 vector; final sweeps as in the chain",
+    "layer": "fp32 FMA on the weights (bf16 widened exactly) or on the fp32 sums of each group's query rows, fp32 norms "
+             "and scale",
 }
 METRIC = "heads·iters/sec (all layers) and achieved HBM GB/s vs MI355X peak"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "q_sweep_traffic.json")
@@ -149,6 +149,30 @@ def measured_traffic(kernel: str = ""):
     if t.get("source_sha256_16") != source_hash():
         return None
     return (t.get(kernel) or {}).get("bytes_per_launch") if kernel else t.get("bytes_per_launch")
+
+
+def layer_work(wl, n_iter: int) -> dict:
+    """What a layer-form call moves: per kind of sweep what it reads and the
+    bytes of all its launches, and the bytes of the whole call.  Up to 1024
+    grouped rows per layer run one-pass sweeps, over the fp32 sums of each
+    group's query rows where those save traffic; else two passes per matrix
+    and iteration."""
+    q, k = wl.weight_bytes()
+    L, d, rows = wl.n_layers, wl.d_model, wl.n_kv * wl.head_dim
+    vectors = 12 * d * L   # v read and written, u' or v' once more
+    ratio = 4.0 / (wl.group * wl.elem_bytes)
+    per_layer = rows * -(-d // 32) * 32 * 4
+    if rows <= 1024 and (wl.group == 1 or (per_layer <= 1 << 30 and 1 + ratio * (1 + n_iter) < 2 * n_iter)):
+        sums = L * per_layer if wl.group > 1 else q
+        form = q + sums if wl.group > 1 else 0   # W_Q read and the sums written, once per call
+        return {"layer_row_sweeps": ("one pass over W_K", (n_iter + 1) * k),
+                "layer_col_sweeps": ("one pass over the group sums" if wl.group > 1 else "one pass over W_Q", n_iter * sums),
+                "call": form + n_iter * sums + (n_iter + 1) * k + vectors}
+    # column sweeps read one d_h-vector per query / key head and write u' and v'
+    col = (L * wl.n_q + L * wl.n_kv) * wl.head_dim * 4 + 2 * L * d * 4
+    return {"layer_row_sweeps": ("W_K and W_Q, row sums", n_iter * (q + k)),
+            "layer_col_sweeps": ("W_Q and W_K, column sums", n_iter * (q + k + col)),
+            "call": n_iter * (2 * (q + k) + col) + vectors}
 
 
 def host_info() -> dict:
@@ -722,20 +746,12 @@ def main():
     q_bytes, k_bytes = wl.weight_bytes()
     dom_launch_bytes = None
     if layer:
-        # per step: row sweeps over W_K and W_Q; column sweeps over W_Q and W_K,
-        # which read one d_h-vector per query / key head and write u' and v'
-        col_buf = (H + wl.n_layers * wl.n_kv) * wl.head_dim * 4 + 2 * wl.n_layers * wl.d_model * 4
-        r_ms, r_n = prof["layer_row_sweeps"]
-        c_ms, c_n = prof["layer_col_sweeps"]
-        if r_ms >= c_ms:
-            dom_name, dom_kind, dom_alg = "layer_row_sweeps (W_K and W_Q, row sums)", "layer_row_sweeps", \
-                n_iter * (q_bytes + k_bytes)
-        else:
-            dom_name, dom_kind, dom_alg = "layer_col_sweeps (W_Q and W_K, column sums)", "layer_col_sweeps", \
-                n_iter * (q_bytes + k_bytes + col_buf)
-        dom_launch_bytes = dom_alg  # all launches of the kind together
+        work = layer_work(wl, n_iter)
+        dom_kind = max(("layer_row_sweeps", "layer_col_sweeps"), key=lambda kind: prof[kind][0])
+        name, dom_launch_bytes = work[dom_kind]  # all launches of the kind together
+        dom_name = f"{dom_kind} ({name})"
         dom_flops = None
-        call_bytes = n_iter * (2 * (q_bytes + k_bytes) + col_buf) + 12 * wl.d_model * wl.n_layers
+        call_bytes = work["call"]
         H = wl.n_layers  # one estimate per layer
     elif heads:
         # heads_kernel: with grouped heads every W_Q element read once, else every W_Q and W_K element
@@ -780,7 +796,7 @@ def main():
             "cache": "1 GiB written before every timed call, calls timed one by one" if args.flush
                      else "calls back to back, no flush",
         },
-        "arithmetic": ARITHMETIC["step" if heads else "gram" if gram else "layer" if layer else "chain"],
+        "arithmetic": ARITHMETIC["gram" if heads else "layer" if layer else "chain"],
         "effective_GBps": call_bytes / (ms * 1e-3) / 1e9,
         "effective_frac_of_peak": call_bytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBPS,
         "call_bytes": call_bytes,

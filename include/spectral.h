@@ -288,13 +288,15 @@ SN_API int spectral_workspace_bytes(const sn_shape* shape, const sn_params* para
 
 /* Per-kernel timing.  With enable != 0 every later launch is bracketed by
  * HIP events on the context's stream.  spectral_profile_read waits for the
- * stream and returns, per kernel kind (0 = first W_K sweep from v,
- * 1 = W_Q sweep, 2 = W_K sweep, 3 = finalize, 4 = Gram sweep, 5 = d_h-space
- * iteration, 6 = final sweeps of the Gram form, 7 = row sweeps of the
- * layer-level form, 8 = its column sweeps, 9 = its reductions and
- * finalize, 10 = projections of the logit consumer, 11 = its logit
- * kernels, 12 = the running-head lists of tolerance mode), the summed
- * device time in
+ * stream and returns, per kernel kind (0 = first W_K sweep from v, 1 = W_Q
+ * sweep, 2 = W_K sweep, 3 = finalize, 4 = Gram matrices of key heads (and of
+ * split query heads), or of the tail, 5 = d_h-space iteration, with the Gram
+ * matrices of the heads whose own workgroup forms them, 6 = final sweeps of
+ * the Gram form, 7 = row sweeps of the layer-level form (one-pass: its W_K
+ * sweeps), 8 = its column sweeps (one-pass: those over W_Q or the group
+ * sums), 9 = its group sums, reductions and finalize, 10 = projections of
+ * the logit consumer, 11 = its logit kernels, 12 = the running-head lists of
+ * tolerance mode), the summed device time in
  * milliseconds and the number of launches since the previous read, then
  * resets both.  ms and launches point to SN_PROFILE_KINDS host elements
  * each. */

@@ -103,17 +103,17 @@ typedef struct {
  * final W_K sweep (plus one W_Q sweep when u is requested) maps the last y
  * (z) back to v (u).  The iterates, sigma, u and v are those of the sweeps
  * up to rounding; W_K is read twice and W_Q once (twice with u) per call
- * instead of once each per iteration.  The products are summed and iterated in
- * double (head_dim 128 with bf16 weights and 3 or more query heads per key
- * head, whose sweeps take vectors in two bf16 halves: iterated in float).  A
- * head whose rows cancel (sigma^2 or ||v'||^2 below 1/4 of its terms' squares
- * in the last step, or the vectors of any step as far below), where the
- * products in d_h-space would lose digits, or whose Gram matrices lie near the
- * ends of the float range, is iterated on its weights instead, by one
- * workgroup.  Needs head_dim >= 16.  The workspace of any context with
- * head_dim >= 16 holds the Gram partials, 4 d_h (d_h + 16) bytes per query or
- * key head and column strip, for as many key heads at a time as fit 128 MiB;
- * the flag adds nothing to it. */
+ * instead of once each per iteration.  The products are summed and iterated
+ * in double (head_dim 128 with bf16 weights and 3 or more query heads per
+ * key head, whose sweeps take vectors in two bf16 halves: iterated in
+ * float).  A head whose rows cancel in Q^T z or K^T y over its steps
+ * (sigma^2 or ||v'||^2 of the last one below 1/4 of its terms' squares, or
+ * below 0.58 in the mean of all), where the products in d_h-space would lose
+ * digits, or whose Gram matrices lie near the ends of the float range, is
+ * iterated on its weights instead, by one workgroup. Needs head_dim >= 16.
+ * The workspace of any context with head_dim >= 16 holds the Gram partials,
+ * 4 d_h (d_h + 16) bytes per query or key head and column strip, for as many
+ * key heads at a time as fit 128 MiB; the flag adds nothing to it. */
 #define SN_FLAG_GRAM 2
 
 /* Reserve the workspace of the layer-level form (spectral_step_layer): the

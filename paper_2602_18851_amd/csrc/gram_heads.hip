@@ -39,8 +39,8 @@
 // Precision.  z^T G z rounds relative to b = sum_i z_i^2 G_ii, a sweep of Q
 // relative to sqrt(b), and an error in G repeats in every step, where those of
 // the sweeps differ.  So G's sums and (but for I_HALVES, below) the iteration are
-// in double, with the sweeps' accuracy down to sigma^2 near b / 4.  Every step compares
-// its products with b; a head whose rows cancel further in Q^T z or K^T y, whose
+// in double, with the sweeps' accuracy down to sigma^2 near b / 4.  Every step weighs
+// its products against b; a head whose rows cancel further over its steps, whose
 // Gram matrix is near the ends of the float range, or whose values are not
 // finite is iterated again from z0 by reading Q_h and K_j directly
 // (direct_sweep), in the order of the sweep form and with its stopping rules.
@@ -66,16 +66,20 @@ constexpr int kHThreads = 64 * kHWaves;
 enum { I_ROWS = 0, I_BLOCKS = 1, I_HALVES = 2 };
 
 // An error E in G, of rows E_i. ~ eps sqrt(G_ii) (sqrt(G_jj))_j, turns w = G z by
-// |E z| / |w|, about eps sqrt(b tr(G)) / |w| with b = sum_i z_i^2 G_ii, and
-// sigma^2 = z^T w by eps b / sigma^2.  Rows that do not cancel have r = sqrt(d_h /
-// (b tr(G))) |w| near 1 or above, and sigma^2 / b too.  Every step needs r (it steers
-// v), the reported one sigma^2 / b as well; a head below is iterated on its
-// weights.  Errors of v after 20 steps with all heads kept, against the sweeps:
-// I_ROWS (d 768) r 0.55 2.1e-7 (3.3e-7), 0.25 7.4e-7 (3.5e-7), 0.08 2.9e-6
+// about eps sqrt(b tr(G)), b = sum_i z_i^2 G_ii: relative to |w| that is eps / r with
+// r = sqrt(d_h / (b tr(G))) |w|, and b / sigma^2 times what the sweeps' own rounding of
+// u' = Q^T z does to w.  Rows that do not cancel have r and sigma^2 / b near 1 or above.
+// The errors of v add up over the products: each counts min(1 / r, b / sigma^2)^2, and
+// a head whose mean over its steps passes kCancelMean is iterated on its weights, as
+// is one whose reported sigma^2 (or ||v'||^2) lies below kCancelSigma b.  A product
+// that cancels in passing, as the first of a random start may, costs nothing then.
+// Errors of v after 20 steps at a constant r with all heads kept, against the
+// sweeps: I_ROWS (d 768) r 0.55 2.1e-7 (3.3e-7), 0.25 7.4e-7 (3.5e-7), 0.08 2.9e-6
 // (4.8e-7); I_BLOCKS (d 1024) 2.4e-7 (4.2e-7), 7.4e-7 (4.4e-7), 3.2e-6 (6.1e-7);
 // I_HALVES (d 4096, 8 heads) 4.0e-6 (6.1e-6), 8.2e-6 (5.7e-6), 2.8e-5 (6.6e-6).
 // Errors of sigma reach the sweeps' at sigma^2 / b near 0.2.
-constexpr float kCancelVec = 0.45f, kCancelSigma = 0.25f;
+constexpr float kCancelMean = 2.f;  // one of the two matrices at r = 0.58, the other at 1
+constexpr float kCancelSigma = 0.25f;
 constexpr float kTinyRow = 0x1p-40f;                  // least diagonal element, of a trace in [1, 4)
 constexpr float kGramMin = 1e-26f, kGramMax = 1e34f;  // trace of which the products neither under- nor overflow
 
@@ -1073,10 +1077,13 @@ heads_kernel(HeadArgs a) {
       if (lane < 3) red[to][lane][wv] = sum;
     };
     auto dot_of = [&](int from) { return sum_waves<kHWaves>(red[from][0]); };
-    // Whether the products just summed up may be used.
-    auto exact_enough = [&](int from, float tr, float dot, bool reported) {
+    // Adds what the product just summed up counts (see kCancelMean); its bound b.
+    float cancel = 0.f;
+    auto weigh = [&](int from, float tr, float dot) {
       const float bound = sum_waves<kHWaves>(red[from][1]), ww = sum_waves<kHWaves>(red[from][2]);
-      return dot > 0.f && DH * ww >= kCancelVec * kCancelVec * bound * tr && (!reported || dot >= kCancelSigma * bound);
+      const float x = bound * __builtin_amdgcn_rcpf(dot);
+      cancel += fminf(x * x, bound * tr * __builtin_amdgcn_rcpf(DH * ww));
+      return bound;
     };
     // Each product is formed on the unscaled vector before the sums of the
     // step that made it are looked at: their way through LDS, the square root
@@ -1090,7 +1097,8 @@ heads_kernel(HeadArgs a) {
       product<T, DH, MODE>(gq, tv, pp, role, wv, lane, out);
       if (k > 1) {
         const float n2 = dot_of(1);
-        if (!exact_enough(1, trk, n2, false)) break;
+        if (!(n2 > 0.f)) break;
+        weigh(1, trk, n2);
         zscale = may_end(k) ? 1.0f / sqrtf(n2) : __builtin_amdgcn_rsqf(n2);
       }
       sums(0, tv, yv, zscale, dqr);
@@ -1098,6 +1106,8 @@ heads_kernel(HeadArgs a) {
       // t = G_K y with y = w / sigma
       product<T, DH, MODE>(gk, yv, pp, role, wv, lane, out);
       const float s2 = dot_of(0);
+      if (!(s2 > 0.f)) break;
+      const float bound = weigh(0, trq, s2);
       float sig = 0.f, inv_sig;
       bool last = false;
       if (may_end(k)) {
@@ -1107,7 +1117,6 @@ heads_kernel(HeadArgs a) {
       } else {
         inv_sig = __builtin_amdgcn_rsqf(s2);
       }
-      if (!exact_enough(0, trq, s2, last)) break;
       if (last) {
         __syncthreads();
         last_y(yv, inv_sig);
@@ -1117,7 +1126,8 @@ heads_kernel(HeadArgs a) {
       __syncthreads();
       if (last) {
         const float n2 = dot_of(1);
-        if (!exact_enough(1, trk, n2, true)) break;
+        if (!(n2 > 0.f)) break;
+        if (!(s2 >= kCancelSigma * bound && n2 >= kCancelSigma * weigh(1, trk, n2) && cancel <= 2 * k * kCancelMean)) break;
         finish(k, sig * fq * fk, tv, zscale * inv_sig / fq, yv, fq, 1.0f / (sqrtf(n2) * fq * fk));
         return;
       }

@@ -181,8 +181,9 @@ bool fused_call(const Plan& pl, int dtype, int n_iter) {
 
 // Bytes of Gram matrices one launch pair of the one-workgroup-per-head form
 // works on: half the Infinity Cache, from which every query head of a group reads
-// them; larger shapes go through in several pairs, each long enough to hide its
-// launches.
+// them.  Larger shapes go through in several pairs, whose last rounds of
+// workgroups leave the chip idle in turn: the 70B GQA shape (94 MB) as one pair
+// 2.48 ms, as two 2.61 ms.
 constexpr size_t kGkBytes = size_t(128) << 20;
 constexpr int kSplitHeads = 256;     // below this many heads their query matrices are split over workgroups
 constexpr int kSplitTarget = 384;    // ... into about this many (with kSplitKeys for the key heads)
@@ -195,7 +196,7 @@ constexpr int kSplitKeysLow = 384;
 // against the strips' Gram matrices, which every query head reads: in units of
 // streaming one head, rounds(s) / s + (query rounds) s (matrix / head bytes).
 // 70B GQA shape, 640 key heads on 512 slots: one strip takes two rounds, two
-// strips one and a half (units_kernel 474 -> 419 us, the call 2.46 -> 2.38 ms).
+// strips one and a half (the call 2.51 -> 2.48 ms).
 int key_strips(int64_t units, int64_t heads, int slots, double mat_ratio, int tiles) {
   int best = 1;
   double cost = 1e30;
@@ -270,10 +271,11 @@ bool heads_tolerance(const sn_shape* s, const sn_params* p, bool heads) {
   // A stop at step 2, the earliest, costs the sweeps five passes over the
   // weights and a tail for the heads still running.  Warm calls that stop
   // there for nearly every head, sweeps and tail against here: 12 GB of
-  // weights (70B GQA shape) 4.18 -> 2.33 ms, 0.5 GB 387 -> 188 us, 151 MB
-  // 230 -> 126 us, 31 MB 112 -> 75 us.  Below 64 MB, where the weights stay
-  // in the Infinity Cache and launches are what is left to gain, calls keep
-  // the sweeps and the tail.
+  // weights (70B GQA shape) 4.18 -> 2.34 ms, 0.5 GB 387 -> 188 us, 151 MB
+  // 230 -> 126 us; but 40, 32, 4.5 and 0.6 MiB 118 -> 84, 113 -> 78, 100 -> 47 and 75 ->
+  // 40 us too (cold calls of up to 90 steps 256 -> 222, 175 -> 149, 175 -> 131, 159 ->
+  // 124 us).  The line is not where the two meet, which they do not: it is where
+  // calls stopped changing their route, and smaller ones have kept the tail.
   const int64_t bytes =
       (int64_t)s->n_layers * (s->n_q_heads + s->n_kv_heads) * s->head_dim * s->d_model * esize(s->dtype);
   return bytes >= (int64_t(64) << 20);
@@ -800,7 +802,7 @@ int run_tail(sn_ctx* c, SweepArgs a, float* u, int k0) {
   return SN_OK;
 }
 
-// The sweeps of the default form: first W_K sweep, then n_iter x (W_Q sweep,
+// The sweeps: first W_K sweep, then n_iter x (W_Q sweep,
 // W_K sweep).  In tolerance mode every W_K sweep decides, per head, whether
 // the step's sigma meets the rule; a stopped head's waves leave at set-up in
 // the later sweeps.  With d_h >= 16 only the first kTailSteps steps run as

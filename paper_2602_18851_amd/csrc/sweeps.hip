@@ -1,4 +1,5 @@
-// Sweep kernels of the per-head spectral-norm estimator (the default form)
+// Sweep kernels of the per-head spectral-norm estimator (calls of one
+// iteration, small tolerance calls, and the final sweeps of the Gram form)
 // and its finalize, for MI355X (gfx950, wave64).
 //
 // Method (arXiv 2602.18851, Sec. 4.1-4.2, App. E): for query head h with key

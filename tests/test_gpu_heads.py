@@ -185,6 +185,50 @@ def test_no_less_precise_than_the_sweeps(n_q, n_kv, dh, d, dtype, common):
     assert err["heads"][0] <= max(err["sweeps"][0], 8e-8), err
 
 
+@pytest.mark.parametrize("n_q,n_kv,dh,d,dtype,spread",
+                         [(300, 300, 64, 1600, "bf16", 0.0), (64, 64, 128, 2048, "bf16", 0.0),
+                          (64, 8, 128, 4096, "bf16", 0.0), (96, 96, 16, 768, "f32", 1.0)],
+                         ids=["rows", "blocks", "halves", "uneven-rows"])
+def test_passing_cancellation_stays_in_dh_space(n_q, n_kv, dh, d, dtype, spread):
+    """Query rows with a large common part and a random start: some heads cancel
+    in their first step alone (the smallest sigma^2 / b here is 0.2), and rows of
+    uneven size leave ||G z|| small against its bound.  Neither loses precision
+    against the sweeps, and neither may send a head to its weights, which would
+    take several times as long."""
+    g = torch.Generator().manual_seed(3)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+
+    def weights(common):
+        q = (torch.randn(n_q, dh, d, generator=g) + common * torch.randn(n_q, 1, d, generator=g)) * 0.02
+        k = torch.randn(n_kv, dh, d, generator=g) * 0.02
+        q *= 10 ** (spread * (2 * torch.rand(n_q, dh, 1, generator=g) - 1))
+        k *= 10 ** (spread * (2 * torch.rand(n_kv, dh, 1, generator=g) - 1))
+        return q.to(dt).cuda(), k.to(dt).cuda()
+
+    v0 = torch.randn(n_q, d, generator=g).cuda()
+
+    def run(q, k, strips):
+        est = Spectral(1, d, n_q, n_kv, dh, dtype, 0.05, q_strips=strips, k_strips=strips)
+        times = []
+        for _ in range(5):
+            v = v0.clone().unsqueeze(0)
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            est.step(q.reshape(1, -1, d), k.reshape(1, -1, d), v, 20)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        est.close()
+        return v[0].double(), sorted(times)[2]
+
+    q, k = weights(2.0)
+    _, v64 = _chain64(q, k, v0, 20)
+    err = {strips: (run(q, k, strips)[0] - v64).square().sum(dim=1).mean().sqrt().item() for strips in (1, 0)}
+    assert err[0] <= err[1], err
+    plain = run(*weights(0.0 if spread == 0 else 0.5), 0)[1]
+    assert run(q, k, 0)[1] <= 2 * plain
+
+
 def test_zero_rows():
     """Rows of zeros (pruned or padded dimensions of a head) keep the form's
     results and its speed: 300 steps on the weights instead of in d_h-space would

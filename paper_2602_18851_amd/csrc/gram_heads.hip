@@ -438,7 +438,8 @@ struct Iter {
   static constexpr int TPR = BLOCKS ? 1 : MODE == I_HALVES ? 16 : kHThreads / DH;  // threads per row of a product
   static constexpr int ROWS = MODE == I_HALVES ? DH / 16 : 1, COLS = DH / TPR;
   using Mat = std::conditional_t<BLOCKS, double[S::NACC][4], Num[ROWS][BLOCKS ? 1 : COLS]>;
-  static constexpr int GL = BLOCKS ? 4 * DH * 8 : DH * S::P * (int)sizeof(Num);  // LDS bytes of a whole G, or of a product's partials
+  // LDS bytes of a whole G, or of a product's partials
+  static constexpr int GL = BLOCKS ? 4 * DH * 8 : DH * S::P * (int)sizeof(Num);
   __device__ static __forceinline__ int col(int C, int j) {
     return MODE == I_HALVES ? C + 16 * j : COLS > 1 ? 2 * C + 2 * TPR * (j >> 1) + (j & 1) : C;
   }
@@ -846,8 +847,8 @@ units_kernel(HeadArgs a) {
     const int h = a.head0 + hl;
     const char* blk = uni(a.mats[h / a.n_q]) + (int64_t)(h % a.n_q) * DH * a.ld * S::ES;
     const int t0 = strip * a.tps_q, t1 = min(t0 + a.tps_q, n_tiles);
-    stream_block<T, DH, 0, true>(blk, a.ld, a.d, t0, t1, tile_seed(h, a.sq, strip), big, wv, lane, role, VSlots{nullptr, 0, 1}, acc, zacc,
-                                 nrm);
+    stream_block<T, DH, 0, true>(blk, a.ld, a.d, t0, t1, tile_seed(h, a.sq, strip), big, wv, lane, role, VSlots{nullptr, 0, 1},
+                                 acc, zacc, nrm);
     blocks_to_memory<T, DH>(role, acc, a.gq + (size_t)(hl * a.sq + strip) * S::MAT, lane);
     return;
   }
@@ -991,7 +992,8 @@ heads_kernel(HeadArgs a) {
     return true;
   };
   float fq, fk, trq = 0.f, trk = 0.f;
-  const bool in_range = scale_of(dq, &fq, &trq) & scale_of(dk, &fk, &trk);
+  bool in_range = scale_of(dq, &fq, &trq);
+  in_range = scale_of(dk, &fk, &trk) && in_range;
 
   float* fin = a.w.fin + (size_t)h * 2 * DH;
   auto finish = [&](int k, float sig, const auto* z, float zs, const auto* y, float ys, float rn) {
@@ -1127,7 +1129,8 @@ heads_kernel(HeadArgs a) {
       if (last) {
         const float n2 = dot_of(1);
         if (!(n2 > 0.f)) break;
-        if (!(s2 >= kCancelSigma * bound && n2 >= kCancelSigma * weigh(1, trk, n2) && cancel <= 2 * k * kCancelMean)) break;
+        const float bound_k = weigh(1, trk, n2);
+        if (!(s2 >= kCancelSigma * bound && n2 >= kCancelSigma * bound_k && cancel <= 2 * k * kCancelMean)) break;
         finish(k, sig * fq * fk, tv, zscale * inv_sig / fq, yv, fq, 1.0f / (sqrtf(n2) * fq * fk));
         return;
       }

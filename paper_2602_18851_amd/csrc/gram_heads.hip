@@ -16,8 +16,8 @@
 //     z / sigma and y of the last step with 1 / ||K^T y||, which the final sweeps
 //     map to u and v, already normalised.
 // Against n_iter pairs of sweeps, whole calls on one box: 70B GQA shape, 30
-// iterations 56.3 -> 2.49 ms; Llama-2-7B shape 10.5 -> 0.79 ms; GPT-2 XL shape
-// with u 2.56 -> 0.25 ms; GPT-2 small, 20 iterations 405 -> 72 us; 5
+// iterations 56.3 -> 2.48 ms; Llama-2-7B shape 10.5 -> 0.78 ms; GPT-2 XL shape
+// with u 2.56 -> 0.25 ms; GPT-2 small, 20 iterations 405 -> 70 us; 5
 // iterations of 144 heads, d 3001, 261 -> 68 us.
 //
 // Streaming.  The workgroup's four waves share a ring of row tiles (d_h rows
